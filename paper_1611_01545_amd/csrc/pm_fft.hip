@@ -612,11 +612,13 @@ constexpr int rows_per_wg() {
 template <int M>
 __global__ __launch_bounds__(rows_per_wg<M>() * Plan<M>::T) void k_row_r2c(
     const float* in, float2* out, float2* nyq, int64_t nrows, const float2* __restrict__ tw,
-    int twmask) {
+    int twmask, unsigned int* amax) {
   using P = Plan<M>;
   constexpr int R = rows_per_wg<M>();
   constexpr int LF = P::E * P::TP;
   __shared__ float lds[R * LF];
+  // the first pass of the force clears the max |a| that its last pass folds into
+  if (amax && blockIdx.x == 0 && threadIdx.x == 0) *amax = 0u;
   // the twiddles in LDS: from global memory the compiler issues most of them one at a
   // time, each waited for (13.2 against 14.5 ms at 2048^3)
   __shared__ float2 stw[2 * M];
@@ -720,114 +722,123 @@ __global__ __launch_bounds__(rows_per_wg<M>() * Plan<M>::T) void k_row_c2r(
 // gradient: D f(x) = n (8 (f(x + 1) - f(x - 1)) - (f(x + 2) - f(x - 2))) / 12 (mesh
 // spacing 1/n, periodic). Its Fourier symbol is i D(k) with the D(k) of the spectral
 // form, so the components equal the three inverse transforms of -i D(k_c) G rho but take
-// one transform of G rho and this pass. A workgroup owns a tile of GX x GY nodes of the
-// (x, y) plane and walks GZ planes along z: each thread keeps a window of five z values
-// of its RPT rows in registers (the z difference), and the current plane, with a halo of
-// two nodes in x and y, is staged in LDS (the x and y differences). Writes the per-block
-// max |a| (float bits) to part[block].
+// one transform of G rho and this pass. Bound by memory (4 n^3 bytes read, 12 n^3
+// written). A thread owns four consecutive x nodes (16-byte loads and stores) of RY
+// neighbouring rows and walks GZ planes along z with a window of five planes in
+// registers; the rows' y and x neighbours in the current plane come through the L1, so
+// there is no LDS tile and no barrier and a wave waits only for its own loads. Folds
+// max |a| into *amax (float bits, cleared by the forward row pass), one atomic per block.
 constexpr int GRAD_T = 256;
+struct GradTile {
+  int xw;       // threads along x (4 nodes each)
+  int yg;       // row groups per workgroup
+  int ry, gz;   // rows per thread, planes per workgroup
+  int threads;
+  int64_t blocks;
+};
+template <int RY, bool NT>
 __global__ __launch_bounds__(GRAD_T) void k_grad4(const float* __restrict__ phi, float* ax,
-                                                  float* ay, float* az, int lgn, int GX,
-                                                  int GY, int GZ, float scale,
-                                                  unsigned int* part) {
-  constexpr int RPT = 8;  // rows of the tile per thread
-  __shared__ float tile[(32 + 4) * (64 + 4)];
-  __shared__ float wmax[GRAD_T / 64];
-  const int64_t n = (int64_t)1 << lgn, n2 = n * n;
-  const uint32_t m = (uint32_t)n - 1u;
-  const int LX = GX + 4;                       // staged row length
-  const int nty = (int)(n / GY), ntx = (int)(n / GX);
-  const int bx = blockIdx.x % ntx, by = (blockIdx.x / ntx) % nty;
-  const int bz = blockIdx.x / (ntx * nty);
-  const int x0 = bx * GX, y0 = by * GY, z0 = bz * GZ;
-  const int nthr = GX * GY / RPT;
-  const int tid = threadIdx.x;
-  const bool act = tid < nthr;
-  const int lx = tid % GX, ly0 = tid / GX;     // rows ly0 + (GY / RPT) r
-  const int ystep = GY / RPT;
-  const uint32_t gx = (uint32_t)(x0 + lx);
-  float w[RPT][5];  // phi at z - 2 .. z + 2 of the thread's rows
-  auto at = [&](uint32_t x, uint32_t y, uint32_t z) {
-    return phi[((int64_t)(z & m) * n + (y & m)) * n + (x & m)];
-  };
-  if (act) {
-#pragma unroll
-    for (int r = 0; r < RPT; ++r)
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        w[r][k + 1] = at(gx, (uint32_t)(y0 + ly0 + ystep * r), (uint32_t)(z0 - 2 + k));
-  }
+                                                  float* ay, float* az, int lgn, GradTile t,
+                                                  float scale, unsigned int* amax) {
+  const uint32_t n = 1u << lgn, m = n - 1u;
+  const uint64_t n2 = (uint64_t)n * n;
+  const uint32_t ntx = n / (4u * t.xw), nty = n / (uint32_t)(t.yg * RY);
+  const uint32_t bx = blockIdx.x % ntx, by = (blockIdx.x / ntx) % nty, bz = blockIdx.x / (ntx * nty);
+  const int lx = threadIdx.x % t.xw, lg = threadIdx.x / t.xw;
   float amx = 0.f;
-  for (int dz = 0; dz < GZ; ++dz) {
-    const uint32_t z = (uint32_t)(z0 + dz);
-    // the window moves on by one plane: z + 2 comes in
-    if (act) {
+  if (lg < t.yg) {
+    const uint32_t x = 4u * (bx * t.xw + lx), y0 = (by * t.yg + lg) * RY;
+    const uint32_t xl = (x - 2u) & m, xr = (x + 4u) & m;
+    auto row = [&](uint32_t y, uint32_t z) { return phi + (((uint64_t)(z & m) << lgn) + (y & m)) * n; };
+    float4 w[RY][5];  // phi at z - 2 .. z + 2
+    const uint32_t z0 = bz * t.gz;
 #pragma unroll
-      for (int r = 0; r < RPT; ++r) {
+    for (int r = 0; r < RY; ++r)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) w[r][k + 1] = *(const float4*)(row(y0 + r, z0 - 2u + k) + x);
+    for (int dz = 0; dz < t.gz; ++dz) {
+      const uint32_t z = z0 + dz;
+      float4 yh[4];  // rows y0 - 2, y0 - 1, y0 + RY, y0 + RY + 1
+      float2 l[RY], rr[RY];
+#pragma unroll
+      for (int r = 0; r < RY; ++r) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) w[r][k] = w[r][k + 1];
-        w[r][4] = at(gx, (uint32_t)(y0 + ly0 + ystep * r), z + 2);
+        w[r][4] = *(const float4*)(row(y0 + r, z + 2u) + x);
       }
-    }
-    __syncthreads();  // the previous plane's tile has been read
-    // plane z into LDS: the tile's own nodes from the windows, the halo from memory
-    if (act) {
 #pragma unroll
-      for (int r = 0; r < RPT; ++r) tile[(ly0 + ystep * r + 2) * LX + lx + 2] = w[r][2];
-    }
-    const int nh = 4 * LX + 4 * GY;  // halo rows (2 above, 2 below) and halo columns
-    for (int i = tid; i < nh; i += GRAD_T) {
-      int ty, tx;
-      if (i < 4 * LX) {
-        const int hr = i / LX;
-        ty = hr < 2 ? hr : GY + hr;  // rows 0, 1 and GY + 2, GY + 3
-        tx = i % LX;
-      } else {
-        const int j = i - 4 * LX;
-        ty = 2 + j / 4;
-        const int hc = j % 4;
-        tx = hc < 2 ? hc : GX + hc;  // columns 0, 1 and GX + 2, GX + 3
+      for (int k = 0; k < 4; ++k) yh[k] = *(const float4*)(row(y0 + (k < 2 ? k - 2 : RY + k - 2), z) + x);
+#pragma unroll
+      for (int r = 0; r < RY; ++r) {
+        const float* q = row(y0 + r, z);
+        l[r] = *(const float2*)(q + xl);
+        rr[r] = *(const float2*)(q + xr);
       }
-      tile[ty * LX + tx] = at((uint32_t)(x0 - 2 + tx), (uint32_t)(y0 - 2 + ty), z);
-    }
-    __syncthreads();
-    if (act) {
+      // row y0 + d of the current plane, d in [-2, RY + 2)
+      auto at = [&](int d) -> const float4& { return d < 0 ? yh[d + 2] : d >= RY ? yh[d - RY + 2] : w[d][2]; };
 #pragma unroll
-      for (int r = 0; r < RPT; ++r) {
-        const int ty = ly0 + ystep * r + 2, tx = lx + 2;
-        const float* c = tile + ty * LX + tx;
-        const float gxv = 8.f * (c[1] - c[-1]) - (c[2] - c[-2]);
-        const float gyv = 8.f * (c[LX] - c[-LX]) - (c[2 * LX] - c[-2 * LX]);
-        const float gzv = 8.f * (w[r][3] - w[r][1]) - (w[r][4] - w[r][0]);
-        const float a0 = -scale * gxv, a1 = -scale * gyv, a2 = -scale * gzv;
-        const int64_t o = (int64_t)z * n2 + (int64_t)(y0 + ly0 + ystep * r) * n + gx;
-        ax[o] = a0;
-        ay[o] = a1;
-        az[o] = a2;
-        amx = fmaxf(amx, fmaxf(fabsf(a0), fmaxf(fabsf(a1), fabsf(a2))));
+      for (int r = 0; r < RY; ++r) {
+        const float4 c = w[r][2];
+        const float p[8] = {l[r].x, l[r].y, c.x, c.y, c.z, c.w, rr[r].x, rr[r].y};
+        float4 o[3];
+        float* ox = &o[0].x;
+        float* oy = &o[1].x;
+        float* oz = &o[2].x;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float gx = 8.f * (p[k + 3] - p[k + 1]) - (p[k + 4] - p[k]);
+          const float gy = 8.f * ((&at(r + 1).x)[k] - (&at(r - 1).x)[k]) -
+                           ((&at(r + 2).x)[k] - (&at(r - 2).x)[k]);
+          const float gz = 8.f * ((&w[r][3].x)[k] - (&w[r][1].x)[k]) -
+                           ((&w[r][4].x)[k] - (&w[r][0].x)[k]);
+          ox[k] = -scale * gx;
+          oy[k] = -scale * gy;
+          oz[k] = -scale * gz;
+          amx = fmaxf(amx, fmaxf(fabsf(ox[k]), fmaxf(fabsf(oy[k]), fabsf(oz[k]))));
+        }
+        const uint64_t i = (uint64_t)z * n2 + (uint64_t)(y0 + r) * n + x;
+        if constexpr (NT) {
+          typedef float v4 __attribute__((ext_vector_type(4)));
+          __builtin_nontemporal_store(*(const v4*)&o[0], (v4*)(ax + i));
+          __builtin_nontemporal_store(*(const v4*)&o[1], (v4*)(ay + i));
+          __builtin_nontemporal_store(*(const v4*)&o[2], (v4*)(az + i));
+        } else {
+          *(float4*)(ax + i) = o[0];
+          *(float4*)(ay + i) = o[1];
+          *(float4*)(az + i) = o[2];
+        }
       }
     }
   }
+  __shared__ float wmax[GRAD_T / 64];
   for (int d = 32; d >= 1; d >>= 1) amx = fmaxf(amx, __shfl_xor(amx, d, 64));
-  if ((tid & 63) == 0) wmax[tid >> 6] = amx;
+  if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = amx;
   __syncthreads();
-  if (tid == 0) {
+  if (threadIdx.x == 0) {
     for (int q = 1; q < (int)(blockDim.x >> 6); ++q) amx = fmaxf(amx, wmax[q]);
-    part[blockIdx.x] = __float_as_uint(amx);
+    // most blocks see a larger maximum already there: a plain read instead of an atomic
+    // (1024 atomics on one word take 10 us)
+    const unsigned int b = __float_as_uint(amx);
+    if (b > __hip_atomic_load(amax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(amax, b);
   }
 }
 
-// tile of the gradient pass at mesh side n: GX x GY nodes, GZ planes per workgroup
-struct GradTile {
-  int gx, gy, gz;
-  int64_t blocks;
-};
+// Rows per thread and planes per workgroup by mesh side, from a sweep of RY = 1, 2, 4 and
+// GZ = 1 .. 64. Small meshes need many short workgroups (one of 64 planes is a chain of 64
+// dependent loads): 64^3 takes 7.9 us at GZ = 2 against 48 at 64 (118 with the LDS tile
+// that this pass had), 128^3 13 against 50 (131). Large ones trade the window's refill (4
+// planes per workgroup) against planes in flight: 256^3 54 us (139 with the LDS tile),
+// 512^3 426 (540), 1024^3 3.38 ms at GZ = 4 with nontemporal stores against 3.63 with
+// plain ones and 3.44 with the LDS tile. At 1024^3 the components are too large for any
+// cache to hold them until the kick reads them; below it they are stored plainly.
 GradTile grad_tile(int64_t n) {
   GradTile t;
-  t.gx = (int)std::min<int64_t>(n, 64);
-  t.gy = (int)std::min<int64_t>(n, 32);
-  t.gz = (int)std::min<int64_t>(n, 64);
-  t.blocks = (n / t.gx) * (n / t.gy) * (n / t.gz);
+  t.xw = (int)std::min<int64_t>(n / 4, 64);
+  t.ry = n >= 256 ? 4 : n >= 128 ? 2 : 1;
+  t.gz = n >= 1024 || n == 128 ? 4 : 2;
+  t.yg = (int)std::min<int64_t>(GRAD_T / t.xw, n / t.ry);
+  t.threads = (t.xw * t.yg + 63) / 64 * 64;
+  t.blocks = (n / (4 * t.xw)) * (n / (t.yg * t.ry)) * (n / t.gz);
   return t;
 }
 
@@ -988,12 +999,12 @@ pm_status col_zconv(const FftCtx& f, int mode, bool blk, const float2* i0, const
 }
 
 template <int M>
-pm_status row_r2c(const FftCtx& f, const float* in, float2* out, float2* nyq) {
+pm_status row_r2c(const FftCtx& f, const float* in, float2* out, float2* nyq, float* amax) {
   constexpr int R = rows_per_wg<M>();
   int64_t nrows = (int64_t)f.n * f.n;
   if (nrows % R) return PM_ERR_SHAPE;
   hipLaunchKernelGGL(k_row_r2c<M>, dim3((unsigned)cdiv(nrows, R)), dim3(R * Plan<M>::T), 0,
-                     f.c->stream, in, out, nyq, nrows, f.c->tw, f.twmask);
+                     f.c->stream, in, out, nyq, nrows, f.c->tw, f.twmask, (unsigned int*)amax);
   PM_LAUNCH_CHECK();
   return PM_OK;
 }
@@ -1044,10 +1055,12 @@ pm_status d_col_zconv(const FftCtx& f, int mode, bool blk, const float2* i0,
   }
   return PM_ERR_SHAPE;
 }
-pm_status d_row_r2c(const FftCtx& f, const float* in, float2* out, float2* nyq) {
+// amax (nullable): a max |a| word to clear
+pm_status d_row_r2c(const FftCtx& f, const float* in, float2* out, float2* nyq,
+                    float* amax = nullptr) {
   switch (f.n) {
 #define CASE(N) \
-  case N: return row_r2c<N / 2>(f, in, out, nyq);
+  case N: return row_r2c<N / 2>(f, in, out, nyq, amax);
     PM_FFT_SIZES(CASE)
 #undef CASE
   }
@@ -1061,16 +1074,6 @@ pm_status d_row_c2r(const FftCtx& f, const float2* in, const float2* nyq, float*
 #undef CASE
   }
   return PM_ERR_SHAPE;
-}
-
-int64_t d_row_blocks(int n) {
-  switch (n) {
-#define CASE(N) \
-  case N: return cdiv((int64_t)N * N, rows_per_wg<N / 2>());
-    PM_FFT_SIZES(CASE)
-#undef CASE
-  }
-  return 0;
 }
 
 // Line descriptors of the z-blocked half spectrum (main, [z/ZB][y][z%ZB][kx < n/2]) and
@@ -1144,7 +1147,7 @@ pm_status build_kernel_table(pm_context* c) {
 //   Z      G F: A1 in place
 //   Y^-1   A1 in place
 //   c2r    phi: A1 -> S
-//   k_grad4  a = -D phi: S -> A0, A1, A2, and the per-block max |a|
+//   k_grad4  a = -D phi: S -> A0, A1, A2, and max |a|
 pm_status run_force(pm_context* c, const float* rho, float* acc, float2* nyq, float* amax) {
   const int n = (int)c->g.ng;
   const int64_t n3 = (int64_t)n * n * n;
@@ -1154,15 +1157,9 @@ pm_status run_force(pm_context* c, const float* rho, float* acc, float2* nyq, fl
   if (!phi) return PM_ERR_NOMEM;
   float2* N0 = nyq;
   pm_status s;
-  const GradTile gt = grad_tile(n);
-  unsigned int* part = nullptr;
-  if (amax) {
-    part = (unsigned int*)scratch(c, SC_PARTS, (size_t)gt.blocks * 4);
-    if (!part) return PM_ERR_NOMEM;
-  }
   {
     ProfScope ps(c, ST_FFT_R2C);
-    if ((s = d_row_r2c(f, rho, A1, N0)) != PM_OK) return s;
+    if ((s = d_row_r2c(f, rho, A1, N0, amax)) != PM_OK) return s;
   }
   const Lines ym = lines_y_main(n), yn = lines_y_nyq(n);
   const Lines zm = lines_z_main(n), zn = lines_z_nyq(n);
@@ -1191,12 +1188,19 @@ pm_status run_force(pm_context* c, const float* rho, float* acc, float2* nyq, fl
   // the three components from the potential by the difference stencil
   {
     ProfScope ps(c, ST_GRAD);
-    hipLaunchKernelGGL(k_grad4, dim3((unsigned)gt.blocks), dim3(GRAD_T), 0, c->stream,
-                       (const float*)phi, acc, acc + n3, acc + 2 * n3, ilog2(n), gt.gx, gt.gy,
-                       gt.gz, (float)((double)n / 12.0), part);
+    const GradTile gt = grad_tile(n);
+    const float scale = (float)((double)n / 12.0);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)gt.blocks), dim3(gt.threads), 0, c->stream,
+                         (const float*)phi, acc, acc + n3, acc + 2 * n3, ilog2(n), gt, scale,
+                         (unsigned int*)amax);
+    };
+    if (n >= 1024) launch(k_grad4<4, true>);
+    else if (gt.ry == 4) launch(k_grad4<4, false>);
+    else if (gt.ry == 2) launch(k_grad4<2, false>);
+    else launch(k_grad4<1, false>);
     PM_LAUNCH_CHECK();
   }
-  if (amax) return fold_max_u32(c, part, gt.blocks, (uint32_t*)amax);
   return PM_OK;
 }
 pm_status run_force_transpose(pm_context* c, float* acc, float2* nyq) {
