@@ -532,13 +532,8 @@ pm_status positions(pm_context* c, const pm_species* sp, int n_sp, int scratch_i
   }
   if (sp[0].layout != PM_COMPRESSED) return PM_OK;
   if (!decode) {
-    for (int i = 0; i < n_sp; ++i) {
-      P.x[i] = nullptr;
-      P.offs[i] = (int64_t*)scratch(c, SC_SPOFF0 + i, (size_t)(c->g.ncell3 + 1) * 8);
-      if (!P.offs[i]) return PM_ERR_NOMEM;
-      if ((s = run_cell_offsets(c, &sp[i], P.offs[i])) != PM_OK) return s;
-    }
-    return PM_OK;
+    for (int i = 0; i < n_sp; ++i) P.x[i] = nullptr;
+    return run_species_offsets(c, sp, n_sp, P.offs);
   }
   size_t bytes = 0;
   for (int i = 0; i < n_sp; ++i) bytes += 2 * align256((size_t)sp[i].n * 12);
@@ -556,11 +551,8 @@ pm_status positions(pm_context* c, const pm_species* sp, int n_sp, int scratch_i
     at += align256((size_t)sp[i].n * 12);
     if ((s = run_decode(c, &sp[i], &dec)) != PM_OK) return s;
     P.x[i] = dec.x;
-    P.offs[i] = (int64_t*)scratch(c, SC_SPOFF0 + i, (size_t)(c->g.ncell3 + 1) * 8);
-    if (!P.offs[i]) return PM_ERR_NOMEM;
-    if ((s = run_cell_offsets(c, &sp[i], P.offs[i])) != PM_OK) return s;
   }
-  return PM_OK;
+  return run_species_offsets(c, sp, n_sp, P.offs);
 }
 
 pm_status deposit_all(pm_context* c, const pm_species* sp, int n_sp, const Positions& P,

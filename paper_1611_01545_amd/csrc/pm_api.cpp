@@ -175,6 +175,7 @@ pm_status pm_query_sizes(const pm_config* cfg, int64_t n_max, int n_sp, pm_sizes
   if (!is_pow2(B) || B > 8 || B > nc) return PM_ERR_SHAPE;
   const int64_t n3 = ng * ng * ng, n2 = ng * ng, h1 = ng / 2 + 1, nc3 = nc * nc * nc;
   const int64_t nb = (nc / B) * (nc / B) * (nc / B), N = n_max;
+  const int64_t NP = N + 8 * n_sp;  // species start at multiples of 8 in the step's arrays
   // grown scratch buffers carry 1/8 headroom
   auto grown = [](int64_t b) { return b + b / 8; };
   *out = pm_sizes{};
@@ -190,16 +191,18 @@ pm_status pm_query_sizes(const pm_config* cfg, int64_t n_max, int n_sp, pm_sizes
   st += grown(3 * n2 * 4);                              // per-row max |a| partials (bound)
   st += n_sp * grown((nc3 + 1) * 8);                    // cell offsets per species
   st += grown((nc3 + 1) * 8);                           // decode/pack offsets
-  st += grown((nb + 1) * 8) + grown(nb * 4);            // re-sort: brick starts and totals
-  st += grown(nc3 * 8 * n_sp);                          // new counts per cell
-  st += grown(nc3 * 4) * 2 + grown((nc3 + 1) * 8);      // escape flags, their scan, counts
-  st += grown(N * 3) + grown(N * 6) + grown(N * 2);     // new codes and digits, old order
-  st += 4 * grown(N * 4);                               // mover keys and indices, two copies
-  st += grown(nb * 4 * n_sp) + grown((nb + 1) * 8);     // movers per brick, their offsets
+  st += grown(n_sp * (nb + 1) * 8) + grown(n_sp * (nb + 1) * 4);  // re-sort: brick starts
+  st += 2 * grown(n_sp * nb * 4) + grown(n_sp * nb * 4 + 16);  // movers, arrivals, escapes
+  st += grown(nc3 * 4 * n_sp);                          // stayers per cell
+  st += grown(nc3 * 4) * 2 + grown((nc3 + 1) * 8);      // encode: runs, counts, escapes
+  st += 2 * grown(NP * 6) + grown(NP * 2);              // new codes and digits, old order
+  st += 4 * grown(NP * 4);                              // sort keys and indices, two copies
   st += grown(std::max<int64_t>(nb * 8 * n_sp, (N / 256 + 1) * 8));  // grid partials
   st += grown(rs_blocks * 256 * 4) + grown((rs_blocks * 256 + 1) * 8);  // radix histograms
-  st += grown((std::max<int64_t>(std::max<int64_t>(nc3, N), rs_blocks * 256) / 4096 + 1) * 8);
-  st += grown(4096) + grown(512 * 25 * 8) + grown(32);  // folds, reductions, mover counts
+  st += grown(std::max<int64_t>(
+      (std::max<int64_t>(n_sp * nc3, std::max<int64_t>(N, rs_blocks * 256)) / 4096 + n_sp) * 8,
+      (nb / 4096 + 1) * n_sp * 24));                    // block sums of the scans
+  st += grown(4096) + grown(512 * 25 * 8);              // folds, reductions
   st += grown(N * 12 + n_sp * 256);                     // extra accelerations (PP, long range)
   out->step_scratch_bytes = st;
   // pm_step_vjp adds the three adjoint meshes, the decoded positions and the recomputed
@@ -306,11 +309,7 @@ static pm_status kick_all(pm_context* c, const pm_species* in, pm_species* out, 
   }
   int64_t* own[4] = {nullptr, nullptr, nullptr, nullptr};
   if (!offs) {
-    for (int i = 0; i < n_sp; ++i) {
-      own[i] = (int64_t*)scratch(c, SC_SPOFF0 + i, (size_t)(c->g.ncell3 + 1) * 8);
-      if (!own[i]) return PM_ERR_NOMEM;
-      if ((s = run_cell_offsets(c, &in[i], own[i])) != PM_OK) return s;
-    }
+    if ((s = run_species_offsets(c, in, n_sp, own)) != PM_OK) return s;
     offs = own;
   }
   return run_kick_compressed_all(c, in, out, n_sp, offs, acc, a_max, ck, cd, perm);
@@ -365,11 +364,7 @@ pm_status pm_step(pm_ctx c, const pm_species* in, pm_species* out, int n_sp, dou
   float* mesh = c->mesh;
   if (in[0].layout == PM_COMPRESSED) {
     int64_t* offs[4] = {nullptr, nullptr, nullptr, nullptr};
-    for (int i = 0; i < n_sp; ++i) {
-      offs[i] = (int64_t*)scratch(c, SC_SPOFF0 + i, (size_t)(c->g.ncell3 + 1) * 8);
-      if (!offs[i]) return PM_ERR_NOMEM;
-      if ((s = run_cell_offsets(c, &in[i], offs[i])) != PM_OK) return s;
-    }
+    if ((s = run_species_offsets(c, in, n_sp, offs)) != PM_OK) return s;
     if ((s = run_deposit_tile(c, in, n_sp, offs, mesh)) != PM_OK) return s;
     if ((s = run_force(c, mesh, mesh, c->nyq, c->amax)) != PM_OK) return s;
     return kick_all(c, in, out, n_sp, mesh, c->amax, dt, dt, offs);
@@ -389,12 +384,8 @@ pm_status pm_pp_accel(pm_ctx c, const pm_species* sp, int n_sp, double r_soft,
     if (sp[i].n > 0 && !app[i]) return PM_ERR_ARG;
   }
   int64_t* offs[4] = {nullptr, nullptr, nullptr, nullptr};
-  pm_status s;
-  for (int i = 0; i < n_sp; ++i) {
-    offs[i] = (int64_t*)scratch(c, SC_SPOFF0 + i, (size_t)(c->g.ncell3 + 1) * 8);
-    if (!offs[i]) return PM_ERR_NOMEM;
-    if ((s = run_cell_offsets(c, &sp[i], offs[i])) != PM_OK) return s;
-  }
+  const pm_status s = run_species_offsets(c, sp, n_sp, offs);
+  if (s != PM_OK) return s;
   return run_pp_accel(c, sp, n_sp, offs, r_soft, app, app_max ? app_max : c->amax + 1);
 }
 
@@ -409,12 +400,8 @@ pm_status pm_step_pp(pm_ctx c, const pm_species* in, pm_species* out, int n_sp, 
   float* mesh = c->mesh;
   int64_t* offs[4] = {nullptr, nullptr, nullptr, nullptr};
   size_t bytes = 0;
-  for (int i = 0; i < n_sp; ++i) {
-    offs[i] = (int64_t*)scratch(c, SC_SPOFF0 + i, (size_t)(c->g.ncell3 + 1) * 8);
-    if (!offs[i]) return PM_ERR_NOMEM;
-    if ((s = run_cell_offsets(c, &in[i], offs[i])) != PM_OK) return s;
-    bytes += ((size_t)in[i].n * 12 + 255) & ~(size_t)255;
-  }
+  for (int i = 0; i < n_sp; ++i) bytes += ((size_t)in[i].n * 12 + 255) & ~(size_t)255;
+  if ((s = run_species_offsets(c, in, n_sp, offs)) != PM_OK) return s;
   char* pool = (char*)scratch(c, SC_PPACC, bytes);
   if (!pool) return PM_ERR_NOMEM;
   float* app[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -440,12 +427,8 @@ pm_status pm_interp_accel(pm_ctx c, const pm_species* sp, int n_sp, const float*
     if (sp[i].n > 0 && !out[i]) return PM_ERR_ARG;
   }
   int64_t* offs[4] = {nullptr, nullptr, nullptr, nullptr};
-  pm_status s;
-  for (int i = 0; i < n_sp; ++i) {
-    offs[i] = (int64_t*)scratch(c, SC_SPOFF0 + i, (size_t)(c->g.ncell3 + 1) * 8);
-    if (!offs[i]) return PM_ERR_NOMEM;
-    if ((s = run_cell_offsets(c, &sp[i], offs[i])) != PM_OK) return s;
-  }
+  const pm_status s = run_species_offsets(c, sp, n_sp, offs);
+  if (s != PM_OK) return s;
   return run_interp_accel(c, sp, n_sp, offs, acc, out, accumulate);
 }
 
@@ -462,12 +445,8 @@ pm_status pm_step_p3m(pm_ctx f, pm_ctx cc, const pm_species* in, pm_species* out
   // cell offsets depend on the counts, n_cell and brick only: the pair shares them
   int64_t* offs[4] = {nullptr, nullptr, nullptr, nullptr};
   size_t bytes = 0;
-  for (int i = 0; i < n_sp; ++i) {
-    offs[i] = (int64_t*)scratch(f, SC_SPOFF0 + i, (size_t)(f->g.ncell3 + 1) * 8);
-    if (!offs[i]) return PM_ERR_NOMEM;
-    if ((s = run_cell_offsets(f, &in[i], offs[i])) != PM_OK) return s;
-    bytes += ((size_t)in[i].n * 12 + 255) & ~(size_t)255;
-  }
+  for (int i = 0; i < n_sp; ++i) bytes += ((size_t)in[i].n * 12 + 255) & ~(size_t)255;
+  if ((s = run_species_offsets(f, in, n_sp, offs)) != PM_OK) return s;
   char* pool = (char*)scratch(f, SC_LRACC, bytes > 0 ? bytes : 256);
   if (!pool) return PM_ERR_NOMEM;
   float* app[4] = {nullptr, nullptr, nullptr, nullptr};

@@ -122,20 +122,11 @@ __global__ __launch_bounds__(T256) void k_run_counts(const uint32_t* keys_sorted
   if (j == n - 1 || keys_sorted[j + 1] != k) count32[k] = (uint32_t)(j + 1 - run_start[k]);
 }
 
-// Full count -> u8 byte and escape flag (count >= 255).
-struct CountSrc {
-  const uint32_t* c32;
-  const uint64_t* c64;
-  __device__ uint32_t operator()(int64_t i) const {
-    return c32 ? c32[i] : (uint32_t)(c64[i] & 0xffffffffull);
-  }
-};
-
 // Per block of T256 cells: the byte counts, and the block's number of escapes in bcnt.
-__global__ __launch_bounds__(T256) void k_count_bytes(CountSrc src, int64_t ncell,
+__global__ __launch_bounds__(T256) void k_count_bytes(const uint32_t* src, int64_t ncell,
                                                      uint8_t* count, uint32_t* bcnt) {
   const int64_t i = (int64_t)blockIdx.x * T256 + threadIdx.x;
-  const uint32_t c = i < ncell ? src(i) : 0u;
+  const uint32_t c = i < ncell ? src[i] : 0u;
   if (i < ncell) count[i] = (uint8_t)(c >= 255u ? 255u : c);
   const int ne = __syncthreads_count(c >= 255u);
   if (threadIdx.x == 0) bcnt[blockIdx.x] = (uint32_t)ne;
@@ -144,7 +135,7 @@ __global__ __launch_bounds__(T256) void k_count_bytes(CountSrc src, int64_t ncel
 // The escape table in cell order: one thread per block of T256 cells writes that block's
 // escapes from boff[b] (the exclusive prefix of the block counts, boff[nb] the total);
 // blocks without escapes, nearly all of them, read one word.
-__global__ __launch_bounds__(T256) void k_escapes(CountSrc src, int64_t ncell, int64_t nb,
+__global__ __launch_bounds__(T256) void k_escapes(const uint32_t* src, int64_t ncell, int64_t nb,
                                                  const uint32_t* bcnt, const int64_t* boff,
                                                  uint64_t* esc, int64_t cap, pm_shdr* h,
                                                  DevErr* err) {
@@ -158,7 +149,7 @@ __global__ __launch_bounds__(T256) void k_escapes(CountSrc src, int64_t ncell, i
   int64_t k = boff[b];
   const int64_t i1 = min((b + 1) * T256, ncell);
   for (int64_t i = b * T256; i < i1; ++i) {
-    const uint32_t c = src(i);
+    const uint32_t c = src[i];
     if (c >= 255u) {
       if (k < cap) {
         esc[2 * k] = (uint64_t)i;
@@ -167,10 +158,6 @@ __global__ __launch_bounds__(T256) void k_escapes(CountSrc src, int64_t ncell, i
       ++k;
     }
   }
-}
-
-__global__ void k_check_total(const int64_t* off, int64_t ncell, int64_t n, DevErr* err) {
-  if (off[ncell] != n) latch_error(err, ERRBIT_CORRUPT);
 }
 
 __device__ inline int64_t find_cell(const int64_t* off, int64_t ncell, int64_t j) {
@@ -470,36 +457,46 @@ __global__ void k_reduce_final(const double* pmesh, int nmesh_part, double cell_
 
 }  // namespace
 
+// cell offsets of compressed streams and the check that the counts sum to n; bsum
+// (nullable) holds the scan's block sums
+static pm_status scan_counts_into(pm_context* c, const pm_species* sp, int n_sp,
+                                  int64_t* const* off, int64_t* bsum) {
+  ScanArgs<GetCount> A{};
+  for (int s = 0; s < n_sp; ++s) {
+    A.g[s] = GetCount{sp[s].count, sp[s].esc, sp[s].hdr};
+    A.out[s] = off[s];
+    A.want[s] = sp[s].n;
+  }
+  A.err = c->err;
+  return scan_batch(c, A, n_sp, c->g.ncell3, bsum);
+}
+
 pm_status run_cell_offsets(pm_context* c, const pm_species* sp, int64_t* off) {
   ProfScope ps(c, ST_OFFSETS);
-  return scan_counts_into(c, sp, off, nullptr);
+  return scan_counts_into(c, sp, 1, &off, nullptr);
 }
 
-// cell offsets of a compressed stream and the check that the counts sum to n; bsum
-// (nullable) holds the scan's block sums
-pm_status scan_counts_into(pm_context* c, const pm_species* sp, int64_t* off, int64_t* bsum) {
-  pm_status s = scan_generic(c, GetCount{sp->count, sp->esc, sp->hdr}, c->g.ncell3, off, bsum);
-  if (s != PM_OK) return s;
-  hipLaunchKernelGGL(k_check_total, dim3(1), dim3(1), 0, c->stream, off, c->g.ncell3, sp->n,
-                     c->err);
-  PM_LAUNCH_CHECK();
-  return PM_OK;
+pm_status run_species_offsets(pm_context* c, const pm_species* sp, int n_sp, int64_t** offs) {
+  for (int s = 0; s < n_sp; ++s) {
+    offs[s] = (int64_t*)scratch(c, SC_SPOFF0 + s, (size_t)(c->g.ncell3 + 1) * 8);
+    if (!offs[s]) return PM_ERR_NOMEM;
+  }
+  ProfScope ps(c, ST_OFFSETS);
+  return scan_counts_into(c, sp, n_sp, offs, nullptr);
 }
 
-pm_status run_finalize_counts(pm_context* c, const uint32_t* cnt32, const uint64_t* cnt64,
-                              pm_species* out) {
+pm_status run_finalize_counts(pm_context* c, const uint32_t* cnt32, pm_species* out) {
   const int64_t nc3 = c->g.ncell3;
   const int64_t nb = cdiv(nc3, T256);  // blocks of T256 cells
   uint32_t* bcnt = (uint32_t*)scratch(c, SC_FLAG, (size_t)nb * 4);
   int64_t* boff = (int64_t*)scratch(c, SC_FOFF, (size_t)(nb + 1) * 8);
   if (!bcnt || !boff) return PM_ERR_NOMEM;
-  CountSrc src{cnt32, cnt64};
-  hipLaunchKernelGGL(k_count_bytes, dim3((unsigned)nb), dim3(T256), 0, c->stream, src, nc3,
+  hipLaunchKernelGGL(k_count_bytes, dim3((unsigned)nb), dim3(T256), 0, c->stream, cnt32, nc3,
                      out->count, bcnt);
   PM_LAUNCH_CHECK();
   pm_status s = scan_u32(c, bcnt, nb, boff);
   if (s != PM_OK) return s;
-  hipLaunchKernelGGL(k_escapes, dim3((unsigned)cdiv(nb, T256)), dim3(T256), 0, c->stream, src,
+  hipLaunchKernelGGL(k_escapes, dim3((unsigned)cdiv(nb, T256)), dim3(T256), 0, c->stream, cnt32,
                      nc3, nb, bcnt, boff, out->esc, out->cap_esc, out->hdr, c->err);
   PM_LAUNCH_CHECK();
   return PM_OK;
@@ -549,7 +546,7 @@ pm_status run_encode(pm_context* c, const pm_species* in, pm_species* out, int64
     PM_LAUNCH_CHECK();
     if ((s = fold_minmax_to_header(c, part, part + nb, nb, out->hdr)) != PM_OK) return s;
   }
-  return run_finalize_counts(c, cnt32, nullptr, out);
+  return run_finalize_counts(c, cnt32, out);
 }
 
 pm_status run_decode(pm_context* c, const pm_species* in, pm_species* out) {
@@ -636,7 +633,7 @@ pm_status reduce_core(pm_context* c, const pm_species* sp, int n_sp, const float
     if (sp[s].layout == PM_COMPRESSED) {
       int64_t* off = off_of(s);
       if (!off) return PM_ERR_NOMEM;
-      pm_status st = scan_counts_into(c, &sp[s], off, bsum);
+      pm_status st = scan_counts_into(c, &sp[s], 1, &off, bsum);
       if (st != PM_OK) return st;
       rs.off = off;
     }

@@ -153,8 +153,8 @@ struct ProfScope {
 
 enum ScratchId {
   SC_OFF = 0,      // int64 [ncell3+1] cell offsets (species A)
-  SC_OFF2,         // int64 [nbrick+1] first new stream position of each brick (re-sort)
-  SC_CNT,          // uint64 [ncell3] counts (stay | arrivals-before << 32)
+  SC_OFF2,         // int64 [nbrick+1] per species: first new stream position of each brick
+  SC_CNT,          // uint32 [ncell3] per species: stayers of each cell (re-sort)
   SC_BSUM,         // int64 block sums for scans
   SC_KEYA,         // uint32 [N]
   SC_VALA,         // uint32 [N]
@@ -165,8 +165,8 @@ enum ScratchId {
   SC_TPOS,         // uint8 [N][3]
   SC_TVEL,         // uint16 [N][3]
   SC_TDST,         // uint32 [N]
-  SC_MCNT,         // uint32 [nbrick] movers per brick
-  SC_MOFF,         // int64 [nbrick+1]
+  SC_MCNT,         // uint32 [nbrick] per species: movers of each brick
+  SC_ASTART,       // uint32 [nbrick+1] per species: first arrival of each brick
   SC_ACC64,        // uint64 [ng^3] fixed-point accumulator (float layout deposit)
   SC_FLAG,         // uint32: escape counts per block of cells / misc
   SC_FOFF,         // int64: their offsets / misc
@@ -182,11 +182,11 @@ enum ScratchId {
   SC_PARTS,        // per-workgroup partial results of grid reductions
   SC_SPEC,         // float [ng^3] spectrum scratch of the force transforms
   SC_FOLD,         // first-stage results of the grid min / max folds
-  SC_NMOV,         // int64 [4]: mover count of each species (device-side)
+  SC_ECNT,         // uint32 [nbrick] per species: escapes of each brick, then 4 totals
   SC_PPMAX,        // per-workgroup max |a| of the PP force
   SC_PPACC,        // float [N][3] PP accelerations of pm_step_pp
   SC_LRACC,        // float [N][3] long-range accelerations of pm_step_p3m
-  SC_BTOT,         // uint32 [nbrick] new particles per brick (re-sort)
+  SC_ACNT,         // uint32 [nbrick] per species: arrivals of each brick (re-sort)
   SC_N
 };
 
@@ -213,27 +213,19 @@ pm_status launch_fill_u64(pm_context* c, uint64_t* p, int64_t n, uint64_t v);
 pm_status run_iota(pm_context* c, int64_t* p, int64_t n);  // p[i] = i
 // exclusive scans into int64 out[n+1]
 pm_status scan_u32(pm_context* c, const uint32_t* in, int64_t n, int64_t* out);
-pm_status scan_u64lo(pm_context* c, const uint64_t* in, int64_t n, int64_t* out);
-pm_status scan_counts(pm_context* c, const uint8_t* count, const uint64_t* esc,
-                      const pm_shdr* hdr, int64_t n, int64_t* out);
 // stable LSD radix sort of (key, val) pairs on the low `bits` of key; results land in
 // *keys/*vals (which may be swapped with the alternate buffers).
 pm_status radix_sort_pairs(pm_context* c, uint32_t** keys, uint32_t** vals,
                            uint32_t** keys_alt, uint32_t** vals_alt, int64_t n,
                            int bits);
-// the same with the pair count read on the device (*n_dev <= n_max): nothing waits on
-// the host for a count the device produced
-pm_status radix_sort_pairs_dev(pm_context* c, uint32_t** keys, uint32_t** vals,
-                               uint32_t** keys_alt, uint32_t** vals_alt, int64_t n_max,
-                               const int64_t* n_dev, int bits);
-
 // codec (pm_codec.hip)
 pm_status run_encode(pm_context* c, const pm_species* in, pm_species* out, int64_t* perm);
 pm_status run_decode(pm_context* c, const pm_species* in, pm_species* out);
 pm_status run_cell_offsets(pm_context* c, const pm_species* sp, int64_t* off);
-pm_status scan_counts_into(pm_context* c, const pm_species* sp, int64_t* off, int64_t* bsum);
-pm_status run_finalize_counts(pm_context* c, const uint32_t* cnt32, const uint64_t* cnt64,
-                              pm_species* out);
+// cell offsets of n_sp compressed species in one scan, in the context's buffers
+// (SC_SPOFF0 + s), whose addresses go to offs
+pm_status run_species_offsets(pm_context* c, const pm_species* sp, int n_sp, int64_t** offs);
+pm_status run_finalize_counts(pm_context* c, const uint32_t* cnt32, pm_species* out);
 pm_status run_pack(pm_context* c, const pm_species* sp, int32_t sid, uint8_t* buf,
                    int64_t cap, int64_t* used);
 pm_status run_reduce(pm_context* c, const pm_species* sp, int n_sp, const float* rho,
@@ -278,9 +270,6 @@ pm_status run_interp_accel(pm_context* c, const pm_species* sp, int n_sp,
                            int64_t* const* offs, const float* acc, float* const* out,
                            int accumulate);
 bool split_pair_ok(const pm_context* fine, const pm_context* coarse);
-pm_status run_kick_compressed(pm_context* c, const pm_species* in, pm_species* out,
-                              const float* acc, const float* amax, double ck, double cd,
-                              uint32_t* perm_new_to_old);
 
 // adjoint (pm_adjoint.hip)
 pm_status run_step_vjp(pm_context* c, const pm_species* in, int n_sp, double dt,

@@ -349,12 +349,8 @@ pm_status run_deposit(pm_context* c, const pm_species* sp, int n_sp, float* rho)
     if (sp[s].layout != layout) return PM_ERR_ARG;
   if (layout == PM_COMPRESSED) {
     int64_t* offs[MAX_SP];
-    for (int s = 0; s < n_sp; ++s) {
-      offs[s] = (int64_t*)scratch(c, SC_SPOFF0 + s, (size_t)(g.ncell3 + 1) * 8);
-      if (!offs[s]) return PM_ERR_NOMEM;
-      pm_status st = run_cell_offsets(c, &sp[s], offs[s]);
-      if (st != PM_OK) return st;
-    }
+    const pm_status st = run_species_offsets(c, sp, n_sp, offs);
+    if (st != PM_OK) return st;
     return run_deposit_tile(c, sp, n_sp, offs, rho);
   }
   // float layout

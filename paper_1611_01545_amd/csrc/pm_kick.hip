@@ -3,10 +3,11 @@
 // cell order (Sec. 2.4: particles are written cell by cell).
 //
 // Compressed path, per species:
-//   k_vmax_next     v_max' = smallest power of two >= V + |c_k| A_max (V: largest
+//   k_kick_prep     v_max' = smallest power of two >= V + |c_k| A_max (V: largest
 //                   decoded |v| of the input, from its extreme velocity codes; A_max:
 //                   largest |a| on the mesh). Interpolation is a convex combination of
-//                   mesh values, so no kicked component exceeds the bound.
+//                   mesh values, so no kicked component exceeds the bound. Clears the
+//                   re-sort's counters.
 //   k_kick_pair     two bricks adjacent along x per workgroup (R = 16 nodes per brick
 //   k_kick_brick    side), or one brick of any shape: the force nodes staged in LDS,
 //                   then waves take 64-particle chunks independently (no barrier):
@@ -14,18 +15,18 @@
 //                   drift u' = u + floor(v' c_d S + 1/2), new codes, and the digit: the
 //                   new cell inside the brick, or B^3 for a particle that leaves it (a
 //                   "mover", whose new cell key is kept). Stayers are counted per new
-//                   cell and movers per brick with LDS atomics.
-//   movers          compacted in old order (ballots over the digits, one wave per
-//                   brick), stably radix-sorted by new cell.
-//   k_arrivals      per new cell: arrivals, and how many of them come from earlier
-//                   bricks (they precede the cell's stayers in stream order);
-//   k_brick_arrivals  per brick, its run of the sorted movers (its arrivals).
-//   scan            new cell offsets.
-//   k_place_stayers stayers and arrivals written at their final stream positions, per
-//                   brick by one wave: the stayers' first position in each new cell
-//                   staged in LDS and their stable rank from a multi-split of the
-//                   digits, then the brick's arrivals, so that one wave writes all of the
-//                   brick's output range.
+//                   cell and movers per brick with LDS atomics, arrivals per brick with
+//                   global ones.
+//   k_brick_scan    first new stream position and first arrival of each brick.
+//   k_list_arrivals the movers into their new bricks' lists, unordered.
+//   k_place         per brick: its arrivals sorted by old index, then arrivals from
+//                   earlier bricks, stayers and arrivals from later bricks written at
+//                   their final stream positions, and the new count bytes.
+//   k_escape_table  the cells of 255 particles and more.
+// Seven launches for all species, whatever the mesh. The movers are few (1% of the
+// neutrinos at the large workload), so grouping them by brick with one atomic each and
+// sorting each brick's handful in LDS replaces a device-wide radix sort by cell: at
+// 64^3 its 60 small launches took 170 of the step's 275 us.
 #include <type_traits>
 
 #include "pm_codec.h"
@@ -80,11 +81,25 @@ __global__ __launch_bounds__(KT) void k_kick_float(const float* x, const float* 
 }
 
 // ------------------------------------------------------- compressed layout --
+constexpr int MAXSP = 4;
+
+struct PrepArgs {
+  const pm_shdr* hin[MAXSP];
+  pm_shdr* hout[MAXSP];
+  int64_t n[MAXSP];
+  int n_sp;
+};
 template <int VB = 2>  // velocity bytes per axis
-__global__ void k_vmax_next(const pm_shdr* hin, pm_shdr* hout, const float* amax, double ck,
-                            int64_t n) {
+__global__ __launch_bounds__(KT) void k_kick_prep(PrepArgs A, const float* amax, double ck,
+                                                 uint32_t* acnt, int64_t nacnt,
+                                                 uint32_t* nesc) {
+  for (int64_t i = (int64_t)blockIdx.x * KT + threadIdx.x; i < nacnt; i += (int64_t)gridDim.x * KT)
+    acnt[i] = 0u;
+  if (blockIdx.x || (int)threadIdx.x >= A.n_sp) return;
+  const pm_shdr* hin = A.hin[threadIdx.x];
+  pm_shdr* hout = A.hout[threadIdx.x];
   double V = 0.0;
-  if (n > 0 && hin->j_max >= 0) {
+  if (A.n[threadIdx.x] > 0 && hin->j_max >= 0) {
     double a = fabs((double)vel_decode_v<VB>((uint32_t)hin->j_min, hin->v_max));
     double b = fabs((double)vel_decode_v<VB>((uint32_t)hin->j_max, hin->v_max));
     V = a > b ? a : b;
@@ -102,11 +117,11 @@ __global__ void k_vmax_next(const pm_shdr* hin, pm_shdr* hout, const float* amax
   hout->flags = 0;
   hout->n_esc = 0;
   hout->reserved = 0;
+  nesc[threadIdx.x] = 0u;
 }
 
 constexpr int KB = 512;  // threads per workgroup of the brick kicks
 constexpr int NWK = KB / 64;
-constexpr int MAXSP = 4;
 
 struct KickSpecies {
   int64_t n;
@@ -119,8 +134,9 @@ struct KickSpecies {
   void* tvel;
   uint16_t* tdig;      // new local cell in the brick, or B^3 for movers
   uint32_t* mkey;      // movers: new cell key, at the old stream index
-  uint64_t* cnt;       // per cell: stayers (low 32 bits)
+  uint32_t* cnt;       // stayers per cell
   uint32_t* mcnt;      // movers per brick
+  uint32_t* acnt;      // arrivals per brick
   int32_t* pmn;        // per-brick extreme new velocity codes, folded into hout
   int32_t* pmx;
   const float* app;    // nullable: per-particle acceleration added to the mesh force
@@ -238,8 +254,10 @@ __device__ inline void kick_lane(const KickSpecies& S, const KickArgs& A, const 
       atomicAdd(&run[digit], 1u);
     } else {
       S.tdig[j] = (uint16_t)B3;
-      S.mkey[j] = cell_key(g, un[0] >> SH, un[1] >> SH, un[2] >> SH);
+      const uint32_t key = cell_key(g, un[0] >> SH, un[1] >> SH, un[2] >> SH);
+      S.mkey[j] = key;
       atomicAdd(mvc, 1u);
+      atomicAdd(&S.acnt[key >> (3 * g.lgB)], 1u);
     }
   }
 }
@@ -464,7 +482,7 @@ __global__ __launch_bounds__(KB) void k_kick_brick(KickArgs A, Geom g, DevErr* e
   __syncthreads();
   for (int i = threadIdx.x; i < n_sp * L; i += KB) {
     const int s = i / L, l = i - s * L;
-    if (l < B3) A.sp[s].cnt[kbase + l] = (uint64_t)run[i];
+    if (l < B3) A.sp[s].cnt[kbase + l] = run[i];
   }
   if ((int)threadIdx.x < n_sp) {
     const int s = threadIdx.x;
@@ -697,7 +715,7 @@ __global__ __launch_bounds__(NT, 4) void k_kick_pair(KickArgs A, Geom g, DevErr*
   for (int i = threadIdx.x; i < 2 * MAXSP * L; i += KB) {
     const int k = i / (MAXSP * L), rem = i - k * (MAXSP * L);
     const int s = rem / L, l = rem - s * L;
-    if (s < n_sp && l < B3) A.sp[s].cnt[kb0 + k * B3 + l] = (uint64_t)run[i];
+    if (s < n_sp && l < B3) A.sp[s].cnt[kb0 + k * B3 + l] = run[i];
   }
   if ((int)threadIdx.x < 2 * n_sp) {
     const int k = threadIdx.x / n_sp, s = threadIdx.x - k * n_sp;
@@ -708,136 +726,468 @@ __global__ __launch_bounds__(NT, 4) void k_kick_pair(KickArgs A, Geom g, DevErr*
   if (bad) latch_error(err, ERRBIT_RANGE);
 }
 
-__device__ inline int64_t lower_bound_u32(const uint32_t* a, int64_t lo, int64_t hi, uint32_t v) {
-  while (lo < hi) {
-    int64_t mid = (lo + hi) >> 1;
-    if (a[mid] < v) lo = mid + 1; else hi = mid;
-  }
-  return lo;
-}
+// ----------------------------------------------------------------- re-sort --
+// Every kernel of the re-sort takes all species in one launch (grid.y).
+struct PlaceSpecies {
+  int64_t n;
+  const int64_t* off;      // old cell offsets [ncell3 + 1]
+  const uint16_t* tdig;    // per particle: new local cell, or B^3 for movers
+  const uint32_t* mkey;    // movers: new cell key, at the old stream index
+  const void* tpos;        // new codes, old stream order
+  const void* tvel;
+  uint32_t* cnt;           // stayers per cell; the new count of cells of 255 and more
+  const uint32_t* mcnt;    // movers per brick
+  uint32_t* acnt;          // arrivals per brick (counted down to 0 as they are listed)
+  const int32_t* pmn;      // per-brick extreme new velocity codes
+  const int32_t* pmx;
+  int64_t* bstart;         // first new stream position of each brick [nbrick + 1]
+  uint32_t* astart;        // first arrival of each brick [nbrick + 1]
+  uint32_t* aidx;          // old stream indices of the arrivals, by brick
+  uint32_t* abuf;          // the same size, for sorting long lists
+  uint32_t* ecnt;          // cells of 255 and more per brick
+  uint32_t* nesc;          // their total
+  pm_shdr* hout;
+  void* pos;
+  void* vel;
+  uint8_t* count;
+  uint64_t* esc;
+  int64_t cap_esc;
+  int64_t* perm;           // nullable: new stream position -> old
+};
+struct PlaceArgs {
+  PlaceSpecies sp[MAXSP];
+};
 
-// astart[b] = first sorted mover whose new cell lies in brick b or later, b in [0, nbrick]:
-// the arrivals of brick b are the sorted movers [astart[b], astart[b + 1]).
-// The mover count nm is read on the device (*nmd): the host never waits for it.
-__global__ __launch_bounds__(KT) void k_brick_arrivals(const uint32_t* skey, const int64_t* nmd,
-                                                      int B3, int64_t nbrick, int64_t* astart) {
-  const int64_t b = (int64_t)blockIdx.x * KT + threadIdx.x;
-  if (b > nbrick) return;
-  astart[b] = lower_bound_u32(skey, 0, *nmd, (uint32_t)(b * B3));
-}
+// First new stream position and first arrival of every brick: exclusive prefixes of the
+// bricks' new particle counts (old particles less movers plus arrivals) and of their
+// arrivals. One launch up to BS_TILE bricks; beyond that k_brick_sums first leaves each
+// block's sums, and a block of k_brick_scan adds up those before its own. The extreme
+// velocity codes ride along and end in the header.
+constexpr int BS_T = 1024, BS_I = 4, BS_TILE = BS_T * BS_I;
+struct BrickSum {
+  int64_t tot, arr;
+  int32_t mn, mx;
+};
 
-// per group of sorted movers with the same new cell: add arrivals (low 32 bits) and
-// arrivals from earlier bricks (high 32 bits) to the cell's count. A fixed grid strides
-// over the nm sorted movers.
-__global__ __launch_bounds__(KT) void k_arrivals(const uint32_t* skey, const uint32_t* sidx,
-                                                const int64_t* nmd, const int64_t* off_in,
-                                                int B3, uint64_t* cnt) {
-  const int64_t nm = *nmd;
-  for (int64_t s = (int64_t)blockIdx.x * KT + threadIdx.x; s < nm;
-       s += (int64_t)gridDim.x * KT) {
-    const uint32_t k = skey[s];
-    if (s > 0 && skey[s - 1] == k) continue;  // group leader only
-    const int64_t ge = lower_bound_u32(skey, s, nm, k + 1);
-    const int64_t bstart = off_in[(int64_t)(k / (uint32_t)B3) * B3];  // first old index of the cell's brick
-    const int64_t nb = lower_bound_u32(sidx, s, ge, (uint32_t)bstart) - s;
-    atomicAdd((unsigned long long*)&cnt[k],
-              (unsigned long long)(((uint64_t)nb << 32) | (uint64_t)(ge - s)));
-  }
-}
-
-// The two re-sort kernels below give each brick one wave (WB bricks per workgroup) and
-// take its particles in chunks of 64, PU chunks' loads issued together; ranks come from
-// ballots and a running count per wave, so no kernel has a barrier.
-constexpr int WB = 4;
-constexpr int PU = 4;
-
-// Movers of brick b, in old stream order, to [moff[b], moff[b] + mcnt[b]).
-__global__ __launch_bounds__(64 * WB) void k_compact_movers(
-    const int64_t* off, const uint32_t* mcnt, const int64_t* moff, int B3, int64_t nbrick,
-    int64_t n, const uint16_t* tdig, const uint32_t* mkey, uint32_t* okey, uint32_t* oidx) {
-  const int lane = threadIdx.x & 63;
-  const int64_t b = (int64_t)blockIdx.x * WB + (threadIdx.x >> 6);
-  if (b >= nbrick || mcnt[b] == 0) return;  // the whole wave
-  const uint64_t lt = lane ? ((~0ull) >> (64 - lane)) : 0ull;
-  const int64_t j0 = min(off[b * B3], n), j1 = min(off[b * B3 + B3], n);
-  int64_t dst = moff[b];
-  for (int64_t base = j0; base < j1; base += 64 * PU) {
-    uint32_t d[PU];
+__device__ inline void brick_items(const PlaceSpecies& S, int B3, int64_t nbrick, int64_t b0,
+                                   uint32_t t[BS_I], uint32_t a[BS_I], int& mn, int& mx) {
+  mn = 65536;
+  mx = -1;
 #pragma unroll
-    for (int u = 0; u < PU; ++u) {
-      const int64_t j = base + 64 * u + lane;
-      d[u] = j < j1 ? tdig[j] : 0u;
-    }
-#pragma unroll
-    for (int u = 0; u < PU; ++u) {
-      const int64_t j = base + 64 * u + lane;
-      const bool m = j < j1 && d[u] == (uint32_t)B3;
-      const uint64_t bal = __ballot(m);
-      if (m) {
-        const int64_t o = dst + __popcll(bal & lt);
-        okey[o] = mkey[j];
-        oidx[o] = (uint32_t)j;
-      }
-      dst += __popcll(bal);
-    }
+  for (int k = 0; k < BS_I; ++k) {
+    const int64_t b = b0 + k;
+    t[k] = a[k] = 0;
+    if (b >= nbrick) continue;
+    const int64_t j0 = min(S.off[b * B3], S.n), j1 = min(S.off[(b + 1) * B3], S.n);
+    a[k] = S.acnt[b];
+    const int64_t v = (j1 > j0 ? j1 - j0 : 0) - (int64_t)S.mcnt[b] + (int64_t)a[k];
+    t[k] = (uint32_t)(v > 0 ? v : 0);
+    mn = min(mn, S.pmn[b]);
+    mx = max(mx, S.pmx[b]);
   }
 }
 
-// Stayers of brick b to their final stream positions: the first position of the
-// brick's stayers in each new cell (cell offset + arrivals from earlier bricks), plus
-// the stayer's rank among the brick's stayers of that cell in old stream order (a
-// stable multi-split of each chunk by digit and a running count per cell).
-template <int P = 1, int V = 2>  // code widths
-__global__ __launch_bounds__(64 * WB) void k_place_stayers(
-    const int64_t* off_in, const uint16_t* tdig, const void* tpos_, const void* tvel_,
-    const uint64_t* cnt, const int64_t* bstart, int B3, int nbits, int64_t nbrick,
-    const uint32_t* skey, const uint32_t* sidx, const int64_t* astart,
-    void* pos_, void* vel_, int64_t* perm, int64_t n, DevErr* err) {
-  using PC = typename PosCode<P>::T;
-  using VC = typename VelCode<V>::T;
-  const PC* tpos = (const PC*)tpos_;
-  const VC* tvel = (const VC*)tvel_;
-  PC* pos = (PC*)pos_;
-  VC* vel = (VC*)vel_;
-  extern __shared__ int64_t lds[];  // dbase [WB][B3], then run [WB][B3] (uint32)
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  int64_t* dbase = lds + (int64_t)wv * B3;
-  uint32_t* run = (uint32_t*)(lds + (int64_t)WB * B3) + (int64_t)wv * B3;
-  const int64_t b = (int64_t)blockIdx.x * WB + wv;
-  if (b >= nbrick) return;  // the whole wave
-  const uint64_t lt = lane ? ((~0ull) >> (64 - lane)) : 0ull;
-  const int64_t kbase = b * B3;
-  // new cell offsets of the brick: its first new position bstart[b] plus the exclusive
-  // prefix of its cells' new counts (low 32 bits of cnt); stayers of a cell follow its
-  // arrivals from earlier bricks (high 32 bits)
-  int64_t carry = bstart[b];
-  for (int l0 = 0; l0 < B3; l0 += 64) {
-    const int l = l0 + lane;
-    const uint64_t cv = l < B3 ? cnt[kbase + l] : 0ull;
-    const uint32_t x = (uint32_t)cv;
-    uint32_t inc = x;  // inclusive prefix over the 64 lanes
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t y = __shfl_up(inc, d, 64);
-      if (lane >= d) inc += y;
-    }
-    if (l < B3) {
-      dbase[l] = carry + (int64_t)(inc - x) + (int64_t)(cv >> 32);
-      run[l] = 0;
-    }
-    carry += (int64_t)__shfl(inc, 63, 64);
+// block-wide extremes; sm: 2 x 16 ints of LDS. Valid in thread 0.
+__device__ inline void block_extremes(int& mn, int& mx, int* sm) {
+  for (int d = 32; d >= 1; d >>= 1) {
+    mn = min(mn, __shfl_xor(mn, d, 64));
+    mx = max(mx, __shfl_xor(mx, d, 64));
   }
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) {
+    sm[w] = mn;
+    sm[16 + w] = mx;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0)
+    for (int q = 1; q < (int)(blockDim.x >> 6); ++q) {
+      mn = min(mn, sm[q]);
+      mx = max(mx, sm[16 + q]);
+    }
+}
+
+__global__ __launch_bounds__(BS_T) void k_brick_sums(PlaceArgs A, int B3, int64_t nbrick,
+                                                     BrickSum* sums) {
+  __shared__ int64_t lw[BS_T / 64 + 1];
+  __shared__ int sm[32];
+  uint32_t t[BS_I], a[BS_I];
+  int mn, mx;
+  brick_items(A.sp[blockIdx.y], B3, nbrick, (int64_t)blockIdx.x * BS_TILE + threadIdx.x * BS_I,
+              t, a, mn, mx);
+  int64_t st = 0, sa = 0, tt, ta;
+#pragma unroll
+  for (int k = 0; k < BS_I; ++k) {
+    st += t[k];
+    sa += a[k];
+  }
+  pmscan::block_excl_scan(st, lw, &tt);
+  pmscan::block_excl_scan(sa, lw, &ta);
+  block_extremes(mn, mx, sm);
+  if (threadIdx.x == 0) sums[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = BrickSum{tt, ta, mn, mx};
+}
+
+__global__ __launch_bounds__(BS_T) void k_brick_scan(PlaceArgs A, int B3, int64_t nbrick,
+                                                     const BrickSum* sums) {
+  __shared__ int64_t lw[BS_T / 64 + 1];
+  __shared__ int sm[32];
+  const PlaceSpecies& S = A.sp[blockIdx.y];
+  const int64_t b0 = (int64_t)blockIdx.x * BS_TILE + threadIdx.x * BS_I;
+  uint32_t t[BS_I], a[BS_I];
+  int mn, mx;
+  brick_items(S, B3, nbrick, b0, t, a, mn, mx);
+  int64_t pt = 0, pa = 0;  // the sums of the blocks before this one
+  if (gridDim.x > 1) {
+    const BrickSum* bs = sums + (int64_t)blockIdx.y * gridDim.x;
+    const int nb = blockIdx.x == 0 ? (int)gridDim.x : (int)blockIdx.x;
+    for (int i = threadIdx.x; i < nb; i += BS_T) {
+      const BrickSum q = bs[i];
+      pt += i < (int)blockIdx.x ? q.tot : 0;
+      pa += i < (int)blockIdx.x ? q.arr : 0;
+      mn = min(mn, q.mn);
+      mx = max(mx, q.mx);
+    }
+    int64_t x;
+    pmscan::block_excl_scan(pt, lw, &x);
+    pt = x;
+    pmscan::block_excl_scan(pa, lw, &x);
+    pa = x;
+  }
+  if (blockIdx.x == 0) {  // it has seen every block's extremes
+    block_extremes(mn, mx, sm);
+    if (threadIdx.x == 0) {
+      S.hout->j_min = mn;
+      S.hout->j_max = mx;
+    }
+  }
+  int64_t st = 0, sa = 0, tt, ta;
+#pragma unroll
+  for (int k = 0; k < BS_I; ++k) {
+    st += t[k];
+    sa += a[k];
+  }
+  int64_t et = pt + pmscan::block_excl_scan(st, lw, &tt);
+  int64_t ea = pa + pmscan::block_excl_scan(sa, lw, &ta);
+#pragma unroll
+  for (int k = 0; k < BS_I; ++k) {
+    const int64_t b = b0 + k;
+    if (b < nbrick) {
+      S.bstart[b] = et;
+      S.astart[b] = (uint32_t)ea;
+    }
+    et += t[k];
+    ea += a[k];
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    S.bstart[nbrick] = pt + tt;
+    S.astart[nbrick] = (uint32_t)(pa + ta);
+  }
+}
+
+// The movers into the lists of the bricks they arrive in, in no particular order (the
+// brick's wave sorts its list by old index). A thread looks at MV particles' digits in one
+// 16-byte load.
+constexpr int MV = 8;
+__global__ __launch_bounds__(KT) void k_list_arrivals(PlaceArgs A, int lgB3, int64_t nbrick,
+                                                     DevErr* err) {
+  const PlaceSpecies& S = A.sp[blockIdx.y];
+  const int64_t i = ((int64_t)blockIdx.x * KT + threadIdx.x) * MV;
+  if (i >= S.n) return;
+  uint32_t d[MV];
+  if (i + MV <= S.n) {  // tdig is 16-byte aligned
+    const uint4 q = *(const uint4*)(S.tdig + i);
+    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+    for (int k = 0; k < MV; ++k) d[k] = (w[k >> 1] >> (16 * (k & 1))) & 0xffffu;
+  } else {
+#pragma unroll
+    for (int k = 0; k < MV; ++k) d[k] = i + k < S.n ? S.tdig[i + k] : 0u;
+  }
+  const uint32_t mover = 1u << lgB3;
+#pragma unroll
+  for (int k = 0; k < MV; ++k) {
+    if (d[k] != mover) continue;
+    const int64_t b = S.mkey[i + k] >> lgB3;
+    // counts inconsistent with n (latched by the offset check) leave stale digits
+    const uint32_t left = b < nbrick ? atomicSub(&S.acnt[b], 1u) : 0u;
+    const int64_t slot = left ? (int64_t)S.astart[b] + left - 1 : S.n;
+    if (slot < S.n) S.aidx[slot] = (uint32_t)(i + k);
+    else latch_error(err, ERRBIT_CORRUPT);
+  }
+}
+
+__device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const int64_t j0 = min(off_in[kbase], n), j1 = min(off_in[kbase + B3], n);
-  for (int64_t base = j0; base < j1; base += 64 * PU) {
-    uint32_t d[PU], p[PU][3], v[PU][3];
+}
+
+// Lanes of the wave whose `valid` digit equals this lane's.
+__device__ __forceinline__ uint64_t wave_match(uint32_t d, bool valid, int nbits) {
+  uint64_t match = __ballot(valid);
+  for (int b = 0; b < nbits; ++b) {
+    const uint64_t m = __ballot(valid && ((d >> b) & 1u));
+    match &= ((d >> b) & 1u) ? m : ~m;
+  }
+  return match;
+}
+
+// Ascending sort of a[0, m) in global memory by one wave (stable 8-bit digit passes, an
+// even number of them through b so that the result is in a): arrival lists too long for
+// the LDS sort. hist: 256 words of LDS. bits: significant bits of the values.
+__device__ void wave_sort_long(uint32_t* a, uint32_t* b, int64_t m, int bits, uint32_t* hist) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t lt = lane ? ((~0ull) >> (64 - lane)) : 0ull;
+  for (int shift = 0; shift < (bits <= 16 ? 16 : 32); shift += 8) {
+    for (int q = lane; q < 256; q += 64) hist[q] = 0;
+    wave_sync();
+    for (int64_t i = lane; i < m; i += 64) atomicAdd(&hist[(a[i] >> shift) & 255u], 1u);
+    wave_sync();
+    uint32_t h[4], s = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      h[k] = hist[4 * lane + k];
+      s += h[k];
+    }
+    uint32_t base = (uint32_t)pmscan::wave_incl_scan_dpp((int)s) - s;
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      hist[4 * lane + k] = base;
+      base += h[k];
+    }
+    wave_sync();
+    for (int64_t i0 = 0; i0 < m; i0 += 64) {
+      const bool valid = i0 + lane < m;
+      const uint32_t v = valid ? a[i0 + lane] : 0u, d = (v >> shift) & 255u;
+      const uint64_t match = wave_match(d, valid, 8);
+      const uint32_t rk = (uint32_t)__popcll(match & lt);
+      const uint32_t to = hist[d];
+      wave_sync();
+      if (valid && rk == 0) hist[d] = to + (uint32_t)__popcll(match);
+      wave_sync();
+      if (valid) b[to + rk] = v;
+    }
+    __threadfence();  // this wave reads b next
+    uint32_t* t = a;
+    a = b;
+    b = t;
+  }
+}
+
+// Final stream positions. A brick's new particles, cell by cell, are its arrivals from
+// earlier bricks, its stayers and its arrivals from later bricks, each in old stream
+// order: one running position per cell serves them one after the other, and ranks within a
+// chunk of 64 come from a multi-split by digit. NW = 1: one wave per brick, WB bricks per
+// workgroup, no barrier; the stayers per cell are the kick's counts. NW > 1: a workgroup of
+// NW waves per brick, each with a contiguous part of the stayers and its own running
+// positions (from a first pass over the digits): for bricks of thousands of particles,
+// which one wave takes 80 chunks for. The new count bytes are written here too, so that no
+// pass over the cells follows.
+constexpr int WB = 4;       // bricks per workgroup (NW = 1)
+constexpr int PU = 4;       // chunks whose loads are issued together
+constexpr int ACAP = 256;   // arrivals sorted in LDS, per wave
+template <int P, int V, int NW>
+__global__ __launch_bounds__(NW == 1 ? 64 * WB : 64 * NW) void k_place(
+    PlaceArgs A, int B3, int nbits, int64_t nbrick, int nbits_idx, DevErr* err) {
+  using PC = typename PosCode<P>::T;
+  using VC = typename VelCode<V>::T;
+  const PlaceSpecies& S = A.sp[blockIdx.y];
+  const PC* tpos = (const PC*)S.tpos;
+  const VC* tvel = (const VC*)S.tvel;
+  PC* pos = (PC*)S.pos;
+  VC* vel = (VC*)S.vel;
+  constexpr int NT = 64 * NW, CAP = ACAP * NW;
+  extern __shared__ uint32_t lds[];
+  __shared__ int wsum[16];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tid = NW == 1 ? lane : (int)threadIdx.x;  // thread of the brick
+  const int bw = NW == 1 ? 0 : wv;                    // wave of the brick
+  // [CAP] arrivals (16-byte aligned)
+  uint32_t* al = lds + (NW == 1 ? wv * (CAP + ((B3 + 3) & ~3)) : 0);
+  uint32_t* runs = al + CAP;                             // [NW][B3] running positions
+  uint32_t* run = runs + bw * B3;
+  const int64_t b = (int64_t)blockIdx.x * (NW == 1 ? WB : 1) + (NW == 1 ? wv : 0);
+  if (b >= nbrick) return;  // the whole wave (NW = 1)
+  auto sync = [] {
+    if constexpr (NW == 1) wave_sync();
+    else __syncthreads();
+  };
+  const uint64_t lt = lane ? ((~0ull) >> (64 - lane)) : 0ull;
+  const int64_t kbase = b * B3, n = S.n;
+  const int64_t j0 = min(S.off[kbase], n), j1 = min(S.off[kbase + B3], n);
+  const int64_t a0 = S.astart[b];
+  const int64_t m = (int64_t)S.astart[b + 1] - a0;  // arrivals
+
+  // the arrivals in old stream order: al[0, m), or aidx[a0, a0 + m) when they are many
+  for (int l = tid; l < NW * B3; l += NT) runs[l] = 0;
+  const bool big = m > CAP;
+  if (!big) {
+    uint32_t v[ACAP / 64], r[ACAP / 64];
+#pragma unroll
+    for (int k = 0; k < ACAP / 64; ++k) {
+      const int i = tid + k * NT;
+      v[k] = i < m ? S.aidx[a0 + i] : 0xffffffffu;
+      r[k] = 0;
+      if (k * NT < m) al[i] = v[k];
+    }
+    sync();
+    const int m4 = ((int)m + 3) & ~3;  // the slots up to the next multiple of NT are padding
+    for (int q = 0; q < m4; q += 4) {
+      const uint4 x = *(const uint4*)(al + q);
+#pragma unroll
+      for (int k = 0; k < ACAP / 64; ++k)
+        r[k] += (x.x < v[k]) + (x.y < v[k]) + (x.z < v[k]) + (x.w < v[k]);
+    }
+    sync();
+#pragma unroll
+    for (int k = 0; k < ACAP / 64; ++k)
+      if (tid + k * NT < m) al[r[k]] = v[k];
+  } else if (bw == 0) {
+    wave_sort_long(S.aidx + a0, S.abuf + a0, m, nbits_idx, al);
+  }
+  sync();
+  auto arrival = [&](int64_t i) { return (int64_t)(big ? S.aidx[a0 + i] : al[i]); };
+
+  // arrivals per cell (those from earlier bricks count with the first wave, the others
+  // with the last), and for NW > 1 each wave's stayers
+  int64_t early = 0;  // arrivals from earlier bricks
+  for (int64_t i = tid; i - tid < m; i += NT) {
+    const int64_t j = i < m ? arrival(i) : n;
+    const bool e = j < j0;
+    if (j < n) {
+      const uint32_t d = S.mkey[j] - (uint32_t)kbase;
+      if (d < (uint32_t)B3) atomicAdd(&runs[(e || NW == 1 ? 0 : NW - 1) * B3 + d], 1u);
+    }
+    if constexpr (NW == 1) early += __popcll(__ballot(e));
+    else early += __syncthreads_count(e);
+  }
+  // this wave's stayers: [s0, s1)
+  const int64_t per = NW == 1 ? j1 - j0 : ((j1 - j0 + NW - 1) / NW + 63) / 64 * 64;
+  const int64_t s0 = min(j0 + bw * per, j1), s1 = min(s0 + per, j1);
+  if constexpr (NW > 1) {
+    for (int64_t base = s0; base < s1; base += 64 * PU) {
+      uint32_t d[PU];
+#pragma unroll
+      for (int u = 0; u < PU; ++u) {
+        const int64_t j = base + 64 * u + lane;
+        d[u] = j < s1 ? S.tdig[j] : (uint32_t)B3;
+      }
+#pragma unroll
+      for (int u = 0; u < PU; ++u)
+        if (d[u] < (uint32_t)B3) atomicAdd(&run[d[u]], 1u);
+    }
+  }
+  sync();
+  // new counts, count bytes, escapes, and the running positions (relative to the brick's
+  // first new position; exclusive prefix over the cells, then over the waves)
+  const int64_t first = S.bstart[b];
+  uint32_t carry = 0;
+  int ne = 0;
+  for (int l0 = 0; l0 < B3; l0 += NT) {
+    const int l = l0 + tid;
+    uint32_t x = 0;
+    if (l < B3) {
+      if constexpr (NW == 1) x = S.cnt[kbase + l];
+#pragma unroll
+      for (int q = 0; q < NW; ++q) x += runs[q * B3 + l];
+      S.count[kbase + l] = (uint8_t)(x >= 255u ? 255u : x);
+      if (x >= 255u) {
+        S.cnt[kbase + l] = x;
+        ++ne;
+      }
+    }
+    uint32_t ex, tot;
+    if constexpr (NW == 1) {
+      const uint32_t inc = (uint32_t)pmscan::wave_incl_scan_dpp((int)x);
+      ex = inc - x;
+      tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+    } else {
+      ex = (uint32_t)pmscan::block_excl_scan_i32((int)x, wsum);
+      tot = 0;
+      for (int q = 0; q < NW; ++q) tot += (uint32_t)wsum[q];
+      __syncthreads();
+    }
+    if (l < B3) {
+      uint32_t at = carry + ex;
+      if constexpr (NW == 1) {
+        runs[l] = at;
+      } else {
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+          const uint32_t c = runs[q * B3 + l];
+          runs[q * B3 + l] = at;
+          at += c;
+        }
+      }
+    }
+    carry += tot;
+  }
+  {
+    for (int d = 32; d >= 1; d >>= 1) ne += __shfl_xor(ne, d, 64);
+    if constexpr (NW > 1) {
+      __syncthreads();
+      if (lane == 0) wsum[bw] = ne;
+      __syncthreads();
+      ne = 0;
+      for (int q = 0; q < NW; ++q) ne += wsum[q];
+    }
+    if (tid == 0) {
+      S.ecnt[b] = (uint32_t)ne;
+      if (ne) atomicAdd(S.nesc, (uint32_t)ne);
+    }
+  }
+  sync();
+  // a chunk of at most 64 particles: each valid lane's particle to its cell's next
+  // positions, in lane order
+  auto put = [&](bool valid, uint32_t d, int64_t j, const PC (&p)[3], const VC (&v)[3]) {
+    const uint64_t match = wave_match(d, valid, nbits);
+    const uint32_t rk = (uint32_t)__popcll(match & lt);
+    uint32_t at = 0;
+    if (valid) at = run[d];
+    wave_sync();
+    if (valid && rk == 0) run[d] = at + (uint32_t)__popcll(match);
+    wave_sync();
+    if (!valid) return;
+    const int64_t dst = first + at + rk;
+    if (dst < 0 || dst >= n) {
+      latch_error(err, ERRBIT_CORRUPT);
+      return;
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      pos[3 * dst + a] = p[a];
+      vel[3 * dst + a] = v[a];
+    }
+    if (S.perm) S.perm[dst] = j;
+  };
+  auto put_arrivals = [&](int64_t i0, int64_t i1) {
+    for (int64_t i = i0; i < i1; i += 64) {
+      const int64_t j = i + lane < i1 ? arrival(i + lane) : n;
+      const uint32_t d = j < n ? S.mkey[j] - (uint32_t)kbase : (uint32_t)B3;
+      const bool valid = d < (uint32_t)B3;
+      PC p[3];
+      VC v[3];
+      const int64_t jj = valid ? j : 0;  // n > 0 whenever there are arrivals
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        p[a] = tpos[3 * jj + a];
+        v[a] = tvel[3 * jj + a];
+      }
+      put(valid, d, j, p, v);
+    }
+  };
+  if (bw == 0) put_arrivals(0, early);
+  for (int64_t base = s0; base < s1; base += 64 * PU) {
+    uint32_t d[PU];
+    PC p[PU][3];
+    VC v[PU][3];
 #pragma unroll
     for (int u = 0; u < PU; ++u) {
       const int64_t j = base + 64 * u + lane;
-      const bool h = j < j1;
-      const int64_t jj = h ? j : j0;
-      d[u] = h ? tdig[jj] : (uint32_t)B3;  // past the end: not a stayer
+      const bool h = j < s1;
+      const int64_t jj = h ? j : s0;
+      d[u] = h ? S.tdig[jj] : (uint32_t)B3;  // past the end: not a stayer
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
         p[u][a] = tpos[3 * jj + a];
@@ -845,83 +1195,46 @@ __global__ __launch_bounds__(64 * WB) void k_place_stayers(
       }
     }
 #pragma unroll
-    for (int u = 0; u < PU; ++u) {
-      const uint32_t du = d[u];
-      const bool stay = du < (uint32_t)B3;
-      uint64_t match = __ballot(stay);
-      for (int bit = 0; bit < nbits; ++bit) {
-        const uint64_t mbit = __ballot(stay && ((du >> bit) & 1u));
-        match &= ((du >> bit) & 1u) ? mbit : ~mbit;
-      }
-      const uint32_t rk = (uint32_t)__popcll(match & lt);
-      uint32_t before = 0;
-      if (stay) before = run[du];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      if (stay && rk == 0) run[du] = before + (uint32_t)__popcll(match);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      if (stay) {
-        const int64_t dst = dbase[du] + (int64_t)(before + rk);
-        const int64_t j = base + 64 * u + lane;
-        if (dst < 0 || dst >= n) {
-          latch_error(err, ERRBIT_CORRUPT);
-        } else {
-#pragma unroll
-          for (int a = 0; a < 3; ++a) {
-            pos[3 * dst + a] = (PC)p[u][a];
-            vel[3 * dst + a] = (VC)v[u][a];
-          }
-          if (perm) perm[dst] = j;
-        }
-      }
-    }
+    for (int u = 0; u < PU; ++u)
+      put(d[u] < (uint32_t)B3, d[u], base + 64 * u + lane, p[u], v[u]);
   }
-  // the brick's arrivals, placed by the same wave so that every line of the brick's
-  // output range is written by one wave: arrivals from earlier bricks precede the
-  // stayers of their new cell, the others follow them
-  if (astart) {
-    const int64_t ms = astart[b], me = astart[b + 1];
-    for (int64_t s = ms + lane; s < me; s += 64) {
-      const uint32_t k = skey[s];
-      const int64_t gs = lower_bound_u32(skey, ms, s, k);
-      const int64_t ge = lower_bound_u32(skey, s, me, k + 1);
-      const uint64_t cv = cnt[k];
-      const int64_t before = (int64_t)(cv >> 32), total = (int64_t)(cv & 0xffffffffull);
-      const int64_t stay = total - (ge - gs);
-      const int64_t jg = s - gs;
-      // the cell's new offset is its stayers' base less the arrivals that precede them
-      const int64_t dst = dbase[k - kbase] - before + (jg < before ? jg : stay + jg);
-      const int64_t j = sidx[s];
-      if (dst < 0 || dst >= n || j < 0 || j >= n) {
-        latch_error(err, ERRBIT_CORRUPT);
-        continue;
-      }
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        pos[3 * dst + a] = tpos[3 * j + a];
-        vel[3 * dst + a] = tvel[3 * j + a];
-      }
-      if (perm) perm[dst] = j;
-    }
-  }
+  if (bw == NW - 1) put_arrivals(early, m);
 }
 
-__global__ void k_read_total(const int64_t* moff, int64_t nb, int64_t* out) { *out = moff[nb]; }
-
-// New particles of each brick: its old particles less its movers, plus its arrivals (the
-// brick's run [astart[b], astart[b + 1]) of the sorted movers); their scan gives each
-// brick's first new stream position, so that no scan over all cells is needed.
-__global__ __launch_bounds__(KT) void k_brick_totals(const int64_t* off_in, const uint32_t* mcnt,
-                                                    const int64_t* astart, int B3,
-                                                    int64_t nbrick, int64_t n, uint32_t* tot) {
-  const int64_t b = (int64_t)blockIdx.x * KT + threadIdx.x;
-  if (b >= nbrick) return;
-  const int64_t j0 = min(off_in[b * B3], n), j1 = min(off_in[(b + 1) * B3], n);
-  const int64_t t = (j1 > j0 ? j1 - j0 : 0) - (int64_t)mcnt[b] + (astart[b + 1] - astart[b]);
-  tot[b] = (uint32_t)(t > 0 ? t : 0);
+// The escape table in cell order (cells of 255 particles and more are rare: without any,
+// every workgroup returns after one load). Workgroup x takes a range of bricks; the
+// escapes before it are the sum of the earlier bricks' counts.
+__global__ __launch_bounds__(KT) void k_escape_table(PlaceArgs A, int B3, int64_t nbrick,
+                                                    DevErr* err) {
+  const PlaceSpecies& S = A.sp[blockIdx.y];
+  const uint32_t total = *S.nesc;
+  if (total == 0) return;  // the header's n_esc is 0 already
+  __shared__ int64_t lw[KT / 64 + 1];
+  const int64_t per = (nbrick + gridDim.x - 1) / gridDim.x;
+  const int64_t q0 = min((int64_t)blockIdx.x * per, nbrick), q1 = min(q0 + per, nbrick);
+  int64_t before = 0, tot;
+  for (int64_t b = threadIdx.x; b < q0; b += KT) before += S.ecnt[b];
+  pmscan::block_excl_scan(before, lw, &tot);
+  int64_t at = tot;
+  for (int64_t b0 = q0; b0 < q1; b0 += KT) {
+    const int64_t b = b0 + threadIdx.x;
+    const uint32_t ne = b < q1 ? S.ecnt[b] : 0u;
+    int64_t k = at + pmscan::block_excl_scan((int64_t)ne, lw, &tot);
+    at += tot;
+    if (!ne) continue;
+    for (int64_t i = b * B3; i < (b + 1) * B3; ++i)
+      if (S.count[i] == 255) {
+        if (k < S.cap_esc) {
+          S.esc[2 * k] = (uint64_t)i;
+          S.esc[2 * k + 1] = (uint64_t)S.cnt[i];
+        }
+        ++k;
+      }
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    S.hout->n_esc = (int64_t)total;
+    if ((int64_t)total > S.cap_esc) latch_error(err, ERRBIT_CAPACITY, (int64_t)total);
+  }
 }
 
 }  // namespace
@@ -948,29 +1261,37 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
   const Geom& g = c->g;
   if (n_sp <= 0 || n_sp > MAXSP) return PM_ERR_ARG;
   const int B3 = g.B * g.B * g.B;
-  int64_t ntot = 0, nbase[MAXSP + 1];
+  // the species' scratch arrays start at multiples of 8 particles (16-byte digit loads)
+  int64_t ntot = 0, nbase[MAXSP];
   for (int s = 0; s < n_sp; ++s) {
     nbase[s] = ntot;
-    ntot += in[s].n;
+    ntot += (in[s].n + 7) & ~(int64_t)7;
   }
-  nbase[n_sp] = ntot;
   const size_t nn = (size_t)(ntot > 0 ? ntot : 1);
-  uint64_t* cnt = (uint64_t*)scratch(c, SC_CNT, (size_t)g.ncell3 * 8 * n_sp);
-  int64_t* bstart = (int64_t*)scratch(c, SC_OFF2, (size_t)(g.nbrick + 1) * 8);
-  uint32_t* btot = (uint32_t*)scratch(c, SC_BTOT, (size_t)g.nbrick * 4);
+  const int64_t nbrick = g.nbrick;
+  uint32_t* cnt = (uint32_t*)scratch(c, SC_CNT, (size_t)g.ncell3 * 4 * n_sp);
+  int64_t* bstart = (int64_t*)scratch(c, SC_OFF2, (size_t)(nbrick + 1) * 8 * n_sp);
+  uint32_t* astart = (uint32_t*)scratch(c, SC_ASTART, (size_t)(nbrick + 1) * 4 * n_sp);
+  uint32_t* acnt = (uint32_t*)scratch(c, SC_ACNT, (size_t)nbrick * 4 * n_sp);
+  uint32_t* ecnt = (uint32_t*)scratch(c, SC_ECNT, ((size_t)nbrick * n_sp + MAXSP) * 4);
   char* tpos = (char*)scratch(c, SC_TPOS, nn * 3 * P);
   char* tvel = (char*)scratch(c, SC_TVEL, nn * 3 * V);
   uint16_t* tdig = (uint16_t*)scratch(c, SC_TDST, nn * 2);
   uint32_t* mkey = (uint32_t*)scratch(c, SC_KEYA, nn * 4);
-  uint32_t* midx = (uint32_t*)scratch(c, SC_VALA, nn * 4);
-  uint32_t* skey = (uint32_t*)scratch(c, SC_KEYB, nn * 4);
-  uint32_t* sidx = (uint32_t*)scratch(c, SC_VALB, nn * 4);
-  uint32_t* mcnt = (uint32_t*)scratch(c, SC_MCNT, (size_t)g.nbrick * 4 * n_sp);
-  int64_t* moff = (int64_t*)scratch(c, SC_MOFF, (size_t)(g.nbrick + 1) * 8);
-  int32_t* part = (int32_t*)scratch(c, SC_PARTS, (size_t)g.nbrick * 8 * n_sp);
-  if (!cnt || !bstart || !btot || !tpos || !tvel || !tdig || !mkey || !midx || !skey || !sidx ||
-      !mcnt || !moff || !part)
+  uint32_t* aidx = (uint32_t*)scratch(c, SC_VALA, nn * 4);
+  uint32_t* abuf = (uint32_t*)scratch(c, SC_VALB, nn * 4);
+  uint32_t* mcnt = (uint32_t*)scratch(c, SC_MCNT, (size_t)nbrick * 4 * n_sp);
+  int32_t* part = (int32_t*)scratch(c, SC_PARTS, (size_t)nbrick * 8 * n_sp);
+  const int64_t nbs = cdiv(nbrick, BS_TILE);
+  BrickSum* bsum = (BrickSum*)scratch(c, SC_BSUM, (size_t)nbs * n_sp * sizeof(BrickSum));
+  if (!cnt || !bstart || !astart || !acnt || !ecnt || !tpos || !tvel || !tdig || !mkey ||
+      !aidx || !abuf || !mcnt || !part || !bsum)
     return PM_ERR_NOMEM;
+  uint32_t* nesc = ecnt + nbrick * n_sp;
+  PrepArgs R{};
+  R.n_sp = n_sp;
+  PlaceArgs Q{};
+  int64_t nmax = 0;
   KickArgs A{};
   A.n_sp = n_sp;
   A.acc = acc;
@@ -990,91 +1311,90 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
     S.cnt = cnt + (int64_t)s * g.ncell3;
     S.mkey = mkey + nbase[s];
     S.mcnt = mcnt + (int64_t)s * g.nbrick;
+    S.acnt = acnt + (int64_t)s * g.nbrick;
     S.pmn = part + (int64_t)2 * s * g.nbrick;
     S.pmx = S.pmn + g.nbrick;
     S.app = app ? app[s] : nullptr;
+    R.hin[s] = in[s].hdr;
+    R.hout[s] = out[s].hdr;
+    R.n[s] = in[s].n;
+    nmax = std::max(nmax, in[s].n);
+    PlaceSpecies& L = Q.sp[s];
+    L.n = S.n;
+    L.off = S.off;
+    L.tdig = S.tdig;
+    L.mkey = S.mkey;
+    L.tpos = S.tpos;
+    L.tvel = S.tvel;
+    L.cnt = S.cnt;
+    L.mcnt = S.mcnt;
+    L.acnt = S.acnt;
+    L.pmn = S.pmn;
+    L.pmx = S.pmx;
+    L.bstart = bstart + s * (nbrick + 1);
+    L.astart = astart + s * (nbrick + 1);
+    L.aidx = aidx + nbase[s];
+    L.abuf = abuf + nbase[s];
+    L.ecnt = ecnt + s * nbrick;
+    L.nesc = nesc + s;
+    L.hout = out[s].hdr;
+    L.pos = out[s].pos;
+    L.vel = out[s].vel;
+    L.count = out[s].count;
+    L.esc = out[s].esc;
+    L.cap_esc = out[s].cap_esc;
+    L.perm = perm ? perm[s] : nullptr;
   }
   {
-    pm_status st0;
-    for (int s = 0; s < n_sp; ++s)
-      hipLaunchKernelGGL(k_vmax_next<V>, dim3(1), dim3(1), 0, c->stream, in[s].hdr,
-                         out[s].hdr, amax, ck, in[s].n);
+    const int64_t na = nbrick * n_sp;
+    hipLaunchKernelGGL(k_kick_prep<V>, dim3((unsigned)std::min<int64_t>(cdiv(na, KT), 1024)),
+                       dim3(KT), 0, c->stream, R, amax, ck, acnt, na, nesc);
     ProfScope ps(c, ST_KICK);
-    const int R = g.B * g.r;
+    const int RN = g.B * g.r;
     const size_t tail = (size_t)MAXSP * (B3 + 1) * 4 * 2;
     // two bricks per workgroup: R = 16, an even number of bricks per side, z quarters of
     // whole cells
     const size_t pbytes = (size_t)3 * (2 * PR + 1) * (PR + 1) * (PR / 4 + 1) * 4 + 2 * tail;
-    const size_t fbytes = (size_t)3 * (R + 1) * (R + 1) * (R + 1) * 4;
-    if (R == PR && g.lgnb >= 1 && (g.B % 4) == 0 && pbytes <= 48 * 1024)
+    const size_t fbytes = (size_t)3 * (RN + 1) * (RN + 1) * (RN + 1) * 4;
+    if (RN == PR && g.lgnb >= 1 && (g.B % 4) == 0 && pbytes <= 48 * 1024)
       hipLaunchKernelGGL((k_kick_pair<256, 4, P, V>), dim3((unsigned)(g.nbrick / 2)),
                          dim3(256), pbytes, c->stream, A, g, c->err);
-    else if (R == 16 && fbytes + tail <= 96 * 1024)
+    else if (RN == 16 && fbytes + tail <= 96 * 1024)
       hipLaunchKernelGGL((k_kick_brick<16, P, V>), dim3((unsigned)g.nbrick), dim3(KB),
                          fbytes + tail, c->stream, A, g, c->err);
-    else if (R == 8)
+    else if (RN == 8)
       hipLaunchKernelGGL((k_kick_brick<8, P, V>), dim3((unsigned)g.nbrick), dim3(KB),
                          fbytes + tail, c->stream, A, g, c->err);
     else
       hipLaunchKernelGGL((k_kick_brick<0, P, V>), dim3((unsigned)g.nbrick), dim3(KB), tail,
                          c->stream, A, g, c->err);
     PM_LAUNCH_CHECK();
-    prof_end(c);  // the scope covers the brick kernel only
-    for (int s = 0; s < n_sp; ++s)
-      if ((st0 = fold_minmax_to_header(c, A.sp[s].pmn, A.sp[s].pmx, g.nbrick, out[s].hdr)) !=
-          PM_OK)
-        return st0;
   }
-  const size_t place_lds = (size_t)WB * B3 * 12;
-  int64_t* nmov = (int64_t*)scratch(c, SC_NMOV, (size_t)MAXSP * 8);
-  if (!nmov) return PM_ERR_NOMEM;
-  for (int s = 0; s < n_sp; ++s) {
-    const int64_t n = in[s].n;
-    const KickSpecies& S = A.sp[s];
-    ProfScope ps(c, ST_RESORT);
-    pm_status st = scan_u32(c, S.mcnt, g.nbrick, moff);
-    if (st != PM_OK) return st;
-    // the mover count stays on the device; the kernels below read it there and are
-    // launched for the worst case (every particle a mover), so nothing waits on the host
-    int64_t* nmd = nmov + s;
-    hipLaunchKernelGGL(k_read_total, dim3(1), dim3(1), 0, c->stream, moff, g.nbrick, nmd);
-    uint32_t* sk = skey + nbase[s];
-    uint32_t* si = sidx + nbase[s];
-    if (n > 0) {
-      hipLaunchKernelGGL(k_compact_movers, dim3((unsigned)cdiv(g.nbrick, WB)), dim3(64 * WB),
-                         0, c->stream, S.off, S.mcnt, moff, B3, g.nbrick, n, S.tdig, S.mkey,
-                         sk, si);
-      PM_LAUNCH_CHECK();
-      // stable sort (old order preserved inside each new cell)
-      uint32_t *k1 = sk, *v1 = si, *k2 = S.mkey, *v2 = midx + nbase[s];
-      st = radix_sort_pairs_dev(c, &k1, &v1, &k2, &v2, n, nmd, 3 * (g.lgB + g.lgnb));
-      if (st != PM_OK) return st;
-      sk = k1;
-      si = v1;
-      const int64_t ag = std::min<int64_t>(cdiv(n, KT), 2048);
-      hipLaunchKernelGGL(k_arrivals, dim3((unsigned)ag), dim3(KT), 0, c->stream, sk, si, nmd,
-                         S.off, B3, S.cnt);
-      PM_LAUNCH_CHECK();
-    }
-    // the mover offsets are spent: moff now takes each brick's run of arrivals
-    hipLaunchKernelGGL(k_brick_arrivals, dim3((unsigned)cdiv(g.nbrick + 1, KT)), dim3(KT), 0,
-                       c->stream, sk, nmd, B3, g.nbrick, moff);
-    PM_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_brick_totals, dim3((unsigned)cdiv(g.nbrick, KT)), dim3(KT), 0,
-                       c->stream, S.off, S.mcnt, moff, B3, g.nbrick, n, btot);
-    PM_LAUNCH_CHECK();
-    st = scan_u32(c, btot, g.nbrick, bstart);
-    if (st != PM_OK) return st;
-    int64_t* pm = perm ? perm[s] : nullptr;
-    hipLaunchKernelGGL((k_place_stayers<P, V>), dim3((unsigned)cdiv(g.nbrick, WB)),
-                       dim3(64 * WB), place_lds, c->stream, S.off, S.tdig,
-                       (const void*)S.tpos, (const void*)S.tvel, S.cnt, bstart, B3,
-                       3 * g.lgB, g.nbrick, sk, si, moff, (void*)out[s].pos,
-                       (void*)out[s].vel, pm, n, c->err);
-    PM_LAUNCH_CHECK();
-    st = run_finalize_counts(c, nullptr, S.cnt, &out[s]);
-    if (st != PM_OK) return st;
-  }
+  ProfScope ps(c, ST_RESORT);
+  const unsigned ny = (unsigned)n_sp;
+  if (nbs > 1)
+    hipLaunchKernelGGL(k_brick_sums, dim3((unsigned)nbs, ny), dim3(BS_T), 0, c->stream, Q, B3,
+                       nbrick, bsum);
+  hipLaunchKernelGGL(k_brick_scan, dim3((unsigned)nbs, ny), dim3(BS_T), 0, c->stream, Q, B3,
+                     nbrick, (const BrickSum*)bsum);
+  if (nmax > 0)
+    hipLaunchKernelGGL(k_list_arrivals, dim3((unsigned)cdiv(nmax, KT * MV), ny), dim3(KT), 0,
+                       c->stream, Q, 3 * g.lgB, nbrick, c->err);
+  PM_LAUNCH_CHECK();
+  // bits of an old stream index (the long lists' sort)
+  const int ibits = nmax > 65536 ? 32 : 16;
+  // bricks of 8^3 cells hold thousands of particles: four waves each
+  if (B3 >= 512)
+    hipLaunchKernelGGL((k_place<P, V, 4>), dim3((unsigned)nbrick, ny), dim3(256),
+                       (size_t)4 * (ACAP + B3) * 4, c->stream, Q, B3, 3 * g.lgB, nbrick, ibits,
+                       c->err);
+  else
+    hipLaunchKernelGGL((k_place<P, V, 1>), dim3((unsigned)cdiv(nbrick, WB), ny), dim3(64 * WB),
+                       (size_t)WB * (ACAP + ((B3 + 3) & ~3)) * 4, c->stream, Q, B3, 3 * g.lgB, nbrick, ibits,
+                       c->err);
+  hipLaunchKernelGGL(k_escape_table, dim3((unsigned)std::min<int64_t>(cdiv(nbrick, KT), 64), ny),
+                     dim3(KT), 0, c->stream, Q, B3, nbrick, c->err);
+  PM_LAUNCH_CHECK();
   return PM_OK;
 }
 
@@ -1089,15 +1409,4 @@ pm_status run_kick_compressed_all(pm_context* c, const pm_species* in, pm_specie
     return kick_compressed_t<decltype(P_)::value, decltype(V_)::value>(
         c, in, out, n_sp, offs, acc, amax, ck, cd, perm, app);
   });
-}
-
-pm_status run_kick_compressed(pm_context* c, const pm_species* in, pm_species* out,
-                              const float* acc, const float* amax, double ck, double cd,
-                              uint32_t* /*unused*/) {
-  int64_t* off = (int64_t*)scratch(c, SC_SPOFF0, (size_t)(c->g.ncell3 + 1) * 8);
-  if (!off) return PM_ERR_NOMEM;
-  pm_status s = run_cell_offsets(c, in, off);
-  if (s != PM_OK) return s;
-  int64_t* offs[1] = {off};
-  return run_kick_compressed_all(c, in, out, 1, offs, acc, amax, ck, cd, nullptr);
 }

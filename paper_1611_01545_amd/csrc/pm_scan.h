@@ -21,10 +21,6 @@ struct GetU32 {
   const uint32_t* p;
   __device__ int64_t operator()(int64_t i) const { return p[i]; }
 };
-struct GetU64Lo {
-  const uint64_t* p;
-  __device__ int64_t operator()(int64_t i) const { return (int64_t)(p[i] & 0xffffffffull); }
-};
 // Full per-cell count of a compressed species: the byte, or the escape table entry.
 struct GetCount {
   const uint8_t* count;
@@ -126,11 +122,23 @@ __device__ inline int64_t block_excl_scan(int64_t v, int64_t* lds_w, int64_t* to
   return r;
 }
 
+// Up to SCAN_BATCH scans of n items each in the same launches (grid.y). want (with err):
+// what the total has to be, checked by the block that finds it.
+constexpr int SCAN_BATCH = 4;
 template <typename Get>
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_reduce(Get g, int64_t n,
+struct ScanArgs {
+  Get g[SCAN_BATCH];
+  int64_t* out[SCAN_BATCH];
+  int64_t want[SCAN_BATCH];
+  DevErr* err = nullptr;
+};
+
+template <typename Get>
+__global__ __launch_bounds__(SCAN_THREADS) void k_scan_reduce(ScanArgs<Get> A, int64_t n,
                                                               int64_t* bsum) {
   __shared__ int64_t lw[SCAN_THREADS / 64 + 1];
   using PH = Phase<Get>;
+  const Get g = A.g[blockIdx.y];
   const int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
   typename PH::R r[SCAN_ITEMS];
 #pragma unroll
@@ -146,12 +154,13 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_reduce(Get g, int64_t n,
   }
   int64_t tot;
   block_excl_scan(s, lw, &tot);
-  if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+  if (threadIdx.x == 0) bsum[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = tot;
 }
 
-static __global__ __launch_bounds__(1024) void k_scan_blocks(int64_t* bsum, int64_t nb,
-                                                      int64_t* total_out) {
+// exclusive prefix of each batch entry's nb block sums, in place
+static __global__ __launch_bounds__(1024) void k_scan_blocks(int64_t* bsum, int64_t nb) {
   __shared__ int64_t lw[1024 / 64 + 1];
+  bsum += (int64_t)blockIdx.x * nb;
   int64_t carry = 0;
   for (int64_t b0 = 0; b0 < nb; b0 += 1024) {
     int64_t i = b0 + threadIdx.x;
@@ -161,23 +170,37 @@ static __global__ __launch_bounds__(1024) void k_scan_blocks(int64_t* bsum, int6
     if (i < nb) bsum[i] = carry + ex;
     carry += tot;
   }
-  if (threadIdx.x == 0) *total_out = carry;
 }
 
+// scanned: bsum holds prefixes (k_scan_blocks ran); otherwise it holds the blocks' sums, and
+// each block adds up those before its own (none when it is the only one).
 template <typename Get>
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_down(Get g, int64_t n,
-                                                            const int64_t* bsum,
-                                                            int64_t* out) {
+__global__ __launch_bounds__(SCAN_THREADS) void k_scan_down(ScanArgs<Get> A, int64_t n,
+                                                            const int64_t* bsum, bool scanned) {
   __shared__ int64_t vals[SCAN_TILE + SCAN_TILE / SCAN_ITEMS];
   __shared__ int64_t lw[SCAN_THREADS / 64 + 1];
   using PH = Phase<Get>;
+  const Get g = A.g[blockIdx.y];
+  int64_t* out = A.out[blockIdx.y];
   const int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
+  int64_t before = 0;
   {
     typename PH::R r[SCAN_ITEMS];
 #pragma unroll
     for (int k = 0; k < SCAN_ITEMS; ++k) {
       const int64_t i = base + k * SCAN_THREADS + threadIdx.x;
       r[k] = PH::raw(g, i < n ? i : n - 1);  // n > 0 whenever a block runs
+    }
+    if (blockIdx.x > 0) {
+      const int64_t* bs = bsum + (int64_t)blockIdx.y * gridDim.x;
+      if (scanned) {
+        before = bs[blockIdx.x];
+      } else {
+        for (int64_t i = threadIdx.x; i < blockIdx.x; i += SCAN_THREADS) before += bs[i];
+        int64_t tot;
+        block_excl_scan(before, lw, &tot);
+        before = tot;
+      }
     }
 #pragma unroll
     for (int k = 0; k < SCAN_ITEMS; ++k) {
@@ -193,9 +216,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_down(Get g, int64_t n,
     loc[k] = s;
     s += vals[scan_pad(threadIdx.x * SCAN_ITEMS + k)];
   }
-  int64_t ex = block_excl_scan(s, lw, nullptr);
-  int64_t off = bsum[blockIdx.x] + ex;
-  __syncthreads();
+  int64_t tot;
+  const int64_t off = before + block_excl_scan(s, lw, &tot);
 #pragma unroll
   for (int k = 0; k < SCAN_ITEMS; ++k) vals[scan_pad(threadIdx.x * SCAN_ITEMS + k)] = off + loc[k];
   __syncthreads();
@@ -204,30 +226,48 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_down(Get g, int64_t n,
     const int64_t i = base + k * SCAN_THREADS + threadIdx.x;
     if (i < n) out[i] = vals[scan_pad(k * SCAN_THREADS + threadIdx.x)];
   }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    out[n] = before + tot;
+    if (A.err && before + tot != A.want[blockIdx.y]) latch_error(A.err, ERRBIT_CORRUPT);
+  }
 }
 
-// bsum_ext (nullable): caller-provided block sums of at least cdiv(n, SCAN_TILE) entries
-// instead of the context's scratch
+// bsum_ext (nullable): caller-provided block sums of at least nbatch cdiv(n, SCAN_TILE)
+// entries instead of the context's scratch. One launch up to SCAN_TILE items, two up to
+// SCAN_DIRECT blocks (each adds up the sums before it: at most 4 loads per thread, against
+// 4 us of a launch of its own), three beyond.
+constexpr int64_t SCAN_DIRECT = 1024;
 template <typename Get>
-pm_status scan_generic(pm_context* c, Get g, int64_t n, int64_t* out,
-                       int64_t* bsum_ext = nullptr) {
-  int64_t nb = cdiv(n, SCAN_TILE);
-  if (nb == 0) {
-    hipLaunchKernelGGL(k_fill<int64_t>, dim3(1), dim3(64), 0, c->stream, out, 1,
-                       (int64_t)0);
-    PM_LAUNCH_CHECK();
-    return PM_OK;
+pm_status scan_batch(pm_context* c, const ScanArgs<Get>& A, int nbatch, int64_t n,
+                     int64_t* bsum_ext = nullptr) {
+  const int64_t nb = cdiv(n, SCAN_TILE);
+  int64_t* bsum = bsum_ext;
+  if (nb > 1) {
+    if (!bsum) bsum = (int64_t*)scratch(c, SC_BSUM, (size_t)nb * nbatch * sizeof(int64_t));
+    if (!bsum) return PM_ERR_NOMEM;
+    hipLaunchKernelGGL(k_scan_reduce<Get>, dim3((unsigned)nb, (unsigned)nbatch),
+                       dim3(SCAN_THREADS), 0, c->stream, A, n, bsum);
   }
-  int64_t* bsum = bsum_ext ? bsum_ext : (int64_t*)scratch(c, SC_BSUM, (size_t)nb * sizeof(int64_t));
-  if (!bsum) return PM_ERR_NOMEM;
-  hipLaunchKernelGGL(k_scan_reduce<Get>, dim3((unsigned)nb), dim3(SCAN_THREADS), 0,
-                     c->stream, g, n, bsum);
-  hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(1024), 0, c->stream, bsum, nb, out + n);
-  hipLaunchKernelGGL(k_scan_down<Get>, dim3((unsigned)nb), dim3(SCAN_THREADS), 0,
-                     c->stream, g, n, bsum, out);
+  const bool scanned = nb > SCAN_DIRECT;
+  if (scanned)
+    hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)nbatch), dim3(1024), 0, c->stream, bsum, nb);
+  hipLaunchKernelGGL(k_scan_down<Get>, dim3((unsigned)nb, (unsigned)nbatch), dim3(SCAN_THREADS),
+                     0, c->stream, A, n, bsum, scanned);
   PM_LAUNCH_CHECK();
   return PM_OK;
 }
 
+template <typename Get>
+pm_status scan_generic(pm_context* c, Get g, int64_t n, int64_t* out) {
+  if (n == 0) {
+    hipLaunchKernelGGL(k_fill<int64_t>, dim3(1), dim3(64), 0, c->stream, out, 1, (int64_t)0);
+    PM_LAUNCH_CHECK();
+    return PM_OK;
+  }
+  ScanArgs<Get> A{};
+  A.g[0] = g;
+  A.out[0] = out;
+  return scan_batch(c, A, 1, n);
+}
 
 }  // namespace pmscan
