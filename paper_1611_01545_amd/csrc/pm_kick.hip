@@ -883,42 +883,59 @@ __global__ __launch_bounds__(BS_T) void k_brick_scan(PlaceArgs A, int B3, int64_
   }
 }
 
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // The movers into the lists of the bricks they arrive in, in no particular order (the
 // brick's wave sorts its list by old index). A thread looks at MV particles' digits in one
-// 16-byte load.
+// 16-byte load. A mover costs a chain of dependent accesses (key, its brick's counter, the
+// list), and movers are a few per wave's 512 particles, so the wave first queues them in
+// LDS and then takes 64 chains at a time instead of up to eight one after the other: 219 ->
+// 112 us with 151 M particles in 262144 bricks, 78 -> 64 us with 18.9 M in 4096 (the rest
+// is the atomics on few counters).
 constexpr int MV = 8;
 __global__ __launch_bounds__(KT) void k_list_arrivals(PlaceArgs A, int lgB3, int64_t nbrick,
                                                      DevErr* err) {
+  __shared__ uint16_t queue[KT / 64][64 * MV];
   const PlaceSpecies& S = A.sp[blockIdx.y];
-  const int64_t i = ((int64_t)blockIdx.x * KT + threadIdx.x) * MV;
-  if (i >= S.n) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t base = ((int64_t)blockIdx.x * KT + (threadIdx.x & ~63)) * MV;  // the wave's first
+  if (base >= S.n) return;
+  const int64_t i = base + lane * MV;
   uint32_t d[MV];
   if (i + MV <= S.n) {  // tdig is 16-byte aligned
     const uint4 q = *(const uint4*)(S.tdig + i);
-    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+    const uint32_t v[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-    for (int k = 0; k < MV; ++k) d[k] = (w[k >> 1] >> (16 * (k & 1))) & 0xffffu;
+    for (int k = 0; k < MV; ++k) d[k] = (v[k >> 1] >> (16 * (k & 1))) & 0xffffu;
   } else {
 #pragma unroll
     for (int k = 0; k < MV; ++k) d[k] = i + k < S.n ? S.tdig[i + k] : 0u;
   }
   const uint32_t mover = 1u << lgB3;
+  const uint64_t lt = lane ? ((~0ull) >> (64 - lane)) : 0ull;
+  int m = 0;
 #pragma unroll
   for (int k = 0; k < MV; ++k) {
-    if (d[k] != mover) continue;
-    const int64_t b = S.mkey[i + k] >> lgB3;
+    const uint64_t at = __ballot(d[k] == mover);
+    if (d[k] == mover) queue[w][m + __popcll(at & lt)] = (uint16_t)(lane * MV + k);
+    m += __popcll(at);
+  }
+  wave_sync();
+  for (int q = lane; q < m; q += 64) {
+    const int64_t j = base + queue[w][q];
+    const int64_t b = S.mkey[j] >> lgB3;
     // counts inconsistent with n (latched by the offset check) leave stale digits
-    const uint32_t left = b < nbrick ? atomicSub(&S.acnt[b], 1u) : 0u;
-    const int64_t slot = left ? (int64_t)S.astart[b] + left - 1 : S.n;
-    if (slot < S.n) S.aidx[slot] = (uint32_t)(i + k);
+    const bool ok = b < nbrick;
+    const uint32_t first = S.astart[ok ? b : 0];
+    const uint32_t left = ok ? atomicSub(&S.acnt[b], 1u) : 0u;
+    const int64_t slot = left ? (int64_t)first + left - 1 : S.n;
+    if (slot < S.n) S.aidx[slot] = (uint32_t)j;
     else latch_error(err, ERRBIT_CORRUPT);
   }
-}
-
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Lanes of the wave whose `valid` digit equals this lane's.
