@@ -13,22 +13,29 @@
 // Weights are exact: a compressed position sits at the bin centre (2u+1)/(512 n_c),
 // i.e. at (2u+1) r / 512 mesh cells, so each axis weight is an integer multiple of
 // 1/512 and their product an integer multiple of 2^-27. Each species' weights are
-// summed as integers in LDS (exact, so independent of the order of the atomics): a
-// 32-bit word per node that wraps, plus a 16-bit count of its wraps, so 48 bits per
-// node in 6 bytes. Each species' sum is scaled by its mass in FP64, rounded once to
-// float and added to the thread's float node densities in a fixed species order: every
-// run, and the recomputation in the adjoint, gives bit-identical densities.
+// summed as 32-bit integers in LDS (exact, so independent of the order of the atomics).
+// Each species' sum is scaled by its mass in FP64, rounded once to float and added in a
+// fixed species order: every run, and the recomputation in the adjoint, gives
+// bit-identical densities. A node that 32 particles' weight falls on wraps its sum; the
+// tile's total shows it, and such a tile is summed again in 64 bits.
 //
-// The tile loop is bound by latency (cell offsets, then particle codes, per species),
-// so what pays is tiles in flight: the 26 KB of LDS and 74 VGPRs of a 16^3-node tile
-// let six workgroups share a CU (64-bit sums in LDS and FP64 densities held four), and
-// the prefix over the tile's cells is a DPP wave scan with a single barrier.
+// The tile loop is bound by its instructions, about half of them per node and half per
+// particle, and by the latency of two dependent loads (cell offsets, then codes). So both
+// species are in flight together, with a sum each per node and one conversion pass; the
+// nodes that a particle reaches outside the tile have (shared) slots of their own, which
+// leaves no bounds test per corner; the atomics return nothing (a returned old value
+// detected the wraps one by one before); and a wave finds its lanes' cells by a running
+// maximum over marks instead of a binary search per particle. 512 threads and 47 (54) KB
+// of LDS for tiles of 4^3 (8^3) cells: three tiles on a CU, with no register spilled (any
+// scratch use doubled the time of these short-lived waves). With the offset scans, for two
+// species: 39 -> 12 us on 64^3 nodes, 281 -> 152 at 256^3 (8^3-cell tiles), 429 -> 363 at
+// 512^3, 3.02 -> 2.76 ms at 1024^3, 270 -> 227 us on the 128^3 coarse mesh with one node
+// per cell.
 #include "pm_codec.h"
 #include "pm_scan.h"
 
 namespace {
 
-constexpr int DEP_THREADS = 256;
 constexpr int MAX_SP = 4;
 
 struct DepSpecies {
@@ -43,204 +50,451 @@ struct DepArgs {
   int T;   // tile side in cells
   int r;   // mesh cells per compression cell
   int R;   // tile side in nodes
+  int lgt; // log2(tiles per box side)
 };
 
-// byte offset of the cell starts after the weight sums (low words, then carries)
-__host__ __device__ inline size_t dep_cst_offset(int R3) {
-  return ((size_t)R3 * 4 + (size_t)((R3 + 1) / 2) * 4 + 7) & ~(size_t)7;
+// Node (x, y, z) of a tile of R nodes per side, -1 <= x, y, z <= R, is slot
+// ((z + 1) Rp + y + 1) Rp + x + 1, Rp = R + 1: node R of a row falls on node -1 of the
+// next one, and neither belongs to the tile, so a particle adds to its eight corners at
+// constant slot distances without a bounds test.
+__host__ __device__ constexpr int dep_slots(int R) {
+  return (R + 1) * (R + 1) * (R + 1) + (R + 1) * (R + 1) + (R + 1) + 1;
+}
+// Particles per window, cell tables in LDS at once, type of a cell index of the tile.
+// 16^3-node tiles of 4^3 cells hold few particles: both species' tables are there and their
+// loads in flight together. Those of 8^3 cells take the species' tables one after the other
+// (three tiles on a CU).
+template <int TT> constexpr int dep_win() { return TT == 4 ? 1024 : TT == 8 ? 1536 : 2048; }
+template <int TT> constexpr int dep_tabs() { return TT == 4 ? 2 : 1; }
+template <int TT> struct DepMark { using T = uint16_t; };
+template <> struct DepMark<4> { using T = uint8_t; };  // 125 cells
+template <int TT>
+size_t dep_lds_bytes(int R, int NE) {
+  return (size_t)dep_slots(R) * 8 + (size_t)dep_tabs<TT>() * (NE * 8 + (NE + 1) * 4) +
+         (size_t)dep_tabs<TT>() * dep_win<TT>() * sizeof(typename DepMark<TT>::T);
+}
+
+// Sum over the 64 lanes of a wave by DPP, in lane 63
+__device__ inline double wave_sum_dpp(double v) {
+  auto step = [&](auto ctrl, auto rows) {
+    constexpr int C = decltype(ctrl)::value, M = decltype(rows)::value;
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, C, M, 0xf, false);
+    const uint32_t hi =
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)((uint64_t)b >> 32), C, M, 0xf, false);
+    v += __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+  };
+  step(IC<0x111>{}, IC<0xf>{});
+  step(IC<0x112>{}, IC<0xf>{});
+  step(IC<0x114>{}, IC<0xf>{});
+  step(IC<0x118>{}, IC<0xf>{});
+  step(IC<0x142>{}, IC<0xa>{});
+  step(IC<0x143>{}, IC<0xc>{});
+  return v;
 }
 
 __device__ inline int wrapc(int c, int n) { return c < 0 ? c + n : (c >= n ? c - n : c); }
+
+// Inclusive running maximum over the 64 lanes of a wave by DPP (values >= 0)
+__device__ inline int wave_incl_max_dpp(int v) {
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));
+  return v;
+}
+
+constexpr int DEP_THREADS = 512;
+
+// The three codes of particle j of n: one unaligned load of 4 (8) bytes, moved back by
+// `back` bytes from the array's end where it would pass it (shift the result down by as
+// many); byte loads for a single particle.
+template <int PB, typename CT>
+__device__ __forceinline__ CT dep_codes(const void* pos, int64_t n, uint32_t j, int& back) {
+  const uint8_t* p = (const uint8_t*)pos;
+  const int64_t at = (int64_t)(3 * PB) * j, last = (int64_t)(3 * PB) * n - (int64_t)sizeof(CT);
+  CT c = 0;
+  back = 0;
+  if (last >= 0) {  // two particles and more (uniform)
+    const int64_t from = at < last ? at : last;
+    back = (int)(at - from);
+    __builtin_memcpy(&c, p + from, sizeof(CT));
+  } else {
+    for (int q = 0; q < 3 * PB; ++q) c |= (CT)p[at + q] << (8 * q);
+  }
+  return c;
+}
+
+// One particle's eight weights into slots of type NT; the weight units added.
+template <int PB, typename NT, typename CT>
+__device__ __forceinline__ uint32_t dep_add(NT* node, CT code, uint32_t org, int r, int Rp) {
+  constexpr int FB = 8 * PB + 1;  // fractional bits of a mesh coordinate
+  constexpr int ONE = 1 << FB;    // one mesh cell
+  int sl[3], f[3];
+  code >>= 8 * (org >> 24);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    // position inside the cell in units of 2^-FB mesh cells (1/512 for PB = 1)
+    const int c = (int)((uint32_t)(code >> (8 * PB * a)) & ((1u << (8 * PB)) - 1u));
+    const int gl = (2 * c + 1) * r;
+    sl[a] = (int)(int8_t)(org >> (8 * a)) + (gl >> FB);
+    f[a] = gl & (ONE - 1);
+  }
+  // nothing to add, or a particle of the shell that reaches no node of the tile
+  if ((sl[0] | sl[1] | sl[2]) < 0) return 0;
+  NT* p = node + ((sl[2] * Rp + sl[1]) * Rp + sl[0]);
+  const uint32_t wx[2] = {(uint32_t)(ONE - f[0]), (uint32_t)f[0]},
+                 wy[2] = {(uint32_t)(ONE - f[1]), (uint32_t)f[1]},
+                 wz[2] = {(uint32_t)(ONE - f[2]), (uint32_t)f[2]};
+  uint32_t sum = 0;
+#pragma unroll
+  for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+    for (int dy = 0; dy < 2; ++dy)
+#pragma unroll
+      for (int dx = 0; dx < 2; ++dx) {
+        uint32_t W;  // units of 2^-27
+        if constexpr (PB == 1) {
+          W = __umul24(__umul24(wx[dx], wy[dy]), wz[dz]);  // exact
+        } else {
+          const uint64_t w3 = (uint64_t)wx[dx] * (uint64_t)wy[dy] * (uint64_t)wz[dz];
+          W = (uint32_t)((w3 + (1ull << 23)) >> 24);  // 2^-51 -> 2^-27, rounded
+          sum += W;
+        }
+        atomicAdd(&p[(dz * Rp + dy) * Rp + dx], (NT)W);
+      }
+  return PB == 1 ? 1u << 27 : sum;
+}
 
 // TT: tile side in cells (compile time, 0: runtime A.T); PB: position bytes per axis. With
 // PB = 2 the offset inside a cell has 17 fractional bits of a mesh cell per axis, and each
 // node's weight (the exact product, a multiple of 2^-51) is rounded to a multiple of
 // 2^-27, the unit of the 1-byte form, so that the same integer sums apply.
-template <int TT, int PB = 1>
-__global__ __launch_bounds__(DEP_THREADS) void k_deposit_tile(DepArgs A, Geom g, float* rho) {
-  using PT = typename PosCode<PB>::T;
-  constexpr int FB = 8 * PB + 1;              // fractional bits of a mesh coordinate
-  constexpr int ONE = 1 << FB;                // one mesh cell
-  constexpr uint32_t FMASK = (uint32_t)ONE - 1u;
-  extern __shared__ unsigned char smem[];
+// MORE: more than two species.
+template <int TT, int PB, bool MORE>
+__global__ __launch_bounds__(DEP_THREADS, MORE || TT == 0 ? 4 : 6) void k_deposit_tile(
+    DepArgs A, Geom g, float* rho) {
+  using CT = typename std::conditional<PB == 1, uint32_t, uint64_t>::type;
+  constexpr int NT = DEP_THREADS, NW = NT / 64;
+  constexpr int WIN = dep_win<TT>(), TABS = dep_tabs<TT>();
+  constexpr int U = WIN / NT;                 // chunks of 64 particles per wave and window
+  using MT = typename DepMark<TT>::T;
+  extern __shared__ __align__(16) unsigned char smem[];
   // compile-time tiles have T r = 16 nodes per side (T = 16 / r)
   const int T = TT ? TT : A.T, R = TT ? 16 : A.R, r = TT ? 16 / TT : A.r;
   const bool spread = !TT && r == 1;  // the coarse mesh of the two-level force
   const int E = T + 1;              // extended cells per side
   const int NE = E * E * E;
-  const int R3 = R * R * R;
-  __shared__ int wsum[DEP_THREADS / 64];
-  // a node's weight sum is hi 2^32 + lo: lo wraps in the LDS atomics, and each wrap
-  // increments a 16-bit carry counter (two per word)
-  uint32_t* wlo = (uint32_t*)smem;                    // [R3]
-  uint32_t* whi = wlo + R3;                           // [(R3 + 1) / 2]
-  int64_t* cst = (int64_t*)(smem + dep_cst_offset(R3));  // [NE] stream start of each extended cell
-  int* pre = (int*)(cst + NE);                        // [NE + 1] particle prefix over extended cells
-  const int nt = (int)(g.nc / T);
-  const int64_t tile = xcd_tile(blockIdx.x, (int64_t)nt * nt * nt);
-  const int tx = (int)(tile % nt), ty = (int)((tile / nt) % nt), tz = (int)(tile / ((int64_t)nt * nt));
+  const int Rp = R + 1, NS = TT ? dep_slots(16) : dep_slots(R);
+  __shared__ int wsum[2][NW];
+  __shared__ double lost[NW];  // weight units missing from the sums, per wave
+  uint32_t* node = (uint32_t*)smem;                      // [2][NS] weight sums of two species
+  uint2* tab = (uint2*)(node + 2 * NS);                  // [TABS][NE] stream start, origin
+  int* pre = (int*)(tab + TABS * NE);                    // [TABS][NE + 1] particles before
+  MT* mark = (MT*)(pre + TABS * (NE + 1));               // [TABS][WIN] extended cells
+  const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
+  const uint32_t ntm = (uint32_t)(1 << A.lgt) - 1u;  // tiles per side: a power of two
+  const int tx = (int)((uint32_t)tile & ntm), ty = (int)((uint32_t)(tile >> A.lgt) & ntm),
+            tz = (int)(tile >> (2 * A.lgt));
   const int ncs = (int)g.nc;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
-  for (int i = threadIdx.x; i < R3; i += DEP_THREADS) wlo[i] = 0u;
-  // per-thread density of its nodes i = threadIdx.x + k DEP_THREADS (R <= 16, so at most
-  // 16 nodes), summed over species (and segments) in a fixed order
-  constexpr int NPT = 4096 / DEP_THREADS;
+  for (int i = threadIdx.x; i < NS / 2; i += NT) ((uint4*)node)[i] = make_uint4(0, 0, 0, 0);
+  if (threadIdx.x < (NS & 1) * 2) node[2 * NS - 2 + threadIdx.x] = 0;
+  for (int i = threadIdx.x; i < TABS * WIN * (int)sizeof(MT) / 4; i += NT)
+    ((uint32_t*)mark)[i] = 0u;
+  // per-thread density of its slots i = threadIdx.x + k NT, summed over species in order
+  constexpr int NPT = (dep_slots(16) + NT - 1) / NT;
   float racc[NPT];
 #pragma unroll
   for (int k = 0; k < NPT; ++k) racc[k] = 0.0f;
 
-  for (int s = 0; s < A.n_sp; ++s) {
-    const DepSpecies sp = A.sp[s];
-    // counts of the extended cells, then an exclusive prefix (single pass per wave)
-    __syncthreads();
-    for (int i = threadIdx.x; i < (R3 + 1) / 2; i += DEP_THREADS) whi[i] = 0u;
-    for (int e = threadIdx.x; e < NE; e += DEP_THREADS) {
-      int ex = e % E, ey = (e / E) % E, ez = e / (E * E);
-      int cx = wrapc(tx * T + ex - 1, ncs), cy = wrapc(ty * T + ey - 1, ncs),
-          cz = wrapc(tz * T + ez - 1, ncs);
-      uint32_t key = cell_key(g, cx, cy, cz);
-      const int64_t o0 = sp.off[key], o1 = sp.off[key + 1];
-      cst[e] = o0;
-      pre[e + 1] = (int)(o1 - o0);
-    }
-    __syncthreads();
-    {
-      // block-wide inclusive prefix of pre[1..NE]: each thread owns K consecutive
-      const int K = (NE + DEP_THREADS - 1) / DEP_THREADS;
-      const int e0 = 1 + threadIdx.x * K;
-      int loc = 0;
-      for (int k = 0; k < K; ++k)
-        if (e0 + k <= NE) loc += pre[e0 + k];
-      int base = pmscan::block_excl_scan_i32(loc, wsum);
-      for (int k = 0; k < K; ++k)
-        if (e0 + k <= NE) {
-          base += pre[e0 + k];
-          pre[e0 + k] = base;
+  const int n_sp = MORE ? A.n_sp : min(A.n_sp, 2);
+  for (int s0 = 0; s0 < (MORE ? n_sp : min(n_sp, 1)); s0 += 2) {
+    const int ns = min(2, n_sp - s0);
+    // cells of both species: a thread takes K consecutive extended cells
+    constexpr int KMAX = TT ? ((TT + 1) * (TT + 1) * (TT + 1) + NT - 1) / NT : 2;
+    const int K = TT ? KMAX : (NE + NT - 1) / NT;
+    const int e0 = threadIdx.x * K;
+    const bool cells = wv * 64 * K < NE;  // this wave has any
+    uint32_t start[2][KMAX];  // first particle and particle count of the thread's cells
+    int cnt[2][KMAX];
+    auto fetch = [&]() {
+#pragma unroll
+      for (int k = 0; k < KMAX; ++k) {
+        const int e = e0 + k;
+        const bool in = k < K && e < NE;
+        const int ex = e % E, ey = (e / E) % E, ez = e / (E * E);
+        const uint32_t key =
+            in ? cell_key(g, wrapc(tx * T + ex - 1, ncs), wrapc(ty * T + ey - 1, ncs),
+                          wrapc(tz * T + ez - 1, ncs))
+               : 0u;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const int64_t* off = A.sp[s0 + (s < ns ? s : 0)].off;
+          const int64_t o0 = off[key], o1 = off[key + 1];
+          start[s][k] = (uint32_t)o0;
+          cnt[s][k] = in && s < ns ? (int)(o1 - o0) : 0;
         }
-      if (threadIdx.x == 0) pre[0] = 0;
+      }
+    };
+    int before[2] = {0, 0}, loc[2] = {0, 0};
+    if (cells) {
+      fetch();
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) loc[s] += cnt[s][k];
+        before[s] = pmscan::wave_incl_scan_dpp(loc[s]);
+      }
     }
-    __syncthreads();
-    const int P = pre[NE];
-    // U particles per thread per round: their code loads are issued together
-    constexpr int U = 2;
-    static_assert(DEP_THREADS * U == 512, "the spread order is a transpose of 8 x 64 slots");
-    // the carries count at most 2^16 wraps, i.e. 2^48 weight units per node: segments
-    // of 2^21 particles (each adds < 2^27 to a node) are flushed one by one; every
-    // tile of a realistic input has a single segment
-    constexpr int SEG = 1 << 21;
-    for (int s0 = 0;; s0 += SEG) {
-      const int s1 = P - s0 > SEG ? s0 + SEG : P;
-      for (int rb = s0; rb < s1; rb += DEP_THREADS * U) {  // uniform across the block
-        int eu[U];
-        int64_t ju[U];
-        uint32_t pb[U][3];
-        bool ok[U];
+    if (lane == 63) {
+      wsum[0][wv] = before[0];
+      wsum[1][wv] = before[1];
+    }
+    __syncthreads();  // also: the last pair is done with the tables
+    int np[2] = {0, 0};  // particles of the tile and its shell
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          // slot l of the round takes particle l, or, with one mesh cell per compression
-          // cell (8 neutrinos per cell on 8^3 nodes), particle (l % 8) 64 + l / 8: the
-          // lanes of one atomic then hit the nodes of eight different cells instead of
-          // the same eight nodes (spread)
-          const int l = (int)threadIdx.x + u * DEP_THREADS;
-          const int q = rb + (spread ? ((l & 7) << 6) + (l >> 3) : l);
-          // extended cell of flat particle q: largest e with pre[e] <= q
-          int lo = 0, hi = NE;
-          while (hi - lo > 1) {
-            int mid = (lo + hi) >> 1;
-            if (pre[mid] <= q) lo = mid; else hi = mid;
-          }
-          eu[u] = lo;
-          const int64_t j = cst[lo] + (q - pre[lo]);
-          // counts inconsistent with n are latched by the offset check; q >= s1 is padding
-          ok[u] = q < s1 && j < sp.n;
-          ju[u] = ok[u] ? j : 0;  // n > 0 whenever P > 0
-        }
-        // all code loads of the round, then the arithmetic
+    for (int s = 0; s < 2; ++s) {
+      before[s] -= loc[s];
+      for (int w = 0; w * 64 * K < NE; ++w) {  // the waves with cells
+        const int v = wsum[s][w];
+        before[s] += w < wv ? v : 0;
+        np[s] += v;
+      }
+      np[s] = __builtin_amdgcn_readfirstlane(np[s]);
+    }
+    // species s's table into slot t of the tables
+    auto build = [&](int s, int t) {
+      if (!cells) return;
+      int at = s ? before[1] : before[0];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-          for (int a = 0; a < 3; ++a) pb[u][a] = ((const PT*)sp.pos)[3 * ju[u] + a];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          if (!ok[u]) continue;
-          const int e = eu[u];
+      for (int k = 0; k < KMAX; ++k) {
+        const int e = e0 + k;
+        if (k < K && e < NE) {
           const int ex = e % E, ey = (e / E) % E, ez = e / (E * E);
-          int li[3], f[3];
-          const int le[3] = {ex - 1, ey - 1, ez - 1};
-#pragma unroll
-          for (int a = 0; a < 3; ++a) {
-            // position inside the cell in units of 2^-FB mesh cells (1/512 for PB = 1)
-            int gl = (2 * (int)pb[u][a] + 1) * r;
-            li[a] = le[a] * r + (gl >> FB);
-            f[a] = (int)((uint32_t)gl & FMASK);
-          }
-#pragma unroll
-          for (int dz = 0; dz < 2; ++dz) {
-            int nz = li[2] + dz;
-            int wz = dz ? f[2] : ONE - f[2];
-            if (nz < 0 || nz >= R || wz == 0) continue;
-#pragma unroll
-            for (int dy = 0; dy < 2; ++dy) {
-              int ny = li[1] + dy;
-              int wy = dy ? f[1] : ONE - f[1];
-              if (ny < 0 || ny >= R || wy == 0) continue;
-#pragma unroll
-              for (int dx = 0; dx < 2; ++dx) {
-                int nx = li[0] + dx;
-                int wx = dx ? f[0] : ONE - f[0];
-                if (nx < 0 || nx >= R || wx == 0) continue;
-                uint32_t W;  // units of 2^-27
-                if constexpr (PB == 1) {
-                  W = (uint32_t)(wx * wy) * (uint32_t)wz;  // exact
-                } else {
-                  const uint64_t w3 = (uint64_t)wx * (uint64_t)wy * (uint64_t)wz;
-                  W = (uint32_t)((w3 + (1ull << 23)) >> 24);  // 2^-51 -> 2^-27, rounded
-                }
-                const int i = (nz * R + ny) * R + nx;
-                const uint32_t old = atomicAdd(&wlo[i], W);
-                if (old > 0xffffffffu - W) atomicAdd(&whi[i >> 1], 1u << ((i & 1) * 16));
-              }
-            }
-          }
+          // slot of the cell's first node per axis, a signed byte each: -r + 1 .. R
+          const uint32_t ox = (uint32_t)((ex - 1) * r + 1) & 255u,
+                         oy = (uint32_t)((ey - 1) * r + 1) & 255u,
+                         oz = (uint32_t)((ez - 1) * r + 1) & 255u;
+          tab[t * NE + e] =
+              make_uint2((s ? start[1][k] : start[0][k]) - (uint32_t)at, ox | oy << 8 | oz << 16);
+          pre[t * (NE + 1) + e] = at;
+          at += s ? cnt[1][k] : cnt[0][k];
+          if (e == NE - 1) pre[t * (NE + 1) + NE] = at;
         }
       }
-      // the segment's integer weight sums into the thread's node densities
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < NPT; ++k) {
-        const int i = threadIdx.x + k * DEP_THREADS;
-        if (i < R3) {
-          const uint64_t w =
-              ((uint64_t)((whi[i >> 1] >> ((i & 1) * 16)) & 0xffffu) << 32) | wlo[i];
-          racc[k] += (float)((double)w * sp.unit);
-          wlo[i] = 0u;
+    };
+    // A window of WIN particles from particle rb of the tile (nw of them). Each cell marks its
+    // first particle of the window and every 64th slot that it reaches, so that a wave finds
+    // its lanes' cells by a running maximum.
+    auto set_marks = [&](int t, int rb, int nw) {
+      const int* pr = pre + t * (NE + 1);
+      MT* mk = mark + t * WIN;
+      for (int e = threadIdx.x; e < NE; e += NT) {
+        const int lo = max(pr[e], rb) - rb, hi = min(pr[e + 1] - rb, nw);
+        if (lo < hi) {
+          mk[lo] = (MT)e;
+          for (int m = (lo | 63) + 1; m < hi; m += 64) mk[m] = (MT)e;
         }
       }
-      if (s1 >= P) break;
+    };
+    struct Batch {
+      CT code[U];
+      uint32_t org[U];  // first slot per axis (bit 7 set: nothing to add), shift of the code
+    };
+    auto load = [&](int s, int t, int rb, int nw, Batch& B) {
+      const DepSpecies& sp = A.sp[s0 + s];
+      const uint2* tb = tab + t * NE;
+      MT* mk = mark + t * WIN;
+      const int lim = spread ? (nw + 511) & ~511 : nw;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        B.org[u] = 0x80u;
+        B.code[u] = 0;
+        const int b = wv * 64 + u * NT;
+        if (b >= lim) continue;  // uniform across the wave
+        const int l = b + lane;
+        int e, q = l;
+        if (spread) {
+          // slot l of 512 takes particle (l % 8) 64 + l / 8: the lanes of one atomic then
+          // hit the nodes of eight different cells (8 neutrinos per cell on one node each)
+          // instead of the same eight nodes
+          q = (l & ~511) + ((l & 7) << 6) + ((l & 511) >> 3);
+          e = mk[q];
+        } else {
+          e = wave_incl_max_dpp((int)mk[l]);
+          mk[l] = 0;  // read once: clear for the next window
+        }
+        const uint2 c = tb[e];
+        const uint32_t j = c.x + (uint32_t)(rb + q);
+        // counts inconsistent with n are latched by the offset check
+        const bool ok = q < nw && (int64_t)j < sp.n;
+        int back;
+        B.code[u] = dep_codes<PB, CT>(sp.pos, sp.n, ok ? j : 0u, back);
+        B.org[u] = ok ? c.y | (uint32_t)back << 24 : 0x80u;
+      }
+    };
+    // the marks of a window, filled in for the spread order (all threads)
+    auto marks_done = [&](int t, int nw) {
       __syncthreads();
-      for (int i = threadIdx.x; i < (R3 + 1) / 2; i += DEP_THREADS) whi[i] = 0u;
+      if (!spread) return;
+      MT* mk = mark + t * WIN;
+      for (int b = wv * 64; b < nw; b += NT)
+        mk[b + lane] = (MT)wave_incl_max_dpp((int)mk[b + lane]);
       __syncthreads();
+    };
+    // species s's window at rb into B (all threads)
+    auto window = [&](int s, int t, int rb, Batch& B) {
+      const int nw = min(WIN, (s ? np[1] : np[0]) - rb);
+      if (spread) {  // (the other order clears the marks as it reads them)
+        __syncthreads();
+        for (int l = threadIdx.x; l < WIN; l += NT) mark[t * WIN + l] = 0;
+      }
+      __syncthreads();
+      set_marks(t, rb, nw);
+      marks_done(t, nw);
+      load(s, t, rb, nw, B);
+    };
+    uint32_t got = 0;  // PB = 1: particles that this thread added
+    double units = 0.0;  // PB = 2: weight units
+    auto add = [&](auto* to, const Batch& B) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t w = dep_add<PB>(to, B.code[u], B.org[u], r, Rp);
+        if constexpr (PB == 1) got += w >> 27;
+        else units += (double)w;
+      }
+    };
+    // the windows of species s from rb on
+    auto rest = [&](int s, int t, auto* to, int rb) {
+      for (; rb < (s ? np[1] : np[0]) && rb >= 0; rb += WIN) {
+        Batch B;
+        window(s, t, rb, B);
+        add(to, B);
+      }
+    };
+
+    if constexpr (TABS == 2) {
+      // the first windows of both species, their loads in flight together
+      build(0, 0);
+      build(1, 1);
+      __syncthreads();
+      const int n0 = min(WIN, np[0]), n1 = min(WIN, np[1]);
+      set_marks(0, 0, n0);
+      set_marks(1, 0, n1);
+      __syncthreads();
+      Batch B0, B1;
+      load(0, 0, 0, n0, B0);
+      load(ns - 1, 1, 0, n1, B1);
+      add(node, B0);
+      add(node + NS, B1);
+      rest(0, 0, node, WIN);
+      rest(1, 1, node + NS, WIN);
+    } else {
+      build(0, 0);
+      rest(0, 0, node, 0);
+      if (ns > 1) {
+        __syncthreads();
+        build(1, 0);
+        rest(1, 0, node + NS, 0);
+      }
     }
-  }
-  const int64_t ng = g.ng;
-  if (TT) {
-    // R = 16: node i = threadIdx.x + 256 k has lx = i & 15, ly = (i >> 4) & 15, lz = k
-    const int64_t ng2 = ng * ng;
-    float* dst = rho + (int64_t)tz * 16 * ng2 +
-                 ((int64_t)ty * 16 + ((threadIdx.x >> 4) & 15)) * ng + (int64_t)tx * 16 +
-                 (threadIdx.x & 15);
-#pragma unroll
-    for (int k = 0; k < NPT; ++k) dst[k * ng2] = racc[k];
-  } else {
+    __syncthreads();
+    // Where a sum passes 2^32 (a node of 32 particles' weight), the total falls short of the
+    // weights added.
+    const double unit0 = A.sp[s0].unit, unit1 = ns > 1 ? A.sp[s0 + 1].unit : 0.0;
+    double sum = 0.0;
+    float dens[NPT];
 #pragma unroll
     for (int k = 0; k < NPT; ++k) {
-      const int i = threadIdx.x + k * DEP_THREADS;
-      if (i < R3) {
-        int lx = i % R, ly = (i / R) % R, lz = i / (R * R);
-        int64_t gx = (int64_t)tx * R + lx, gy = (int64_t)ty * R + ly,
-                gz = (int64_t)tz * R + lz;
-        rho[(gz * ng + gy) * ng + gx] = racc[k];
+      const int i = threadIdx.x + k * NT;
+      uint32_t v0 = 0, v1 = 0;
+      if (i < NS) {
+        v0 = node[i];
+        v1 = node[NS + i];  // 0 without a second species
       }
+      const double w0 = (double)v0, w1 = (double)v1;
+      sum += w0 + w1;
+      dens[k] = (MORE ? racc[k] : 0.0f) + (float)(w0 * unit0);
+      dens[k] += (float)(w1 * unit1);
+    }
+    if constexpr (PB == 1) units = (double)got * 0x1p27;
+    sum = wave_sum_dpp(units - sum);
+    if (lane == 63) lost[wv] = sum;
+    __syncthreads();
+    double all = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) all += lost[w];
+    if (all == 0.0) {
+#pragma unroll
+      for (int k = 0; k < NPT; ++k) racc[k] = dens[k];
+    } else {
+      // again, one species at a time in 64-bit sums over both arrays
+      unsigned long long* wide = (unsigned long long*)node;
+      if constexpr (!MORE)
+#pragma unroll
+        for (int k = 0; k < NPT; ++k) racc[k] = 0.0f;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        if (s >= ns) break;
+        __syncthreads();
+        for (int i = threadIdx.x; i < 2 * NS; i += NT) node[i] = 0;
+        if (TABS == 1) {
+          if (cells) fetch();
+          build(s, 0);
+        }
+        rest(s, TABS == 2 ? s : 0, wide, 0);
+        __syncthreads();
+        const double unit = s ? unit1 : unit0;
+#pragma unroll
+        for (int k = 0; k < NPT; ++k) {
+          const int i = threadIdx.x + k * NT;
+          if (i < NS) racc[k] += (float)((double)wide[i] * unit);
+        }
+      }
+    }
+    if (MORE && s0 + 2 < n_sp) {  // the next pair's sums start at 0
+      __syncthreads();
+      for (int i = threadIdx.x; i < 2 * NS; i += NT) node[i] = 0;
+    }
+  }
+  // the slots' densities through LDS into rows of the mesh
+  float* out = (float*)node;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < NPT; ++k) {
+    const int i = threadIdx.x + k * NT;
+    if (i < NS) out[i] = racc[k];
+  }
+  __syncthreads();
+  const int64_t ng = g.ng;
+  if (TT) {
+    // R = 16: four consecutive nodes x = 4 (tid % 4) .. of row y = tid / 4 % 16, planes
+    // tid / 64 + NW k
+    const int lx = 4 * (threadIdx.x & 3), ly = (threadIdx.x >> 2) & 15;
+    const bool aligned = ((uintptr_t)rho & 15) == 0;  // the caller's pointer: any float
+#pragma unroll
+    for (int k = 0; k < 16 / NW; ++k) {
+      const int lz = (threadIdx.x >> 6) + NW * k;
+      const float* q = out + ((lz + 1) * 17 + ly + 1) * 17 + lx + 1;
+      float* d = rho + (((int64_t)tz * 16 + lz) * ng + (int64_t)ty * 16 + ly) * ng +
+                 (int64_t)tx * 16 + lx;
+      if (aligned) {
+        *(float4*)d = make_float4(q[0], q[1], q[2], q[3]);
+      } else {
+        for (int a = 0; a < 4; ++a) d[a] = q[a];
+      }
+    }
+  } else {
+    const int R3 = R * R * R;
+    for (int i = threadIdx.x; i < R3; i += NT) {
+      const int lx = i % R, ly = (i / R) % R, lz = i / (R * R);
+      const int64_t gx = (int64_t)tx * R + lx, gy = (int64_t)ty * R + ly,
+                    gz = (int64_t)tz * R + lz;
+      rho[(gz * ng + gy) * ng + gx] = out[((lz + 1) * Rp + ly + 1) * Rp + lx + 1];
     }
   }
 }
@@ -314,28 +568,31 @@ pm_status run_deposit_tile(pm_context* c, const pm_species* sp, int n_sp,
   A.T = deposit_tile_cells(g);
   A.R = A.T * g.r;
   if (A.R > 16) return PM_ERR_SHAPE;  // at most 16 nodes per thread
-  int nt = (int)(g.nc / A.T);
-  const size_t ne = (size_t)(A.T + 1) * (A.T + 1) * (A.T + 1);
-  size_t lds = dep_cst_offset(A.R * A.R * A.R) + ne * 8 + (ne + 1) * 4;
+  const int nt = (int)(g.nc / A.T);  // a power of two, as nc and T are
+  while ((1 << A.lgt) < nt) ++A.lgt;
+  const int ne = (A.T + 1) * (A.T + 1) * (A.T + 1);
   ProfScope ps(c, ST_DEPOSIT);
-  const dim3 grid((unsigned)((int64_t)nt * nt * nt));
+  const unsigned grid = (unsigned)((int64_t)nt * nt * nt);
   // the compile-time variants assume T r = 16; one position width for every species
   const int kind = common_width_kind(sp, n_sp);
   if (kind < 0) return PM_ERR_ARG;
+  auto launch = [&](auto tt, auto pb) {
+    constexpr int TT = decltype(tt)::value, PB = decltype(pb)::value;
+    const size_t lds = dep_lds_bytes<TT>(A.R, ne);
+    if (A.n_sp > 2)
+      hipLaunchKernelGGL((k_deposit_tile<TT, PB, true>), dim3(grid), dim3(DEP_THREADS), lds,
+                         c->stream, A, g, rho);
+    else
+      hipLaunchKernelGGL((k_deposit_tile<TT, PB, false>), dim3(grid), dim3(DEP_THREADS), lds,
+                         c->stream, A, g, rho);
+  };
   if (width_pos(sp[0]) == 1) {
-    if (A.T == 4 && A.r == 4)
-      hipLaunchKernelGGL(k_deposit_tile<4>, grid, dim3(DEP_THREADS), lds, c->stream, A, g, rho);
-    else if (A.T == 8 && A.r == 2)
-      hipLaunchKernelGGL(k_deposit_tile<8>, grid, dim3(DEP_THREADS), lds, c->stream, A, g, rho);
-    else
-      hipLaunchKernelGGL(k_deposit_tile<0>, grid, dim3(DEP_THREADS), lds, c->stream, A, g, rho);
+    if (A.T == 4 && A.r == 4) launch(IC<4>{}, IC<1>{});
+    else if (A.T == 8 && A.r == 2) launch(IC<8>{}, IC<1>{});
+    else launch(IC<0>{}, IC<1>{});
   } else {
-    if (A.T == 4 && A.r == 4)
-      hipLaunchKernelGGL((k_deposit_tile<4, 2>), grid, dim3(DEP_THREADS), lds, c->stream, A, g,
-                         rho);
-    else
-      hipLaunchKernelGGL((k_deposit_tile<0, 2>), grid, dim3(DEP_THREADS), lds, c->stream, A, g,
-                         rho);
+    if (A.T == 4 && A.r == 4) launch(IC<4>{}, IC<2>{});
+    else launch(IC<0>{}, IC<2>{});
   }
   PM_LAUNCH_CHECK();
   return PM_OK;
