@@ -568,68 +568,8 @@ pm_status pm_unpack(pm_ctx c, const uint8_t* buf, int64_t len, pm_species* out, 
   // code widths: a valid word, equal to the destination's
   if (wword > 0xffffu || !widths_valid((int32_t)wword)) return PM_ERR_CORRUPT;
   if ((int32_t)wword != out->widths) return PM_ERR_ARG;
-  const int P = width_pos(*out), V = width_vel(*out);
-  const uint64_t RB = 3 * (uint64_t)(P + V);
-  const uint8_t* body = buf + 64;
-  uint64_t cs = 0;
-  for (uint64_t i = 0; i < blen; ++i) cs += (2ull * i + 1ull) * body[i];
-  if (cs != csum) return PM_ERR_CORRUPT;
-  const int64_t ncell = c->g.ncell3;
-  std::vector<uint8_t> count((size_t)ncell);
-  std::vector<uint64_t> esc;
-  std::vector<uint8_t> pos((size_t)n * 3 * P);
-  std::vector<uint8_t> vel((size_t)n * 3 * V);
-  uint64_t off = 0, p = 0;
-  int32_t jmin = 65536, jmax = -1;
-  for (int64_t cc = 0; cc < ncell; ++cc) {
-    if (off >= blen) return PM_ERR_CORRUPT;
-    uint64_t k = body[off++];
-    if (k == 255) {
-      if (off + 4 > blen) return PM_ERR_CORRUPT;
-      uint32_t kk;
-      std::memcpy(&kk, body + off, 4);
-      off += 4;
-      if (kk < 255) return PM_ERR_CORRUPT;
-      k = kk;
-      esc.push_back((uint64_t)cc);
-      esc.push_back(k);
-    }
-    count[(size_t)cc] = (uint8_t)(k >= 255 ? 255 : k);
-    if (p + k > n || off + RB * k > blen) return PM_ERR_CORRUPT;
-    for (uint64_t q = 0; q < k; ++q, ++p, off += RB) {
-      // little-endian codes in the stream; the device arrays hold them in the host's
-      // byte order, which is little-endian on every machine this library runs on
-      const uint8_t* r = body + off;
-      std::memcpy(&pos[3 * P * p], r, 3 * P);
-      for (int a = 0; a < 3; ++a) {
-        int32_t w = r[3 * P + V * a];
-        if (V == 2) w |= (int32_t)r[3 * P + V * a + 1] << 8;
-        jmin = w < jmin ? w : jmin;
-        jmax = w > jmax ? w : jmax;
-      }
-      std::memcpy(&vel[3 * V * p], r + 3 * P, 3 * V);
-    }
-  }
-  if (p != n || off != blen) return PM_ERR_CORRUPT;
-  const int64_t n_esc = (int64_t)esc.size() / 2;
-  if (n_esc > out->cap_esc) {
-    c->last_detail = n_esc;
-    return PM_ERR_CAPACITY;
-  }
-  pm_shdr h{};
-  h.v_max = vmax;
-  h.j_min = jmin;
-  h.j_max = jmax;
-  h.n_esc = n_esc;
-  PM_HIP_CHECK(hipStreamSynchronize(c->stream));
-  PM_HIP_CHECK(hipMemcpy(out->count, count.data(), (size_t)ncell, hipMemcpyHostToDevice));
-  if (n > 0) {
-    PM_HIP_CHECK(hipMemcpy(out->pos, pos.data(), pos.size(), hipMemcpyHostToDevice));
-    PM_HIP_CHECK(hipMemcpy(out->vel, vel.data(), vel.size(), hipMemcpyHostToDevice));
-  }
-  if (n_esc > 0)
-    PM_HIP_CHECK(hipMemcpy(out->esc, esc.data(), esc.size() * 8, hipMemcpyHostToDevice));
-  PM_HIP_CHECK(hipMemcpy(out->hdr, &h, sizeof(h), hipMemcpyHostToDevice));
+  const pm_status st = run_unpack(c, buf + 64, (int64_t)blen, csum, vmax, out);
+  if (st != PM_OK) return st;
   if (mass) *mass = m;
   if (species_id) *species_id = (int32_t)sid;
   return PM_OK;

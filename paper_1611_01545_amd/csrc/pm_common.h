@@ -228,6 +228,9 @@ pm_status run_species_offsets(pm_context* c, const pm_species* sp, int n_sp, int
 pm_status run_finalize_counts(pm_context* c, const uint32_t* cnt32, pm_species* out);
 pm_status run_pack(pm_context* c, const pm_species* sp, int32_t sid, uint8_t* buf,
                    int64_t cap, int64_t* used);
+// body: the stream after its header, in host memory (synchronous)
+pm_status run_unpack(pm_context* c, const uint8_t* body, int64_t blen, uint64_t csum,
+                     float vmax, pm_species* out);
 pm_status run_reduce(pm_context* c, const pm_species* sp, int n_sp, const float* rho,
                      const float* acc, double* out);
 // the same reductions with every buffer in a fixed device array (no allocation)

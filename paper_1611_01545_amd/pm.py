@@ -400,8 +400,9 @@ class PMContext:
         a = out.c()
         mass = ctypes.c_double()
         sid = ctypes.c_int32()
-        raw = (ctypes.c_uint8 * len(data)).from_buffer_copy(data)
-        check(self.lib.pm_unpack(self.h, ctypes.cast(raw, ctypes.c_void_p), len(data),
+        # the caller's bytes as they are (the call is synchronous)
+        raw = np.frombuffer(data, dtype=np.uint8) if len(data) else np.zeros(1, dtype=np.uint8)
+        check(self.lib.pm_unpack(self.h, ctypes.c_void_p(raw.ctypes.data), len(data),
                                  ctypes.byref(a), ctypes.byref(mass), ctypes.byref(sid)),
               "pm_unpack")
         out.mass = mass.value
