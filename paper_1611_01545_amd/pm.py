@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import math
+from concurrent.futures import ThreadPoolExecutor
 from dataclasses import dataclass
 
 import numpy as np
@@ -104,6 +105,56 @@ def _species_array(species):
     for i, s in enumerate(species):
         arr[i] = s.c()
     return arr
+
+
+_COPY_CHUNK = 16 << 20
+_COPY_THREADS = 4
+
+
+def _device_bytes(t: torch.Tensor) -> bytes:
+    """The content of a contiguous uint8 device tensor as a bytes object.
+
+    A large one is filled in place: 16 MB pieces go to page-locked memory at the link's rate
+    (57 GB/s) and from there into the object by several threads while the next piece is on
+    its way. What costs is touching fresh memory (a fault per 4 KB page, 4 GB/s in one
+    thread), so the object's pages are asked to be large. 153 MB: 69 ms through a tensor and
+    a second copy of it, 6.9 ms this way (6.3 with 8 threads, but 1.5 against 1.1 at 22 MB;
+    10.9 with 4 MB pieces, 7.3 with 8 MB); 2 MB and less in one page fault or copy."""
+    n = t.numel()
+    if n < 2 << 20:
+        return t.cpu().numpy().tobytes()
+    api = ctypes.pythonapi
+    new = ctypes.PYFUNCTYPE(ctypes.py_object, ctypes.c_char_p, ctypes.c_ssize_t)(
+        ("PyBytes_FromStringAndSize", api))
+    address = ctypes.PYFUNCTYPE(ctypes.c_void_p, ctypes.py_object)(("PyBytes_AsString", api))
+    out = new(None, n)  # uninitialised; nobody else has it yet
+    at = address(out)
+    page = 2 << 20
+    lo, hi = -(-at // page) * page, (at + n) // page * page
+    if hi > lo:  # advice only: nothing depends on it
+        ctypes.CDLL(None).madvise(ctypes.c_void_p(lo), ctypes.c_size_t(hi - lo), 14)
+    dst = np.ctypeslib.as_array((ctypes.c_uint8 * n).from_address(at))
+    stage = [torch.empty(min(n, _COPY_CHUNK), dtype=torch.uint8, pin_memory=True)
+             for _ in range(2)]
+    arrived = [torch.cuda.Event() for _ in stage]
+    with torch.cuda.device(t.device), ThreadPoolExecutor(_COPY_THREADS) as pool:
+        def fetch(k):
+            m = min(_COPY_CHUNK, n - k * _COPY_CHUNK)
+            stage[k % 2][:m].copy_(t[k * _COPY_CHUNK: k * _COPY_CHUNK + m], non_blocking=True)
+            arrived[k % 2].record()
+
+        chunks = -(-n // _COPY_CHUNK)
+        fetch(0)
+        for k in range(chunks):
+            if k + 1 < chunks:
+                fetch(k + 1)
+            arrived[k % 2].synchronize()
+            src = stage[k % 2].numpy()
+            base, m = k * _COPY_CHUNK, min(_COPY_CHUNK, n - k * _COPY_CHUNK)
+            cuts = [m * i // _COPY_THREADS for i in range(_COPY_THREADS + 1)]
+            list(pool.map(lambda i: np.copyto(dst[base + cuts[i]: base + cuts[i + 1]],
+                                              src[cuts[i]: cuts[i + 1]]), range(_COPY_THREADS)))
+    return out
 
 
 class PMContext:
@@ -390,7 +441,7 @@ class PMContext:
         check(self.lib.pm_pack(self.h, ctypes.byref(a), int(species_id), _ptr(buf), size,
                                _ptr(used)), "pm_pack")
         self.sync()
-        return buf[: int(used.item())].cpu().numpy().tobytes()
+        return _device_bytes(buf[: int(used.item())])
 
     def unpack(self, data: bytes, n: int, cap_esc: int | None = None):
         import struct

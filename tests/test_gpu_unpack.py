@@ -109,3 +109,12 @@ def test_damaged_streams_are_refused(n):
     assert c.last_error_detail() == s.header()["n_esc"]
     assert refused(with_checksum(body)[:40]) == corrupt
     c.close()
+
+
+@pytest.mark.parametrize("n", [0, 1, (2 << 20) - 1, 2 << 20, (16 << 20) - 1, 16 << 20,
+                               (32 << 20) + 5, 50_000_003])
+def test_device_bytes(n):
+    """Around the pieces and the threads' cuts of the copy into a bytes object."""
+    from paper_1611_01545_amd.pm import _device_bytes
+    t = torch.randint(0, 256, (n + 3,), dtype=torch.uint8, device="cuda")[1: n + 1]
+    assert _device_bytes(t) == t.cpu().numpy().tobytes()
