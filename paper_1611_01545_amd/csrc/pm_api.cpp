@@ -185,7 +185,7 @@ pm_status pm_query_sizes(const pm_config* cfg, int64_t n_max, int n_sp, pm_sizes
                        3 * n2 * 8 + (int64_t)sizeof(DevErr) + 64;
   out->step_mesh_bytes = 3 * n3 * 4;
   // pm_encode / pm_step of N particles in n_sp species
-  const int64_t rs_blocks = N / 4096 + 1;  // radix-sort workgroups (encode: uncapped)
+  const int64_t rs_blocks = N / 4096 + 1;  // radix-sort tiles of the encode
   int64_t st = 0;
   st += grown(n3 * 4);                                  // spectrum scratch mesh
   st += grown(3 * n2 * 4);                              // per-row max |a| partials (bound)
@@ -194,8 +194,9 @@ pm_status pm_query_sizes(const pm_config* cfg, int64_t n_max, int n_sp, pm_sizes
   st += grown(n_sp * (nb + 1) * 8) + grown(n_sp * (nb + 1) * 4);  // re-sort: brick starts
   st += 2 * grown(n_sp * nb * 4) + grown(n_sp * nb * 4 + 16);  // movers, arrivals, escapes
   st += grown(nc3 * 4 * n_sp);                          // stayers per cell
-  st += grown(nc3 * 4) * 2 + grown((nc3 + 1) * 8);      // encode: runs, counts, escapes
-  st += 2 * grown(NP * 6) + grown(NP * 2);              // new codes and digits, old order
+  st += grown(nc3 * 4) * 2 + grown((nc3 + 1) * 8);      // encode: counts, escapes
+  st += 2 * grown(N * 12 + 8 * n_sp * 6);               // encode: records, two copies; step:
+  st += grown(NP * 2);                                  //   new codes and digits, old order
   st += 4 * grown(NP * 4);                              // sort keys and indices, two copies
   st += grown(std::max<int64_t>(nb * 8 * n_sp, (N / 256 + 1) * 8));  // grid partials
   st += grown(rs_blocks * 256 * 4) + grown((rs_blocks * 256 + 1) * 8);  // radix histograms

@@ -41,8 +41,6 @@ __device__ inline int64_t xcd_tile(int64_t bid, int64_t ntiles) {
 // ------------------------------------------------------- partial reductions --
 // Whole-grid min/max without atomics: every workgroup stores its partial result at
 // its own index, and a one-block kernel folds the partials.
-pm_status fold_minmax_to_header(pm_context* c, const int32_t* mn, const int32_t* mx,
-                                int64_t n, pm_shdr* hdr);   // hdr->j_min / j_max
 pm_status fold_max_u32(pm_context* c, const uint32_t* part, int64_t n, uint32_t* out);
 
 // ----------------------------------------------------------------- geometry --
@@ -213,11 +211,6 @@ pm_status launch_fill_u64(pm_context* c, uint64_t* p, int64_t n, uint64_t v);
 pm_status run_iota(pm_context* c, int64_t* p, int64_t n);  // p[i] = i
 // exclusive scans into int64 out[n+1]
 pm_status scan_u32(pm_context* c, const uint32_t* in, int64_t n, int64_t* out);
-// stable LSD radix sort of (key, val) pairs on the low `bits` of key; results land in
-// *keys/*vals (which may be swapped with the alternate buffers).
-pm_status radix_sort_pairs(pm_context* c, uint32_t** keys, uint32_t** vals,
-                           uint32_t** keys_alt, uint32_t** vals_alt, int64_t n,
-                           int bits);
 // codec (pm_codec.hip)
 pm_status run_encode(pm_context* c, const pm_species* in, pm_species* out, int64_t* perm);
 pm_status run_decode(pm_context* c, const pm_species* in, pm_species* out);
