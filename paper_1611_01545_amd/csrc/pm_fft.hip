@@ -395,17 +395,40 @@ __device__ __forceinline__ unsigned xcd_group(unsigned x, unsigned gx) {
 template <int N, int W>
 constexpr int col_group() { return LP<N>::H == 2 && W < 16 ? 16 / W : 1; }
 
+// A column pass takes the main spectrum and the Nyquist plane in one launch: blockIdx.y < n
+// is a line index l2 of the main spectrum, whose n / 2 lines l1 make gridDim.x tiles of W;
+// the plane's n lines are the 2 gridDim.x tiles of the last two values of blockIdx.y. (A
+// launch of its own with n / 16 workgroups took 3.4 us at 64^3, 5 at 128^3, 8 to 15 at
+// 512^3, three times per force.)
+struct ColSet {
+  const float2* in0;
+  const float2* in1;  // two-input passes
+  float2* out;
+  Lines d;
+};
+struct ColPair {
+  ColSet main, nyq;
+};
+template <int G>
+__device__ __forceinline__ unsigned col_tile(bool plane, int n) {
+  return plane ? (blockIdx.y - (unsigned)n) * gridDim.x + blockIdx.x
+               : xcd_group<G>(blockIdx.x, gridDim.x);
+}
+
 // Generic c2c column FFT. OUT 0: out0 = FFT_SIGN(in). OUT 3 (y lines of the transposed
 // force): out0 = +i k_x FFT_SIGN(in) + i k(e) FFT_SIGN(in1), k(e) the line's own wave
 // number, k_x constant along a y line. With two lines per thread the twiddles are staged
 // in LDS (32-bit addresses), which keeps both line arrays in registers without spilling.
 template <int N, int W, int SIGN, int OUT>
-__global__ __launch_bounds__(W * LP<N>::TL) void k_col_fft(const float2* in,
-                                                           const float2* in1, float2* out0,
-                                                           float2* out1, Lines d,
+__global__ __launch_bounds__(W * LP<N>::TL) void k_col_fft(ColPair cp,
                                                            const float2* __restrict__ tw,
                                                            int tws, int twmask, int n,
                                                            const float* __restrict__ gk) {
+  const bool plane = blockIdx.y >= (unsigned)n;
+  const ColSet& io = plane ? cp.nyq : cp.main;
+  const float2 *in = io.in0, *in1 = io.in1;
+  float2* out0 = io.out;
+  const Lines& d = io.d;
   using L = LP<N>;
   constexpr int CS = col_cs<W>(L::LF);
   __shared__ float lds[W * CS];
@@ -418,12 +441,13 @@ __global__ __launch_bounds__(W * LP<N>::TL) void k_col_fft(const float2* in,
     for (int i = threadIdx.x; i < N; i += W * L::TL) stw[i] = tw[(i * tws) & twmask];
     __syncthreads();
   }
-  const unsigned bx = xcd_group<col_group<N, W>()>(blockIdx.x, gridDim.x);
+  const unsigned bx = col_tile<col_group<N, W>()>(plane, n);
+  const unsigned l2 = plane ? 0u : blockIdx.y;
   // the grid covers the lines exactly (W divides the line count; checked on the host)
   int c, t, h;
   col_thread<N, W>(c, t, h);
   // addresses: a workgroup-uniform 64-bit part plus a 32-bit per-thread offset
-  const int64_t ubase = line_base(d, (int64_t)bx * W, blockIdx.y);
+  const int64_t ubase = line_base(d, (int64_t)bx * W, l2);
   const int e0 = L::H * t + h;  // natural point of n1 = 0; point n1 is e0 + H T n1
   const uint32_t lo_in = (uint32_t)(c * d.s1 + (int64_t)e0 * d.es);
   // transposed frequency (t + T v) + E k2 + h N/2: per-thread part and k2 stride
@@ -471,15 +495,18 @@ __global__ __launch_bounds__(W * LP<N>::TL) void k_col_fft(const float2* in,
 // ---------------------------------------------------------------- fused z pass --
 // F = FFT_z(in0) per line, then MODE 0: out0 = IFFT_z(G F) (the potential's spectrum);
 // MODE 1 (transpose of the force): out0 = IFFT_z(G (FFT_z(in0) + i k_z FFT_z(in2))),
-// where in0 already holds the x and y terms +i (k_x mu_x + k_y mu_y) from the y pass. BLK: the
-// lines are z-blocked (main spectrum) or plain strided (Nyquist plane).
-template <int N, int W, int MODE, bool BLK>
+// where in0 already holds the x and y terms +i (k_x mu_x + k_y mu_y) from the y pass. The
+// lines are z-blocked in the main spectrum, plain strided in the Nyquist plane.
+template <int N, int W, int MODE>
 __global__ __launch_bounds__(W * LP<N>::TL) void k_col_zconv(
-    const float2* in0, const float2* in1, const float2* in2, float2* out0, float2* out1,
-    Lines d,
-    const float2* __restrict__ tw, int tws, int twmask, int n,
+    ColPair cp, const float2* __restrict__ tw, int tws, int twmask, int n,
     const float* __restrict__ gtab, const float* __restrict__ gk) {
   using L = LP<N>;
+  const bool plane = blockIdx.y >= (unsigned)n;
+  const ColSet& io = plane ? cp.nyq : cp.main;
+  const float2 *in0 = io.in0, *in2 = io.in1;
+  float2* out0 = io.out;
+  const Lines& d = io.d;
   constexpr int ZB = zblk(N), LZB = ilog2(ZB);
   static_assert((L::H * L::T) % ZB == 0, "z blocks must divide the thread stride");
   constexpr int CS = col_cs<W>(L::LF);
@@ -494,23 +521,24 @@ __global__ __launch_bounds__(W * LP<N>::TL) void k_col_zconv(
   __shared__ float sgk[N];
   for (int i = threadIdx.x; i < N; i += W * L::TL) sgk[i] = gk[i];
   __syncthreads();
-  const unsigned bx = xcd_group<col_group<N, W>()>(blockIdx.x, gridDim.x);
+  const unsigned bx = col_tile<col_group<N, W>()>(plane, n);
+  const unsigned l2 = plane ? 0u : blockIdx.y;
   int c, t, h;
   col_thread<N, W>(c, t, h);
   const int64_t l1 = (int64_t)bx * W + c;
   // point e0 + H T n1 of the line (e0 = H t + h): z-blocked lines split it as (block,
   // row in block). Addresses are a workgroup-uniform 64-bit part (scalar registers) plus
   // a 32-bit per-thread offset, so that no 64-bit address per point stays live in VGPRs.
-  const int64_t ubase = line_base(d, (int64_t)bx * W, blockIdx.y);
+  const int64_t ubase = line_base(d, (int64_t)bx * W, l2);
   const int e0 = L::H * t + h;
   const uint32_t toff =
-      (uint32_t)(c * d.s1 + (BLK ? (int64_t)(e0 >> LZB) * d.es + (int64_t)(e0 & (ZB - 1)) * d.esl
-                                 : (int64_t)e0 * d.es));
-  const int64_t step = BLK ? (int64_t)((L::H * L::T) >> LZB) * d.es
-                           : (int64_t)L::H * L::T * d.es;
+      (uint32_t)(c * d.s1 + (plane ? (int64_t)e0 * d.es
+                                   : (int64_t)(e0 >> LZB) * d.es + (int64_t)(e0 & (ZB - 1)) * d.esl));
+  const int64_t step = plane ? (int64_t)L::H * L::T * d.es
+                             : (int64_t)((L::H * L::T) >> LZB) * d.es;
   float* my = lds + c * CS;
   const int kx = d.kx_mode ? d.kx_fixed : (int)l1;
-  const int ky = d.ky_mode ? (int)l1 : (int)blockIdx.y;
+  const int ky = d.ky_mode ? (int)l1 : (int)l2;
   const int sx = signed_k(kx, n), sy = signed_k(ky, n);
   // kernel values of this line: gtab row (|kx|, |ky|), indexed by |kz|
   const int h1 = n / 2 + 1;
@@ -946,23 +974,21 @@ struct FftCtx {
   int twmask;
 };
 
-// out 0: plain, o0 = FFT(in); in1 (forward only): the two-input pass OUT 3 into o0; o1
-// must be null
+// io.main.in1 (forward only): the two-input pass OUT 3
 template <int N>
-pm_status col_fft(const FftCtx& f, const float2* in, const float2* in1, float2* o0, float2* o1,
-                  const Lines& d, int64_t L2, int sign) {
+pm_status col_fft(const FftCtx& f, const ColPair& io, int sign) {
   constexpr int W1 = col_w<N, false>(), W2 = col_w<N, true>();
-  const int out = in1 ? 3 : 0;
-  if (o1 || !o0 || (out == 3 && sign > 0)) return PM_ERR_ARG;
-  const int W = out == 3 ? W2 : W1;
-  if (d.L1 % W) return PM_ERR_SHAPE;
-  dim3 grid((unsigned)(d.L1 / W), (unsigned)L2);
+  const bool two = io.main.in1 != nullptr;
+  if (two && sign > 0) return PM_ERR_ARG;
+  const int W = two ? W2 : W1;
+  if (io.main.d.L1 % W || io.nyq.d.L1 != 2 * io.main.d.L1) return PM_ERR_SHAPE;
+  dim3 grid((unsigned)(io.main.d.L1 / W), (unsigned)f.n + 2);
   dim3 block(W * LP<N>::TL);
-#define CLAUNCH(S, O)                                                                     \
-  hipLaunchKernelGGL((k_col_fft<N, O == 3 ? W2 : W1, S, O>), grid, block, 0,             \
-                     f.c->stream, in, in1, o0, o1, d, f.c->tw, 1, f.twmask, f.n, f.c->gk)
+#define CLAUNCH(S, O)                                                                    \
+  hipLaunchKernelGGL((k_col_fft<N, O == 3 ? W2 : W1, S, O>), grid, block, 0,            \
+                     f.c->stream, io, f.c->tw, 1, f.twmask, f.n, f.c->gk)
   if (sign < 0) {
-    if (out == 3) CLAUNCH(-1, 3);
+    if (two) CLAUNCH(-1, 3);
     else CLAUNCH(-1, 0);
   } else {
     CLAUNCH(1, 0);
@@ -972,27 +998,20 @@ pm_status col_fft(const FftCtx& f, const float2* in, const float2* in1, float2* 
   return PM_OK;
 }
 
+// every z pass stages its twiddles; MODE 1 (io.main.in1) holds two line arrays
 template <int N>
-pm_status col_zconv(const FftCtx& f, int mode, bool blk, const float2* i0, const float2* i1,
-                    const float2* i2, float2* o0, float2* o1, const Lines& d, int64_t L2) {
-  // every z pass stages its twiddles; MODE 1 holds two line arrays
-  if (mode != 0 && mode != 1) return PM_ERR_ARG;
+pm_status col_zconv(const FftCtx& f, const ColPair& io) {
   constexpr int W1 = zconv_w<N, false>(), W2 = zconv_w<N, true>();
-  const int W = mode == 1 ? W2 : W1;
-  if (d.L1 % W) return PM_ERR_SHAPE;
-  dim3 grid((unsigned)(d.L1 / W), (unsigned)L2);
+  const bool two = io.main.in1 != nullptr;
+  const int W = two ? W2 : W1;
+  if (io.main.d.L1 % W || io.nyq.d.L1 != 2 * io.main.d.L1) return PM_ERR_SHAPE;
+  dim3 grid((unsigned)(io.main.d.L1 / W), (unsigned)f.n + 2);
   dim3 block(W * LP<N>::TL);
-#define ZLAUNCH(MODE, BLK)                                                                  \
-  hipLaunchKernelGGL((k_col_zconv<N, MODE == 1 ? W2 : W1, MODE, BLK>), grid,              \
-                     block, 0, f.c->stream, i0, i1, i2, o0, o1, d, f.c->tw, 1, f.twmask,    \
-                     f.n, f.c->gtab, f.c->gk)
-  if (blk) {
-    if (mode == 0) ZLAUNCH(0, true);
-    else ZLAUNCH(1, true);
-  } else {
-    if (mode == 0) ZLAUNCH(0, false);
-    else ZLAUNCH(1, false);
-  }
+#define ZLAUNCH(MODE)                                                                       \
+  hipLaunchKernelGGL((k_col_zconv<N, MODE == 1 ? W2 : W1, MODE>), grid, block, 0,         \
+                     f.c->stream, io, f.c->tw, 1, f.twmask, f.n, f.c->gtab, f.c->gk)
+  if (two) ZLAUNCH(1);
+  else ZLAUNCH(0);
 #undef ZLAUNCH
   PM_LAUNCH_CHECK();
   return PM_OK;
@@ -1023,33 +1042,19 @@ pm_status row_c2r(const FftCtx& f, const float2* in, const float2* nyq, float* o
 // Size dispatch: the column length is n, the row length (complex) n/2.
 #define PM_FFT_SIZES(X) X(8) X(16) X(32) X(64) X(128) X(256) X(512) X(1024) X(2048)
 
-pm_status d_col_fft(const FftCtx& f, const float2* in, float2* o0, float2* o1, const Lines& d,
-                    int64_t L2, int sign) {
+pm_status d_col_fft(const FftCtx& f, const ColPair& io, int sign) {
   switch (f.n) {
 #define CASE(N) \
-  case N: return col_fft<N>(f, in, nullptr, o0, o1, d, L2, sign);
+  case N: return col_fft<N>(f, io, sign);
     PM_FFT_SIZES(CASE)
 #undef CASE
   }
   return PM_ERR_SHAPE;
 }
-// forward y transform of two spectra into one: o = +i k_x FFT_y(in0) + i k_y FFT_y(in1)
-pm_status d_col_fft_grad2(const FftCtx& f, const float2* in0, const float2* in1, float2* o,
-                          const Lines& d, int64_t L2) {
+pm_status d_col_zconv(const FftCtx& f, const ColPair& io) {
   switch (f.n) {
 #define CASE(N) \
-  case N: return col_fft<N>(f, in0, in1, o, nullptr, d, L2, -1);
-    PM_FFT_SIZES(CASE)
-#undef CASE
-  }
-  return PM_ERR_SHAPE;
-}
-pm_status d_col_zconv(const FftCtx& f, int mode, bool blk, const float2* i0,
-                      const float2* i1, const float2* i2, float2* o0, float2* o1,
-                      const Lines& d, int64_t L2) {
-  switch (f.n) {
-#define CASE(N) \
-  case N: return col_zconv<N>(f, mode, blk, i0, i1, i2, o0, o1, d, L2);
+  case N: return col_zconv<N>(f, io);
     PM_FFT_SIZES(CASE)
 #undef CASE
   }
@@ -1091,6 +1096,16 @@ Lines lines_z_main(int n) {  // l1 = kx, l2 = y, element = z (blocked)
 }
 Lines lines_z_nyq(int n) {  // l1 = y, element = z
   return Lines{1, 0, 0, 0, n, 0, n, 1, 1, n / 2};
+}
+
+// The y (z) lines of a main spectrum and its Nyquist plane; in1, q1: second input (nullable)
+ColPair cols_y(int n, const float2* in, const float2* in1, float2* out, const float2* q,
+               const float2* q1, float2* qout) {
+  return ColPair{{in, in1, out, lines_y_main(n)}, {q, q1, qout, lines_y_nyq(n)}};
+}
+ColPair cols_z(int n, const float2* in, const float2* in1, float2* out, const float2* q,
+               const float2* q1, float2* qout) {
+  return ColPair{{in, in1, out, lines_z_main(n)}, {q, q1, qout, lines_z_nyq(n)}};
 }
 
 }  // namespace
@@ -1161,26 +1176,19 @@ pm_status run_force(pm_context* c, const float* rho, float* acc, float2* nyq, fl
     ProfScope ps(c, ST_FFT_R2C);
     if ((s = d_row_r2c(f, rho, A1, N0, amax)) != PM_OK) return s;
   }
-  const Lines ym = lines_y_main(n), yn = lines_y_nyq(n);
-  const Lines zm = lines_z_main(n), zn = lines_z_nyq(n);
   {
     ProfScope ps(c, ST_FFT_YF);
-    if ((s = d_col_fft(f, A1, A1, nullptr, ym, n, -1)) != PM_OK) return s;
+    if ((s = d_col_fft(f, cols_y(n, A1, nullptr, A1, N0, nullptr, N0), -1)) != PM_OK) return s;
   }
-  if ((s = d_col_fft(f, N0, N0, nullptr, yn, 1, -1)) != PM_OK) return s;
   // the potential's spectrum G rho, in place
   {
     ProfScope ps(c, ST_FFT_Z);
-    if ((s = d_col_zconv(f, 0, true, A1, nullptr, nullptr, A1, nullptr, zm, n)) != PM_OK)
-      return s;
+    if ((s = d_col_zconv(f, cols_z(n, A1, nullptr, A1, N0, nullptr, N0))) != PM_OK) return s;
   }
-  if ((s = d_col_zconv(f, 0, false, N0, nullptr, nullptr, N0, nullptr, zn, 1)) != PM_OK)
-    return s;
   {
     ProfScope ps(c, ST_FFT_YI);
-    if ((s = d_col_fft(f, A1, A1, nullptr, ym, n, +1)) != PM_OK) return s;
+    if ((s = d_col_fft(f, cols_y(n, A1, nullptr, A1, N0, nullptr, N0), +1)) != PM_OK) return s;
   }
-  if ((s = d_col_fft(f, N0, N0, nullptr, yn, 1, +1)) != PM_OK) return s;
   {
     ProfScope ps(c, ST_FFT_C2R);
     if ((s = d_row_c2r(f, A1, N0, phi)) != PM_OK) return s;
@@ -1212,21 +1220,18 @@ pm_status run_force_transpose(pm_context* c, float* acc, float2* nyq) {
   if (!S) return PM_ERR_NOMEM;
   float2* Nq[3] = {nyq, nyq + n2, nyq + 2 * n2};
   pm_status s;
-  const Lines ym = lines_y_main(n), yn = lines_y_nyq(n);
-  const Lines zm = lines_z_main(n), zn = lines_z_nyq(n);
   float2* spec[3] = {A[1], A[2], S};  // spectrum of mu_x, mu_y, mu_z
   for (int ax = 2; ax >= 0; --ax)
     if ((s = d_row_r2c(f, (const float*)A[ax], spec[ax], Nq[ax])) != PM_OK) return s;
-  if ((s = d_col_fft(f, spec[2], spec[2], nullptr, ym, n, -1)) != PM_OK) return s;
-  if ((s = d_col_fft(f, Nq[2], Nq[2], nullptr, yn, 1, -1)) != PM_OK) return s;
-  if ((s = d_col_fft_grad2(f, spec[0], spec[1], spec[0], ym, n)) != PM_OK) return s;
-  if ((s = d_col_fft_grad2(f, Nq[0], Nq[1], Nq[0], yn, 1)) != PM_OK) return s;
-  if ((s = d_col_zconv(f, 1, true, spec[0], nullptr, spec[2], spec[0], nullptr, zm, n)) !=
+  if ((s = d_col_fft(f, cols_y(n, spec[2], nullptr, spec[2], Nq[2], nullptr, Nq[2]), -1)) !=
       PM_OK)
     return s;
-  if ((s = d_col_zconv(f, 1, false, Nq[0], nullptr, Nq[2], Nq[0], nullptr, zn, 1)) != PM_OK)
+  // +i k_x FFT_y(mu_x) + i k_y FFT_y(mu_y)
+  if ((s = d_col_fft(f, cols_y(n, spec[0], spec[1], spec[0], Nq[0], Nq[1], Nq[0]), -1)) != PM_OK)
     return s;
-  if ((s = d_col_fft(f, spec[0], spec[0], nullptr, ym, n, +1)) != PM_OK) return s;
-  if ((s = d_col_fft(f, Nq[0], Nq[0], nullptr, yn, 1, +1)) != PM_OK) return s;
+  if ((s = d_col_zconv(f, cols_z(n, spec[0], spec[2], spec[0], Nq[0], Nq[2], Nq[0]))) != PM_OK)
+    return s;
+  if ((s = d_col_fft(f, cols_y(n, spec[0], nullptr, spec[0], Nq[0], nullptr, Nq[0]), +1)) != PM_OK)
+    return s;
   return d_row_c2r(f, spec[0], Nq[0], (float*)A[0]);
 }
