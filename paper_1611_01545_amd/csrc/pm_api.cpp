@@ -356,6 +356,16 @@ pm_status pm_kick_drift_perm(pm_ctx c, const pm_species* in, pm_species* out, in
   return kick_all(c, in, out, n_sp, acc, a_max, c_kick, c_drift, nullptr, perm);
 }
 
+// The field that a compressed step's kick reads, from the density in the context's mesh: the
+// potential where the kick takes its differences itself, else the three force meshes.
+static pm_status step_field(pm_context* c, float* mesh, const float** field, bool* phi) {
+  *phi = kick_takes_phi(c);
+  *field = mesh;
+  if (!*phi) return run_force(c, mesh, mesh, c->nyq, c->amax);
+  const int64_t n3 = c->g.ng * c->g.ng * c->g.ng;
+  return run_potential(c, mesh, mesh + n3, c->nyq, c->amax, field);
+}
+
 pm_status pm_step(pm_ctx c, const pm_species* in, pm_species* out, int n_sp, double dt) {
   if (!c) return PM_ERR_ARG;
   pm_status s = check_kick_args(c, in, out, n_sp);
@@ -367,8 +377,11 @@ pm_status pm_step(pm_ctx c, const pm_species* in, pm_species* out, int n_sp, dou
     int64_t* offs[4] = {nullptr, nullptr, nullptr, nullptr};
     if ((s = run_species_offsets(c, in, n_sp, offs)) != PM_OK) return s;
     if ((s = run_deposit_tile(c, in, n_sp, offs, mesh)) != PM_OK) return s;
-    if ((s = run_force(c, mesh, mesh, c->nyq, c->amax)) != PM_OK) return s;
-    return kick_all(c, in, out, n_sp, mesh, c->amax, dt, dt, offs);
+    const float* field = mesh;
+    bool phi = false;
+    if ((s = step_field(c, mesh, &field, &phi)) != PM_OK) return s;
+    return run_kick_compressed_all(c, in, out, n_sp, offs, field, c->amax, dt, dt, nullptr,
+                                   nullptr, phi);
   }
   if ((s = run_deposit(c, in, n_sp, mesh)) != PM_OK) return s;
   if ((s = run_force(c, mesh, mesh, c->nyq, c->amax)) != PM_OK) return s;
@@ -412,11 +425,13 @@ pm_status pm_step_pp(pm_ctx c, const pm_species* in, pm_species* out, int n_sp, 
     at += ((size_t)in[i].n * 12 + 255) & ~(size_t)255;
   }
   if ((s = run_deposit_tile(c, in, n_sp, offs, mesh)) != PM_OK) return s;
-  if ((s = run_force(c, mesh, mesh, c->nyq, c->amax)) != PM_OK) return s;
+  const float* field = mesh;
+  bool phi = false;
+  if ((s = step_field(c, mesh, &field, &phi)) != PM_OK) return s;
   if ((s = run_pp_accel(c, in, n_sp, offs, r_soft, app, c->amax + 1)) != PM_OK) return s;
   if ((s = run_add_max(c, c->amax, c->amax + 1, c->amax + 2)) != PM_OK) return s;
-  return run_kick_compressed_all(c, in, out, n_sp, offs, mesh, c->amax + 2, dt, dt, perm,
-                                 app);
+  return run_kick_compressed_all(c, in, out, n_sp, offs, field, c->amax + 2, dt, dt, perm,
+                                 app, phi);
 }
 
 pm_status pm_interp_accel(pm_ctx c, const pm_species* sp, int n_sp, const float* acc,
@@ -466,11 +481,14 @@ pm_status pm_step_p3m(pm_ctx f, pm_ctx cc, const pm_species* in, pm_species* out
   // short range on the fine mesh
   float* fm = f->mesh;
   if ((s = run_deposit_tile(f, in, n_sp, offs, fm)) != PM_OK) return s;
-  if ((s = run_force(f, fm, fm, f->nyq, f->amax)) != PM_OK) return s;
+  const float* field = fm;
+  bool phi = false;
+  if ((s = step_field(f, fm, &field, &phi)) != PM_OK) return s;
   // velocity bound: max |a_short| + max |a_long| (+ max |a_pp|)
   if ((s = run_add_max(f, f->amax, cc->amax, f->amax + 2)) != PM_OK) return s;
   if (pp && (s = run_add_max(f, f->amax + 2, f->amax + 1, f->amax + 2)) != PM_OK) return s;
-  return run_kick_compressed_all(f, in, out, n_sp, offs, fm, f->amax + 2, dt, dt, perm, app);
+  return run_kick_compressed_all(f, in, out, n_sp, offs, field, f->amax + 2, dt, dt, perm, app,
+                                 phi);
 }
 
 pm_status pm_step_vjp(pm_ctx c, const pm_species* in, int n_sp, double dt,

@@ -240,6 +240,10 @@ pm_status run_deposit_tile(pm_context* c, const pm_species* sp, int n_sp,
 pm_status build_kernel_table(pm_context* c);
 pm_status run_force(pm_context* c, const float* rho, float* acc, float2* nyq,
                     float* amax);
+// the potential alone, in the context's scratch (until the next transform), and max |a|
+pm_status run_potential(pm_context* c, const float* rho, float* spec, float2* nyq, float* amax,
+                        const float** phi);
+inline float grad_scale(int64_t ng) { return (float)((double)ng / 12.0); }
 // adjoint transform: nu = sum_a IDFT(+i k_a G DFT(mu_a)); mu in acc[3] (destroyed),
 // result written to acc component 0.
 pm_status run_force_transpose(pm_context* c, float* acc, float2* nyq);
@@ -253,7 +257,11 @@ pm_status run_kick_float(pm_context* c, const pm_species* in, pm_species* out,
 pm_status run_kick_compressed_all(pm_context* c, const pm_species* in, pm_species* out,
                                   int n_sp, int64_t* const* offs, const float* acc,
                                   const float* amax, double ck, double cd,
-                                  int64_t* const* perm, const float* const* app = nullptr);
+                                  int64_t* const* perm, const float* const* app = nullptr,
+                                  bool phi = false);
+// phi: acc is the potential (run_potential) instead of the three force meshes; for the
+// geometries that take it
+bool kick_takes_phi(const pm_context* c);
 // PP force of eq. (4) inside the mesh cells (pm_pp.hip): app[s] float [n][3], stream
 // order; pmax receives max |a| over all particles and axes
 pm_status run_pp_accel(pm_context* c, const pm_species* sp, int n_sp, int64_t* const* offs,

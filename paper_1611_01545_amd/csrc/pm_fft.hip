@@ -12,7 +12,8 @@
 //   X  c2r      phi(x), real
 // and the force a = -D phi (eq. (3)), D the fourth-order central difference, is one
 // stencil pass over phi (k_grad4) that also takes max |a| for the velocity bound of the
-// re-encode: 6 launches moving 52 n^3 bytes. The stencil is the exact real-space form of
+// re-encode: 6 launches moving 52 n^3 bytes, or 40 n^3 where the kick takes the differences
+// at its particles itself and the pass only finds the maximum. The stencil is the exact real-space form of
 // the spectral factor -i D(k_a), D(k) its symbol (which is zero on the Nyquist index).
 // The transposed force (adjoint) applies that factor in the spectrum, in the y and z
 // passes. The 1/n^3 of the inverse transform is folded into the kernel table.
@@ -764,7 +765,9 @@ struct GradTile {
   int threads;
   int64_t blocks;
 };
-template <int RY, bool NT>
+// OUT: 0 max |a| only (the potential's own reader takes the differences), 1 plain stores, 2
+// nontemporal ones.
+template <int RY, int OUT>
 __global__ __launch_bounds__(GRAD_T) void k_grad4(const float* __restrict__ phi, float* ax,
                                                   float* ay, float* az, int lgn, GradTile t,
                                                   float scale, unsigned int* amax) {
@@ -825,7 +828,8 @@ __global__ __launch_bounds__(GRAD_T) void k_grad4(const float* __restrict__ phi,
           amx = fmaxf(amx, fmaxf(fabsf(ox[k]), fmaxf(fabsf(oy[k]), fabsf(oz[k]))));
         }
         const uint64_t i = (uint64_t)z * n2 + (uint64_t)(y0 + r) * n + x;
-        if constexpr (NT) {
+        if constexpr (OUT == 0) {
+        } else if constexpr (OUT == 2) {
           typedef float v4 __attribute__((ext_vector_type(4)));
           __builtin_nontemporal_store(*(const v4*)&o[0], (v4*)(ax + i));
           __builtin_nontemporal_store(*(const v4*)&o[1], (v4*)(ay + i));
@@ -859,11 +863,19 @@ __global__ __launch_bounds__(GRAD_T) void k_grad4(const float* __restrict__ phi,
 // 512^3 426 (540), 1024^3 3.38 ms at GZ = 4 with nontemporal stores against 3.63 with
 // plain ones and 3.44 with the LDS tile. At 1024^3 the components are too large for any
 // cache to hold them until the kick reads them; below it they are stored plainly.
-GradTile grad_tile(int64_t n) {
+// The maximum alone is bound by the rows' neighbours out of the L2 (about 2.5 reads per
+// node): at 1024^3 1.25 ms with 4 rows and 8 planes against 1.33 with 4 planes, 1.29 with 2
+// rows, 1.71 with 1 (3.38 with the stores); at 512^3 187 us with 2 rows and 4 planes against
+// 207 with 4 rows and 2 planes, 204 with 8, 235 with 1 row.
+GradTile grad_tile(int64_t n, bool max_only) {
   GradTile t;
   t.xw = (int)std::min<int64_t>(n / 4, 64);
   t.ry = n >= 256 ? 4 : n >= 128 ? 2 : 1;
   t.gz = n >= 1024 || n == 128 ? 4 : 2;
+  if (max_only && n >= 256) {
+    t.ry = n >= 1024 ? 4 : 2;
+    t.gz = n >= 1024 ? 8 : 4;
+  }
   t.yg = (int)std::min<int64_t>(GRAD_T / t.xw, n / t.ry);
   t.threads = (t.xw * t.yg + 63) / 64 * 64;
   t.blocks = (n / (4 * t.xw)) * (n / (t.yg * t.ry)) * (n / t.gz);
@@ -1163,14 +1175,10 @@ pm_status build_kernel_table(pm_context* c) {
 //   Y^-1   A1 in place
 //   c2r    phi: A1 -> S
 //   k_grad4  a = -D phi: S -> A0, A1, A2, and max |a|
-pm_status run_force(pm_context* c, const float* rho, float* acc, float2* nyq, float* amax) {
+static pm_status potential(pm_context* c, const float* rho, float2* A1, float2* N0, float* amax,
+                           float* phi) {
   const int n = (int)c->g.ng;
-  const int64_t n3 = (int64_t)n * n * n;
   FftCtx f{c, n, n - 1};
-  float2* A1 = (float2*)(acc + n3);
-  float* phi = (float*)scratch(c, SC_SPEC, (size_t)n3 * sizeof(float));
-  if (!phi) return PM_ERR_NOMEM;
-  float2* N0 = nyq;
   pm_status s;
   {
     ProfScope ps(c, ST_FFT_R2C);
@@ -1189,28 +1197,52 @@ pm_status run_force(pm_context* c, const float* rho, float* acc, float2* nyq, fl
     ProfScope ps(c, ST_FFT_YI);
     if ((s = d_col_fft(f, cols_y(n, A1, nullptr, A1, N0, nullptr, N0), +1)) != PM_OK) return s;
   }
-  {
-    ProfScope ps(c, ST_FFT_C2R);
-    if ((s = d_row_c2r(f, A1, N0, phi)) != PM_OK) return s;
-  }
-  // the three components from the potential by the difference stencil
-  {
-    ProfScope ps(c, ST_GRAD);
-    const GradTile gt = grad_tile(n);
-    const float scale = (float)((double)n / 12.0);
-    auto launch = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, dim3((unsigned)gt.blocks), dim3(gt.threads), 0, c->stream,
-                         (const float*)phi, acc, acc + n3, acc + 2 * n3, ilog2(n), gt, scale,
-                         (unsigned int*)amax);
-    };
-    if (n >= 1024) launch(k_grad4<4, true>);
-    else if (gt.ry == 4) launch(k_grad4<4, false>);
-    else if (gt.ry == 2) launch(k_grad4<2, false>);
-    else launch(k_grad4<1, false>);
-    PM_LAUNCH_CHECK();
-  }
+  ProfScope ps(c, ST_FFT_C2R);
+  return d_row_c2r(f, A1, N0, phi);
+}
+
+// the three components from the potential by the difference stencil, or their largest value
+// alone (acc null)
+static pm_status gradient(pm_context* c, const float* phi, float* acc, float* amax) {
+  ProfScope ps(c, ST_GRAD);
+  const int n = (int)c->g.ng;
+  const int64_t n3 = (int64_t)n * n * n;
+  const GradTile gt = grad_tile(n, !acc);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)gt.blocks), dim3(gt.threads), 0, c->stream, phi,
+                       acc, acc ? acc + n3 : nullptr, acc ? acc + 2 * n3 : nullptr, ilog2(n), gt,
+                       grad_scale(n), (unsigned int*)amax);
+  };
+  if (!acc) {
+    if (gt.ry == 4) launch(k_grad4<4, 0>);
+    else if (gt.ry == 2) launch(k_grad4<2, 0>);
+    else launch(k_grad4<1, 0>);
+  } else if (n >= 1024) launch(k_grad4<4, 2>);
+  else if (gt.ry == 4) launch(k_grad4<4, 1>);
+  else if (gt.ry == 2) launch(k_grad4<2, 1>);
+  else launch(k_grad4<1, 1>);
+  PM_LAUNCH_CHECK();
   return PM_OK;
 }
+
+pm_status run_force(pm_context* c, const float* rho, float* acc, float2* nyq, float* amax) {
+  const int64_t n3 = c->g.ng * c->g.ng * c->g.ng;
+  float* phi = (float*)scratch(c, SC_SPEC, (size_t)n3 * sizeof(float));
+  if (!phi) return PM_ERR_NOMEM;
+  const pm_status s = potential(c, rho, (float2*)(acc + n3), nyq, amax, phi);
+  return s != PM_OK ? s : gradient(c, phi, acc, amax);
+}
+
+pm_status run_potential(pm_context* c, const float* rho, float* spec, float2* nyq, float* amax,
+                        const float** phi) {
+  const int64_t n3 = c->g.ng * c->g.ng * c->g.ng;
+  float* p = (float*)scratch(c, SC_SPEC, (size_t)n3 * sizeof(float));
+  if (!p) return PM_ERR_NOMEM;
+  *phi = p;
+  const pm_status s = potential(c, rho, (float2*)spec, nyq, amax, p);
+  return s != PM_OK ? s : gradient(c, p, nullptr, amax);
+}
+
 pm_status run_force_transpose(pm_context* c, float* acc, float2* nyq) {
   const int n = (int)c->g.ng;
   const int64_t n3 = (int64_t)n * n * n, n2 = (int64_t)n * n;

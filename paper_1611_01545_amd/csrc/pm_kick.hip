@@ -9,7 +9,7 @@
 //                   mesh values, so no kicked component exceeds the bound. Clears the
 //                   re-sort's counters.
 //   k_kick_pair     two bricks adjacent along x per workgroup (R = 16 nodes per brick
-//   k_kick_brick    side), or one brick of any shape: the force nodes staged in LDS,
+//   k_kick_brick    side), or one brick of any shape: the force (or potential) nodes in LDS,
 //                   then waves take 64-particle chunks independently (no barrier):
 //                   decode, gather a from the 8 CIC nodes, v' = v + c_k a, fixed-point
 //                   drift u' = u + floor(v' c_d S + 1/2), new codes, and the digit: the
@@ -144,7 +144,8 @@ struct KickSpecies {
 struct KickArgs {
   KickSpecies sp[MAXSP];
   int n_sp;
-  const float* acc;  // [3][ng^3]
+  const float* acc;  // [3][ng^3], or the potential [ng^3] (k_kick_pair with PHI)
+  float scale;       // of its difference: ng / 12
   float ck;
   double cdS;        // c_d S / L (position codes per unit velocity)
 };
@@ -502,16 +503,27 @@ __global__ __launch_bounds__(KB) void k_kick_brick(KickArgs A, Geom g, DevErr* e
 // nodes long, which the memory system serves much faster than rows of R; with NZ = 4
 // and 256 threads the tile is 34 KB and four workgroups share a CU, each staging while
 // the others compute.
+// PHI: the mesh is the potential, and a particle takes the fourth-order differences at its
+// eight nodes itself (the same arithmetic as the force gradient pass, so the same bits).
+// With a particle per seven nodes, as in this brick shape, that is less work than a pass
+// over the nodes that writes three meshes and their staging here: the tile is x in [x0 - 4,
+// x0 + 2R + 4), y in [y0 - 2, y0 + R + 2], and nine planes of z that go round like the
+// layers above. At 1024^3 with 151 M particles 4.37 ms, and 1.25 for the maximum of the
+// force, against 4.86 and 3.39 from the three meshes (512^3, 2-byte codes: 554 + 187 us
+// against 634 + 440). Bound by the vector units (half the time) and by bank conflicts of the
+// gather (56 words per particle, at random).
 constexpr int PR = 16;
-template <int NT, int NZ, int P = 1, int V = 2>  // threads per workgroup, z passes, widths
+constexpr int FX = 2 * PR + 8, FY = PR + 5, FZ = 9;  // PHI: row, rows, planes
+template <int NT, int NZ, bool PHI, int P = 1, int V = 2>  // threads, z passes, mesh, widths
 __global__ __launch_bounds__(NT, 4) void k_kick_pair(KickArgs A, Geom g, DevErr* err) {
   constexpr int KB = NT, NWK = NT / 64;
   constexpr int X1 = 2 * PR + 1, Y1 = PR + 1, Z1 = PR / NZ + 1;
   constexpr int TS = X1 * Y1 * Z1;  // nodes per component
+  static_assert(!PHI || PR / NZ + 5 == FZ, "planes of a z pass with their neighbours");
   const int B = g.B, B3 = B * B * B, L = B3 + 1, H = B3 / NZ;  // H: cells per z pass
   extern __shared__ unsigned char smem[];
-  float* F = (float*)smem;                          // [3][Z1][Y1][X1]
-  uint32_t* rel = (uint32_t*)(smem + 3 * TS * 4);   // [2][MAXSP][L]
+  float* F = (float*)smem;                          // [3][Z1][Y1][X1], PHI: [FZ][FY][FX]
+  uint32_t* rel = (uint32_t*)(smem + (PHI ? FX * FY * FZ : 3 * TS) * 4);  // [2][MAXSP][L]
   uint32_t* run = rel + 2 * MAXSP * L;              // [2][MAXSP][L]
   __shared__ int64_t l0s[2 * MAXSP];
   __shared__ uint32_t mvc[2 * MAXSP];
@@ -634,6 +646,38 @@ __global__ __launch_bounds__(NT, 4) void k_kick_pair(KickArgs A, Geom g, DevErr*
     __syncthreads();
   };
 
+  // PHI: plane q of the tile is z0 + q - 2 and lives in slot q mod FZ; pass h needs planes
+  // 4h .. 4h + 8
+  auto stage_phi = [&](int h, auto np_tag) {
+    constexpr int NP = decltype(np_tag)::value;  // planes loaded: FZ, or PR / NZ
+    constexpr int Q = FX / 4, NQ = NP * FY * Q, PQ = (NQ + KB - 1) / KB;
+    const uint32_t mu = (uint32_t)(ng - 1), ngu = (uint32_t)ng;
+    const int q0 = h * (PR / NZ) + (FZ - NP);
+    const int sb = q0 % FZ;
+    typedef float v4 __attribute__((ext_vector_type(4)));  // (float4 copies went to scratch)
+    v4 vq[PQ];
+#pragma unroll
+    for (int k = 0; k < PQ; ++k) {
+      const uint32_t i = min(threadIdx.x + k * KB, (unsigned)NQ - 1u);
+      const uint32_t row = i / Q, seg = i - row * Q, pl = row / FY, ry = row - pl * FY;
+      const uint32_t gz = ((uint32_t)oz + q0 + pl - 2u) & mu, gy = ((uint32_t)oy + ry - 2u) & mu,
+                     gx = ((uint32_t)ox + 4u * seg - 4u) & mu;
+      vq[k] = *(const v4*)(A.acc + ((uint64_t)(gz * ngu + gy) * ngu + gx));
+    }
+    __syncthreads();  // the previous pass is done with the slots rewritten here
+#pragma unroll
+    for (int k = 0; k < PQ; ++k) {
+      const uint32_t i = threadIdx.x + k * KB;
+      if (i < NQ) {
+        const uint32_t row = i / Q, seg = i - row * Q, pl = row / FY, ry = row - pl * FY;
+        int sl = sb + (int)pl;
+        sl -= sl >= FZ ? FZ : 0;
+        *(v4*)(F + (sl * FY + ry) * FX + 4 * seg) = vq[k];
+      }
+    }
+    __syncthreads();
+  };
+
   // A pass deals 64-particle chunks over each species' particles of the z slice, brick
   // b0's then brick b0 + 1's (the two ranges are apart in the stream), so that a lane's
   // brick k is its own: a species with few particles per slice (16 CDM particles per
@@ -646,6 +690,38 @@ __global__ __launch_bounds__(NT, 4) void k_kick_pair(KickArgs A, Geom g, DevErr*
       int k = 0;  // this lane's brick, set per chunk
       auto gather = [&](const int li[3], const float f[3], float acc3[3]) {
         const int tx = li[0] + k * PR, ty = li[1];
+        if constexpr (PHI) {
+          // slots of the planes z - 2 .. z + 3 around node z = li[2]
+          int zo[6];
+          int sl = li[2] - h * (PR / NZ) + (h * (PR / NZ)) % FZ;
+          sl -= sl >= FZ ? FZ : 0;
+#pragma unroll
+          for (int q = 0; q < 6; ++q) {
+            zo[q] = sl * (FX * FY) + (ty + 2) * FX + tx + 4;
+            sl = sl + 1 == FZ ? 0 : sl + 1;
+          }
+          auto at = [&](int dx, int dy, int dz) { return F[zo[dz + 2] + dy * FX + dx]; };
+          acc3[0] = acc3[1] = acc3[2] = 0.f;
+#pragma unroll
+          for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+            for (int dy = 0; dy < 2; ++dy)
+#pragma unroll
+              for (int dx = 0; dx < 2; ++dx) {
+                const float wgt = (dx ? f[0] : 1.f - f[0]) * (dy ? f[1] : 1.f - f[1]) *
+                                  (dz ? f[2] : 1.f - f[2]);
+                const float gx = 8.f * (at(dx + 1, dy, dz) - at(dx - 1, dy, dz)) -
+                                 (at(dx + 2, dy, dz) - at(dx - 2, dy, dz));
+                const float gy = 8.f * (at(dx, dy + 1, dz) - at(dx, dy - 1, dz)) -
+                                 (at(dx, dy + 2, dz) - at(dx, dy - 2, dz));
+                const float gz = 8.f * (at(dx, dy, dz + 1) - at(dx, dy, dz - 1)) -
+                                 (at(dx, dy, dz + 2) - at(dx, dy, dz - 2));
+                acc3[0] += wgt * (-A.scale * gx);
+                acc3[1] += wgt * (-A.scale * gy);
+                acc3[2] += wgt * (-A.scale * gz);
+              }
+          return;
+        }
         // ring slots of the node layers tz and tz + 1 (local to this pass)
         int z0 = li[2] - h * (PR / NZ) + (h * (PR / NZ)) % Z1;
         z0 -= z0 >= Z1 ? Z1 : 0;
@@ -701,12 +777,14 @@ __global__ __launch_bounds__(NT, 4) void k_kick_pair(KickArgs A, Geom g, DevErr*
       }
     }
   };
-  stage(0, std::integral_constant<int, Z1>{});
+  if constexpr (PHI) stage_phi(0, std::integral_constant<int, FZ>{});
+  else stage(0, std::integral_constant<int, Z1>{});
   if (fast) pass(std::true_type{}, 0);
   else pass(std::false_type{}, 0);
 #pragma nounroll
   for (int h = 1; h < NZ; ++h) {
-    stage(h, std::integral_constant<int, Z1 - 1>{});
+    if constexpr (PHI) stage_phi(h, std::integral_constant<int, PR / NZ>{});
+    else stage(h, std::integral_constant<int, Z1 - 1>{});
     if (fast) pass(std::true_type{}, h);
     else pass(std::false_type{}, h);
   }
@@ -1267,6 +1345,18 @@ pm_status run_kick_float(pm_context* c, const pm_species* in, pm_species* out,
   return PM_OK;
 }
 
+// two bricks per workgroup: R = 16, an even number of bricks per side, z quarters of
+// whole cells
+static size_t pair_bytes(const Geom& g) {
+  return (size_t)3 * (2 * PR + 1) * (PR + 1) * (PR / 4 + 1) * 4 +
+         (size_t)2 * MAXSP * (g.B * g.B * g.B + 1) * 4 * 2;
+}
+static bool pair_shape(const Geom& g) {
+  return g.B * g.r == PR && g.lgnb >= 1 && (g.B % 4) == 0 && pair_bytes(g) <= 48 * 1024;
+}
+
+bool kick_takes_phi(const pm_context* c) { return pair_shape(c->g); }
+
 // All species of a compressed state: one brick kernel launch, then the re-sort of each
 // species. offs[s]: input cell offsets; perm[s] (device int64 [n], nullable): new stream
 // position -> old stream position. P, V: the species' code widths.
@@ -1274,8 +1364,9 @@ template <int P, int V>
 static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_species* out,
                                    int n_sp, int64_t* const* offs, const float* acc,
                                    const float* amax, double ck, double cd,
-                                   int64_t* const* perm, const float* const* app) {
+                                   int64_t* const* perm, const float* const* app, bool phi) {
   const Geom& g = c->g;
+  if (phi && !kick_takes_phi(c)) return PM_ERR_ARG;
   if (n_sp <= 0 || n_sp > MAXSP) return PM_ERR_ARG;
   const int B3 = g.B * g.B * g.B;
   // the species' scratch arrays start at multiples of 8 particles (16-byte digit loads)
@@ -1312,6 +1403,7 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
   KickArgs A{};
   A.n_sp = n_sp;
   A.acc = acc;
+  A.scale = grad_scale(g.ng);
   A.ck = (float)ck;
   A.cdS = cd * g.SL * (P == 1 ? 1.0 : 256.0);
   for (int s = 0; s < n_sp; ++s) {
@@ -1369,12 +1461,13 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
     ProfScope ps(c, ST_KICK);
     const int RN = g.B * g.r;
     const size_t tail = (size_t)MAXSP * (B3 + 1) * 4 * 2;
-    // two bricks per workgroup: R = 16, an even number of bricks per side, z quarters of
-    // whole cells
-    const size_t pbytes = (size_t)3 * (2 * PR + 1) * (PR + 1) * (PR / 4 + 1) * 4 + 2 * tail;
+    const size_t pbytes = pair_bytes(g);
     const size_t fbytes = (size_t)3 * (RN + 1) * (RN + 1) * (RN + 1) * 4;
-    if (RN == PR && g.lgnb >= 1 && (g.B % 4) == 0 && pbytes <= 48 * 1024)
-      hipLaunchKernelGGL((k_kick_pair<256, 4, P, V>), dim3((unsigned)(g.nbrick / 2)),
+    if (phi)
+      hipLaunchKernelGGL((k_kick_pair<256, 4, true, P, V>), dim3((unsigned)(g.nbrick / 2)),
+                         dim3(256), (size_t)FX * FY * FZ * 4 + 2 * tail, c->stream, A, g, c->err);
+    else if (pair_shape(g))
+      hipLaunchKernelGGL((k_kick_pair<256, 4, false, P, V>), dim3((unsigned)(g.nbrick / 2)),
                          dim3(256), pbytes, c->stream, A, g, c->err);
     else if (RN == 16 && fbytes + tail <= 96 * 1024)
       hipLaunchKernelGGL((k_kick_brick<16, P, V>), dim3((unsigned)g.nbrick), dim3(KB),
@@ -1418,12 +1511,12 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
 pm_status run_kick_compressed_all(pm_context* c, const pm_species* in, pm_species* out,
                                   int n_sp, int64_t* const* offs, const float* acc,
                                   const float* amax, double ck, double cd,
-                                  int64_t* const* perm, const float* const* app) {
+                                  int64_t* const* perm, const float* const* app, bool phi) {
   if (n_sp <= 0 || n_sp > MAXSP) return PM_ERR_ARG;
   const int kind = common_width_kind(in, n_sp);
   if (kind < 0) return PM_ERR_ARG;
   return width_dispatch(kind, [&](auto P_, auto V_) {
     return kick_compressed_t<decltype(P_)::value, decltype(V_)::value>(
-        c, in, out, n_sp, offs, acc, amax, ck, cd, perm, app);
+        c, in, out, n_sp, offs, acc, amax, ck, cd, perm, app, phi);
   });
 }
