@@ -174,7 +174,7 @@ __device__ __forceinline__ uint32_t dep_add(NT* node, CT code, uint32_t org, int
 // 2^-27, the unit of the 1-byte form, so that the same integer sums apply.
 // MORE: more than two species.
 template <int TT, int PB, bool MORE>
-__global__ __launch_bounds__(DEP_THREADS, MORE || TT == 0 ? 4 : 6) void k_deposit_tile(
+__global__ __launch_bounds__(DEP_THREADS, MORE && TT == 0 ? 2 : MORE || TT == 0 ? 4 : 6) void k_deposit_tile(
     DepArgs A, Geom g, float* rho) {
   using CT = typename std::conditional<PB == 1, uint32_t, uint64_t>::type;
   constexpr int NT = DEP_THREADS, NW = NT / 64;
