@@ -396,10 +396,18 @@ __global__ __launch_bounds__(ST) void k_scatter_tile(AdjArgs A, Geom g, float* m
 constexpr int GT = 512;  // gather threads per workgroup
 constexpr int GR = 16, GR1 = GR + 1;
 
+// PHI: acc is the potential, staged with two nodes around the brick (x in [x0 - 4, x0 + 20),
+// y and z from -2 to R + 2), and a particle takes the differences at its nodes itself: two
+// meshes are read instead of four, and no pass writes the three.
+constexpr int GX = GR + 8, GY = GR + 5;
+template <bool PHI>
 __global__ __launch_bounds__(GT) void k_gather_brick(AdjArgs A, Geom g, const float* acc,
-                                                     const float* nu) {
+                                                     const float* nu, float scale) {
   constexpr int FS = GR1 * GR1 * GR1;
-  __shared__ float Fm[4 * FS];  // a_x, a_y, a_z, nu on the brick's nodes
+  constexpr int NC = PHI ? 1 : 4;  // meshes staged on the brick's nodes
+  // a_x, a_y, a_z, nu on the brick's nodes; PHI: nu there, then phi [GY][GY][GX]
+  __shared__ __align__(16) float Fm[PHI ? FS + 3 + GX * GY * GY : 4 * FS];
+  float* Fp = Fm + ((FS + 3) & ~3);
   extern __shared__ int64_t loff[];  // [B^3 + 1]: sized at launch, so that two
                                      // workgroups fit one CU's LDS at B = 4
   const int B = g.B, B3 = B * B * B, r = g.r;
@@ -412,7 +420,7 @@ __global__ __launch_bounds__(GT) void k_gather_brick(AdjArgs A, Geom g, const fl
   {
     // rows of 16 nodes as float4 loads plus the x = 16 halo column; all loads of a
     // thread are issued before its LDS writes
-    constexpr int ROWS = 4 * GR1 * GR1, NQ = ROWS * 4;
+    constexpr int ROWS = NC * GR1 * GR1, NQ = ROWS * 4;
     constexpr int PQ = (NQ + GT - 1) / GT, PH = (ROWS + GT - 1) / GT;
     const bool wrapx = ox + GR >= ng;
     float4 vq[PQ];
@@ -426,7 +434,7 @@ __global__ __launch_bounds__(GT) void k_gather_brick(AdjArgs A, Geom g, const fl
       int64_t gz = oz + lz, gy = oy + ly;
       gz -= gz >= ng ? ng : 0;
       gy -= gy >= ng ? ng : 0;
-      const float* src = c < 3 ? acc + (int64_t)c * n3 : nu;
+      const float* src = !PHI && c < 3 ? acc + (int64_t)c * n3 : nu;
       vq[k] = *(const float4*)(src + (gz * ng + gy) * ng + ox + 4 * q);
     }
 #pragma unroll
@@ -437,7 +445,7 @@ __global__ __launch_bounds__(GT) void k_gather_brick(AdjArgs A, Geom g, const fl
       int64_t gz = oz + lz, gy = oy + ly;
       gz -= gz >= ng ? ng : 0;
       gy -= gy >= ng ? ng : 0;
-      const float* src = c < 3 ? acc + (int64_t)c * n3 : nu;
+      const float* src = !PHI && c < 3 ? acc + (int64_t)c * n3 : nu;
       vh[k] = src[(gz * ng + gy) * ng + (wrapx ? 0 : ox + GR)];
     }
 #pragma unroll
@@ -455,6 +463,25 @@ __global__ __launch_bounds__(GT) void k_gather_brick(AdjArgs A, Geom g, const fl
     for (int k = 0; k < PH; ++k) {
       const int row = threadIdx.x + k * GT;
       if (row < ROWS) Fm[row * GR1 + GR] = vh[k];
+    }
+    if constexpr (PHI) {
+      typedef float v4 __attribute__((ext_vector_type(4)));
+      constexpr int Q = GX / 4, NP = GY * GY * Q, PP = (NP + GT - 1) / GT;
+      const uint32_t mu = (uint32_t)(ng - 1), ngu = (uint32_t)ng;
+      v4 vp[PP];
+#pragma unroll
+      for (int k = 0; k < PP; ++k) {
+        const uint32_t i = min(threadIdx.x + k * GT, (unsigned)NP - 1u);
+        const uint32_t row = i / Q, seg = i - row * Q, lz = row / GY, ly = row - lz * GY;
+        const uint32_t gz = ((uint32_t)oz + lz - 2u) & mu, gy = ((uint32_t)oy + ly - 2u) & mu,
+                       gx = ((uint32_t)ox + 4u * seg - 4u) & mu;
+        vp[k] = *(const v4*)(acc + ((uint64_t)(gz * ngu + gy) * ngu + gx));
+      }
+#pragma unroll
+      for (int k = 0; k < PP; ++k) {
+        const uint32_t i = threadIdx.x + k * GT;
+        if (i < NP) *(v4*)(Fp + 4 * i) = vp[k];
+      }
     }
   }
   const float fn = g.ngL;  // d W / d x per axis is +-n / L
@@ -499,8 +526,22 @@ __global__ __launch_bounds__(GT) void k_gather_brick(AdjArgs A, Geom g, const fl
 #pragma unroll
           for (int dx = 0; dx < 2; ++dx) {
             const int node = ((li[2] + dz) * GR1 + (li[1] + dy)) * GR1 + (li[0] + dx);
-            const float val = g0 * Fm[node] + g1 * Fm[FS + node] + g2 * Fm[2 * FS + node] +
-                              sp.sscale * Fm[3 * FS + node];
+            float val;
+            if constexpr (PHI) {
+              const float* p = Fp + ((li[2] + 2) * GY + li[1] + 2) * GX + li[0] + 4;
+              auto at = [&](int x, int y, int z) { return p[(z * GY + y) * GX + x]; };
+              const float gx = 8.f * (at(dx + 1, dy, dz) - at(dx - 1, dy, dz)) -
+                               (at(dx + 2, dy, dz) - at(dx - 2, dy, dz));
+              const float gy = 8.f * (at(dx, dy + 1, dz) - at(dx, dy - 1, dz)) -
+                               (at(dx, dy + 2, dz) - at(dx, dy - 2, dz));
+              const float gz = 8.f * (at(dx, dy, dz + 1) - at(dx, dy, dz - 1)) -
+                               (at(dx, dy, dz + 2) - at(dx, dy, dz - 2));
+              val = g0 * (-scale * gx) + g1 * (-scale * gy) + g2 * (-scale * gz) +
+                    sp.sscale * Fm[node];
+            } else {
+              val = g0 * Fm[node] + g1 * Fm[FS + node] + g2 * Fm[2 * FS + node] +
+                    sp.sscale * Fm[3 * FS + node];
+            }
             const float wx = dx ? f[0] : 1.f - f[0];
             const float wy = dy ? f[1] : 1.f - f[1];
             const float wz = dz ? f[2] : 1.f - f[2];
@@ -582,7 +623,12 @@ pm_status run_step_vjp(pm_context* c, const pm_species* in, int n_sp, double dt,
   // forward recomputation: density, acceleration mesh (in the context mesh)
   float* acc = c->mesh;
   if ((s = deposit_all(c, in, n_sp, P, acc)) != PM_OK) return s;
-  if ((s = run_force(c, acc, acc, c->nyq, c->amax)) != PM_OK) return s;
+  // the potential alone where the kick and the gather take its differences themselves
+  const bool phi = tiled && kick_takes_phi(c);
+  const float* field = acc;
+  if (phi) s = run_potential(c, acc, acc + n3, c->nyq, c->amax, &field);
+  else s = run_force(c, acc, acc, c->nyq, c->amax);
+  if (s != PM_OK) return s;
   // the re-sort of compressed streams: new stream position -> old
   int64_t* perm[4] = {nullptr, nullptr, nullptr, nullptr};
   if (in[0].layout == PM_COMPRESSED) {
@@ -616,8 +662,8 @@ pm_status run_step_vjp(pm_context* c, const pm_species* in, int n_sp, double dt,
       out[i].hdr = (pm_shdr*)(pool + at);
       at += align256(sizeof(pm_shdr));
     }
-    if ((s = run_kick_compressed_all(c, in, out, n_sp, P.offs, acc, c->amax, dt, dt, perm)) !=
-        PM_OK)
+    if ((s = run_kick_compressed_all(c, in, out, n_sp, P.offs, field, c->amax, dt, dt, perm,
+                                     nullptr, phi)) != PM_OK)
       return s;
   }
   // cotangents into old order; g_v lands in lv0
@@ -664,14 +710,22 @@ pm_status run_step_vjp(pm_context* c, const pm_species* in, int n_sp, double dt,
   }
   {
     ProfScope ps(c, ST_ADJOINT);
-    if ((s = run_force_transpose(c, mu, c->nyq)) != PM_OK) return s;
+    // a mesh for the transposed force: the context's first when the potential is in the
+    // scratch mesh, else that one
+    float* tmp = phi ? c->mesh : (float*)scratch(c, SC_SPEC, (size_t)n3 * sizeof(float));
+    if (!tmp) return PM_ERR_NOMEM;
+    if ((s = run_force_transpose(c, mu, tmp, c->nyq)) != PM_OK) return s;
   }
   {
     ProfScope ps(c, ST_ADJOINT);
     if (tiled) {
-      if (T.n_sp > 0)
-        hipLaunchKernelGGL(k_gather_brick, dim3((unsigned)g.nbrick), dim3(GT),
-                           (size_t)(g.B * g.B * g.B + 1) * 8, c->stream, T, g, acc, mu);
+      const size_t lds = (size_t)(g.B * g.B * g.B + 1) * 8;
+      if (T.n_sp > 0 && phi)
+        hipLaunchKernelGGL(k_gather_brick<true>, dim3((unsigned)g.nbrick), dim3(GT), lds,
+                           c->stream, T, g, field, (const float*)mu, grad_scale(ng));
+      else if (T.n_sp > 0)
+        hipLaunchKernelGGL(k_gather_brick<false>, dim3((unsigned)g.nbrick), dim3(GT), lds,
+                           c->stream, T, g, (const float*)acc, (const float*)mu, 0.f);
     } else {
       for (int i = 0; i < n_sp; ++i) {
         if (in[i].n == 0) continue;

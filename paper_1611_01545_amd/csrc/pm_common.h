@@ -143,10 +143,16 @@ enum ProfStage {
 // Record a begin/end event pair around a group of launches (no-op unless profiling).
 void prof_begin(pm_context* c, int stage);
 void prof_end(pm_context* c);
+// A scope inside another one counts with the outer stage.
 struct ProfScope {
   pm_context* c;
-  ProfScope(pm_context* cc, int stage) : c(cc) { prof_begin(c, stage); }
-  ~ProfScope() { prof_end(c); }
+  bool outer;
+  ProfScope(pm_context* cc, int stage) : c(cc), outer(cc->prof_open < 0) {
+    if (outer) prof_begin(c, stage);
+  }
+  ~ProfScope() {
+    if (outer) prof_end(c);
+  }
 };
 
 enum ScratchId {
@@ -245,8 +251,8 @@ pm_status run_potential(pm_context* c, const float* rho, float* spec, float2* ny
                         const float** phi);
 inline float grad_scale(int64_t ng) { return (float)((double)ng / 12.0); }
 // adjoint transform: nu = sum_a IDFT(+i k_a G DFT(mu_a)); mu in acc[3] (destroyed),
-// result written to acc component 0.
-pm_status run_force_transpose(pm_context* c, float* acc, float2* nyq);
+// result written to acc component 0. tmp: a mesh of its own.
+pm_status run_force_transpose(pm_context* c, float* acc, float* tmp, float2* nyq);
 
 // kick-drift (pm_kick.hip)
 pm_status run_kick_float(pm_context* c, const pm_species* in, pm_species* out,
