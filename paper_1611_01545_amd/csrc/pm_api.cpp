@@ -383,8 +383,14 @@ pm_status pm_step(pm_ctx c, const pm_species* in, pm_species* out, int n_sp, dou
     return run_kick_compressed_all(c, in, out, n_sp, offs, field, c->amax, dt, dt, nullptr,
                                    nullptr, phi);
   }
-  if ((s = run_deposit(c, in, n_sp, mesh)) != PM_OK) return s;
-  if ((s = run_force(c, mesh, mesh, c->nyq, c->amax)) != PM_OK) return s;
+  // the transform reads the deposit's fixed-point sums as they are
+  const unsigned long long* fixed = nullptr;
+  double unit = 0.0;
+  {
+    ProfScope ps(c, ST_DEPOSIT);
+    if ((s = run_deposit_fixed(c, in, n_sp, &fixed, &unit)) != PM_OK) return s;
+  }
+  if ((s = run_force(c, MeshSource(fixed, unit), mesh, c->nyq, c->amax)) != PM_OK) return s;
   return kick_all(c, in, out, n_sp, mesh, c->amax, dt, dt, nullptr);
 }
 

@@ -239,15 +239,27 @@ pm_status run_reduce_noalloc(pm_context* c, const pm_species* sp, int n_sp,
 
 // deposit (pm_deposit.hip)
 pm_status run_deposit(pm_context* c, const pm_species* sp, int n_sp, float* rho);
+// float species into the context's fixed-point mesh: density = *fixed times *unit. Cleared
+// by each call and not by its reader, so that no state outlives a call that was captured
+pm_status run_deposit_fixed(pm_context* c, const pm_species* sp, int n_sp,
+                            const unsigned long long** fixed, double* unit);
 pm_status run_deposit_tile(pm_context* c, const pm_species* sp, int n_sp,
                            int64_t* const* offs, float* rho);
 
 // FFT (pm_fft.hip)
 pm_status build_kernel_table(pm_context* c);
-pm_status run_force(pm_context* c, const float* rho, float* acc, float2* nyq,
+// A density mesh: floats, or 64-bit fixed-point sums times unit
+struct MeshSource {
+  const float* rho = nullptr;
+  const unsigned long long* fixed = nullptr;
+  double unit = 0.0;
+  MeshSource(const float* r) : rho(r) {}
+  MeshSource(const unsigned long long* q, double u) : fixed(q), unit(u) {}
+};
+pm_status run_force(pm_context* c, const MeshSource& rho, float* acc, float2* nyq,
                     float* amax);
 // the potential alone, in the context's scratch (until the next transform), and max |a|
-pm_status run_potential(pm_context* c, const float* rho, float* spec, float2* nyq, float* amax,
+pm_status run_potential(pm_context* c, const MeshSource& rho, float* spec, float2* nyq, float* amax,
                         const float** phi);
 inline float grad_scale(int64_t ng) { return (float)((double)ng / 12.0); }
 // adjoint transform: nu = sum_a IDFT(+i k_a G DFT(mu_a)); mu in acc[3] (destroyed),

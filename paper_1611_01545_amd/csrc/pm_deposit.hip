@@ -610,12 +610,28 @@ pm_status run_deposit(pm_context* c, const pm_species* sp, int n_sp, float* rho)
     if (st != PM_OK) return st;
     return run_deposit_tile(c, sp, n_sp, offs, rho);
   }
-  // float layout
   ProfScope ps(c, ST_DEPOSIT);
+  const unsigned long long* acc = nullptr;
+  double unit = 0.0;
+  const pm_status st = run_deposit_fixed(c, sp, n_sp, &acc, &unit);
+  if (st != PM_OK) return st;
+  const int64_t n3 = g.ng * g.ng * g.ng;
+  hipLaunchKernelGGL(k_fixed_to_float, dim3((unsigned)cdiv(n3, 256)), dim3(256), 0, c->stream,
+                     acc, n3, unit, rho);
+  PM_LAUNCH_CHECK();
+  return PM_OK;
+}
+
+pm_status run_deposit_fixed(pm_context* c, const pm_species* sp, int n_sp,
+                            const unsigned long long** fixed, double* unit) {
+  const Geom& g = c->g;
+  if (n_sp <= 0 || n_sp > MAX_SP) return PM_ERR_ARG;
+  for (int s = 0; s < n_sp; ++s)
+    if (sp[s].layout != PM_FLOAT) return PM_ERR_ARG;
   const int64_t n3 = g.ng * g.ng * g.ng;
   unsigned long long* acc = (unsigned long long*)scratch(c, SC_ACC64, (size_t)n3 * 8);
   if (!acc) return PM_ERR_NOMEM;
-  pm_status st = launch_fill_u64(c, (uint64_t*)acc, n3, 0ull);
+  const pm_status st = launch_fill_u64(c, (uint64_t*)acc, n3, 0ull);
   if (st != PM_OK) return st;
   double mmax = 0.0;
   for (int s = 0; s < n_sp; ++s) mmax = fmax(mmax, sp[s].mass);
@@ -625,9 +641,8 @@ pm_status run_deposit(pm_context* c, const pm_species* sp, int n_sp, float* rho)
     hipLaunchKernelGGL(k_deposit_float, dim3((unsigned)cdiv(sp[s].n, 256)), dim3(256), 0,
                        c->stream, sp[s].x, sp[s].n, g.ng, g.ngL, scale, acc);
   }
-  double unit = mmax > 0 ? mmax * 0x1p-32 * (double)n3 / (g.box * g.box * g.box) : 0.0;
-  hipLaunchKernelGGL(k_fixed_to_float, dim3((unsigned)cdiv(n3, 256)), dim3(256), 0, c->stream,
-                     acc, n3, unit, rho);
   PM_LAUNCH_CHECK();
+  *fixed = acc;
+  *unit = mmax > 0 ? mmax * 0x1p-32 * (double)n3 / (g.box * g.box * g.box) : 0.0;
   return PM_OK;
 }
