@@ -30,7 +30,9 @@
 // scratch use doubled the time of these short-lived waves). With the offset scans, for two
 // species: 39 -> 12 us on 64^3 nodes, 281 -> 152 at 256^3 (8^3-cell tiles), 429 -> 363 at
 // 512^3, 3.02 -> 2.76 ms at 1024^3, 270 -> 227 us on the 128^3 coarse mesh with one node
-// per cell.
+// per cell. A single species has a variant without the second one's sums, table and
+// conversions: 2 M particles on 256^3 nodes 62 -> 56 us, on 512^3 275 -> 253 (one particle
+// per cell; 64-bit sums with a binary search per particle take 210 there, and 70 at 256^3).
 #include "pm_codec.h"
 #include "pm_scan.h"
 
@@ -172,10 +174,12 @@ __device__ __forceinline__ uint32_t dep_add(NT* node, CT code, uint32_t org, int
 // PB = 2 the offset inside a cell has 17 fractional bits of a mesh cell per axis, and each
 // node's weight (the exact product, a multiple of 2^-51) is rounded to a multiple of
 // 2^-27, the unit of the 1-byte form, so that the same integer sums apply.
-// MORE: more than two species.
-template <int TT, int PB, bool MORE>
-__global__ __launch_bounds__(DEP_THREADS, MORE && TT == 0 ? 2 : MORE || TT == 0 ? 4 : 6) void k_deposit_tile(
+// SP: one species, two, or (3) any larger number, in pairs.
+template <int TT, int PB, int SP>
+__global__ __launch_bounds__(DEP_THREADS, SP == 3 && TT == 0 ? 2 : SP == 3 || TT == 0 ? 4 : 6) void k_deposit_tile(
     DepArgs A, Geom g, float* rho) {
+  constexpr bool MORE = SP == 3;
+  constexpr int SB = SP == 1 ? 1 : 2;  // species of a batch
   using CT = typename std::conditional<PB == 1, uint32_t, uint64_t>::type;
   constexpr int NT = DEP_THREADS, NW = NT / 64;
   constexpr int WIN = dep_win<TT>(), TABS = dep_tabs<TT>();
@@ -190,6 +194,7 @@ __global__ __launch_bounds__(DEP_THREADS, MORE && TT == 0 ? 2 : MORE || TT == 0 
   const int Rp = R + 1, NS = TT ? dep_slots(16) : dep_slots(R);
   __shared__ int wsum[2][NW];
   __shared__ double lost[NW];  // weight units missing from the sums, per wave
+  __shared__ int full[NW];     // a cell of the wave that 32-bit sums cannot hold
   uint32_t* node = (uint32_t*)smem;                      // [2][NS] weight sums of two species
   uint2* tab = (uint2*)(node + 2 * NS);                  // [TABS][NE] stream start, origin
   int* pre = (int*)(tab + TABS * NE);                    // [TABS][NE + 1] particles before
@@ -201,8 +206,9 @@ __global__ __launch_bounds__(DEP_THREADS, MORE && TT == 0 ? 2 : MORE || TT == 0 
   const int ncs = (int)g.nc;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
-  for (int i = threadIdx.x; i < NS / 2; i += NT) ((uint4*)node)[i] = make_uint4(0, 0, 0, 0);
-  if (threadIdx.x < (NS & 1) * 2) node[2 * NS - 2 + threadIdx.x] = 0;
+  constexpr int ZB = 4 / SB;  // slots of a 16-byte store
+  for (int i = threadIdx.x; i < NS / ZB; i += NT) ((uint4*)node)[i] = make_uint4(0, 0, 0, 0);
+  if (threadIdx.x < NS % ZB * SB) node[NS / ZB * 4 + threadIdx.x] = 0;
   for (int i = threadIdx.x; i < TABS * WIN * (int)sizeof(MT) / 4; i += NT)
     ((uint32_t*)mark)[i] = 0u;
   // per-thread density of its slots i = threadIdx.x + k NT, summed over species in order
@@ -213,7 +219,7 @@ __global__ __launch_bounds__(DEP_THREADS, MORE && TT == 0 ? 2 : MORE || TT == 0 
 
   const int n_sp = MORE ? A.n_sp : min(A.n_sp, 2);
   for (int s0 = 0; s0 < (MORE ? n_sp : min(n_sp, 1)); s0 += 2) {
-    const int ns = min(2, n_sp - s0);
+    const int ns = SP == 1 ? 1 : min(2, n_sp - s0);
     // cells of both species: a thread takes K consecutive extended cells
     constexpr int KMAX = TT ? ((TT + 1) * (TT + 1) * (TT + 1) + NT - 1) / NT : 2;
     const int K = TT ? KMAX : (NE + NT - 1) / NT;
@@ -232,7 +238,7 @@ __global__ __launch_bounds__(DEP_THREADS, MORE && TT == 0 ? 2 : MORE || TT == 0 
                           wrapc(tz * T + ez - 1, ncs))
                : 0u;
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
+        for (int s = 0; s < SB; ++s) {
           const int64_t* off = A.sp[s0 + (s < ns ? s : 0)].off;
           const int64_t o0 = off[key], o1 = off[key + 1];
           start[s][k] = (uint32_t)o0;
@@ -240,24 +246,36 @@ __global__ __launch_bounds__(DEP_THREADS, MORE && TT == 0 ? 2 : MORE || TT == 0 
         }
       }
     };
+    // A cell of the tile gives its particles' whole weight to (r + 1)^3 slots, and 32
+    // particles' weight is 2^32: with more than 32 (r + 1)^3 of them a 32-bit slot passes
+    // 2^32 for certain. Such a tile takes the 64-bit sums at once: 79 k of 262 k particles in
+    // one cell of 128^3 nodes 1229 -> 622 us, 30% of 2 M in 1/64000 of 256^3 2359 -> 1255.
+    const int most = 32 * (r + 1) * (r + 1) * (r + 1) + 32;
+    bool crowd = false;
     int before[2] = {0, 0}, loc[2] = {0, 0};
     if (cells) {
       fetch();
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
+      for (int s = 0; s < SB; ++s) {
 #pragma unroll
-        for (int k = 0; k < KMAX; ++k) loc[s] += cnt[s][k];
+        for (int k = 0; k < KMAX; ++k) {
+          const int e = e0 + k;
+          loc[s] += cnt[s][k];
+          if (cnt[s][k] > most) crowd |= e % E && (e / E) % E && e / (E * E);  // no shell cell
+        }
         before[s] = pmscan::wave_incl_scan_dpp(loc[s]);
       }
     }
+    const bool wave_crowd = __any(crowd);
     if (lane == 63) {
       wsum[0][wv] = before[0];
-      wsum[1][wv] = before[1];
+      if (SP != 1) wsum[1][wv] = before[1];
+      full[wv] = wave_crowd;
     }
     __syncthreads();  // also: the last pair is done with the tables
     int np[2] = {0, 0};  // particles of the tile and its shell
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
+    for (int s = 0; s < SB; ++s) {
       before[s] -= loc[s];
       for (int w = 0; w * 64 * K < NE; ++w) {  // the waves with cells
         const int v = wsum[s][w];
@@ -266,6 +284,10 @@ __global__ __launch_bounds__(DEP_THREADS, MORE && TT == 0 ? 2 : MORE || TT == 0 
       }
       np[s] = __builtin_amdgcn_readfirstlane(np[s]);
     }
+    int any_full = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) any_full |= full[w];
+    const bool dense = __builtin_amdgcn_readfirstlane(any_full) != 0;
     // species s's table into slot t of the tables
     auto build = [&](int s, int t) {
       if (!cells) return;
@@ -380,23 +402,25 @@ __global__ __launch_bounds__(DEP_THREADS, MORE && TT == 0 ? 2 : MORE || TT == 0 
     if constexpr (TABS == 2) {
       // the first windows of both species, their loads in flight together
       build(0, 0);
-      build(1, 1);
+      if (SP != 1) build(1, 1);
       __syncthreads();
-      const int n0 = min(WIN, np[0]), n1 = min(WIN, np[1]);
-      set_marks(0, 0, n0);
-      set_marks(1, 0, n1);
-      __syncthreads();
-      Batch B0, B1;
-      load(0, 0, 0, n0, B0);
-      load(ns - 1, 1, 0, n1, B1);
-      add(node, B0);
-      add(node + NS, B1);
-      rest(0, 0, node, WIN);
-      rest(1, 1, node + NS, WIN);
-    } else {
+      if (!dense) {
+        const int n0 = min(WIN, np[0]), n1 = min(WIN, np[1]);
+        set_marks(0, 0, n0);
+        if (SP != 1) set_marks(1, 0, n1);
+        __syncthreads();
+        Batch B0, B1;
+        load(0, 0, 0, n0, B0);
+        if (SP != 1) load(ns - 1, 1, 0, n1, B1);
+        add(node, B0);
+        if (SP != 1) add(node + NS, B1);
+        rest(0, 0, node, WIN);
+        if (SP != 1) rest(1, 1, node + NS, WIN);
+      }
+    } else if (!dense) {
       build(0, 0);
       rest(0, 0, node, 0);
-      if (ns > 1) {
+      if (SP != 1 && ns > 1) {
         __syncthreads();
         build(1, 0);
         rest(1, 0, node + NS, 0);
@@ -414,12 +438,12 @@ __global__ __launch_bounds__(DEP_THREADS, MORE && TT == 0 ? 2 : MORE || TT == 0 
       uint32_t v0 = 0, v1 = 0;
       if (i < NS) {
         v0 = node[i];
-        v1 = node[NS + i];  // 0 without a second species
+        if (SP != 1) v1 = node[NS + i];  // 0 without a second species
       }
       const double w0 = (double)v0, w1 = (double)v1;
       sum += w0 + w1;
       dens[k] = (MORE ? racc[k] : 0.0f) + (float)(w0 * unit0);
-      dens[k] += (float)(w1 * unit1);
+      if (SP != 1) dens[k] += (float)(w1 * unit1);
     }
     if constexpr (PB == 1) units = (double)got * 0x1p27;
     sum = wave_sum_dpp(units - sum);
@@ -428,7 +452,7 @@ __global__ __launch_bounds__(DEP_THREADS, MORE && TT == 0 ? 2 : MORE || TT == 0 
     double all = 0.0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) all += lost[w];
-    if (all == 0.0) {
+    if (all == 0.0 && !dense) {
 #pragma unroll
       for (int k = 0; k < NPT; ++k) racc[k] = dens[k];
     } else {
@@ -438,7 +462,7 @@ __global__ __launch_bounds__(DEP_THREADS, MORE && TT == 0 ? 2 : MORE || TT == 0 
 #pragma unroll
         for (int k = 0; k < NPT; ++k) racc[k] = 0.0f;
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
+      for (int s = 0; s < SB; ++s) {
         if (s >= ns) break;
         __syncthreads();
         for (int i = threadIdx.x; i < 2 * NS; i += NT) node[i] = 0;
@@ -579,12 +603,12 @@ pm_status run_deposit_tile(pm_context* c, const pm_species* sp, int n_sp,
   auto launch = [&](auto tt, auto pb) {
     constexpr int TT = decltype(tt)::value, PB = decltype(pb)::value;
     const size_t lds = dep_lds_bytes<TT>(A.R, ne);
-    if (A.n_sp > 2)
-      hipLaunchKernelGGL((k_deposit_tile<TT, PB, true>), dim3(grid), dim3(DEP_THREADS), lds,
-                         c->stream, A, g, rho);
-    else
-      hipLaunchKernelGGL((k_deposit_tile<TT, PB, false>), dim3(grid), dim3(DEP_THREADS), lds,
-                         c->stream, A, g, rho);
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(grid), dim3(DEP_THREADS), lds, c->stream, A, g, rho);
+    };
+    if (A.n_sp > 2) go(k_deposit_tile<TT, PB, 3>);
+    else if (A.n_sp == 2) go(k_deposit_tile<TT, PB, 2>);
+    else go(k_deposit_tile<TT, PB, 1>);
   };
   if (width_pos(sp[0]) == 1) {
     if (A.T == 4 && A.r == 4) launch(IC<4>{}, IC<1>{});
