@@ -233,6 +233,20 @@ def stage_bytes(name: str, n: int, wl) -> float:
     }.get(name, 0.0)
 
 
+def step_stage_bytes(name: str, n: int, wl) -> float:
+    """stage_bytes in a step. With 4 mesh cells per compression cell and two bricks of 16
+    mesh cells or more per side the kick takes the differences of the potential itself:
+    the stencil pass only reads it for the largest |a|, and no force mesh is written."""
+    b = stage_bytes(name, n, wl)
+    if n == 4 * wl.n_cell and n >= 32:
+        n3 = float(n) ** 3
+        if name == "force_grad":
+            b -= 12 * n3                        # no components out
+        elif name == "interp_kick_drift":
+            b -= 8 * n3                         # the potential in, not three meshes
+    return b
+
+
 def cpu_baseline_and_error(ctx_cls, make_workload, base: str):
     """The oracle (FP64, numpy, one thread) timed on a bounded sample of the workload:
     the same recipe at 1/4 of the linear size, five compressed steps. The GPU step on
@@ -360,7 +374,7 @@ def timed_steps(ctx, A, B, wl, torch, steps, warmup):
         if cnt == 0:
             continue
         per = ms / cnt
-        b = stage_bytes(name, wl.n_mesh, wl)
+        b = step_stage_bytes(name, wl.n_mesh, wl)
         stages[name] = {"ms_per_step": ms / steps, "launches_per_step": cnt / steps,
                         "ms_per_launch": per,
                         "gbs": (b / (per * 1e-3) / 1e9) if b else None}
@@ -374,14 +388,14 @@ def stage_kernel(name: str, n: int):
     one transform of the potential (one launch per pass) and the stencil pass for its
     three components."""
     return {
-        "deposit": "k_deposit_tile<4, 1>",
-        "fft_x_r2c": f"k_row_r2c<{n // 2}>",
+        "deposit": "k_deposit_tile<4, 1, 2>",
+        "fft_x_r2c": f"k_row_r2c<{n // 2}, false>",
         "fft_y_fwd": f"k_col_fft<{n}, 16, -1, 0>",
         "fft_z": f"k_col_zconv<{n}, 16, 0, true>",
         "fft_y_inv": f"k_col_fft<{n}, 16, 1, 0>",
         "fft_x_c2r": f"k_row_c2r<{n // 2}>",
         "force_grad": "k_grad4",
-        "interp_kick_drift": "k_kick_pair<256, 4, 1, 2>",
+        "interp_kick_drift": "k_kick_pair<256, 4, true, 1, 2>",
     }.get(name)
 
 
@@ -398,7 +412,7 @@ def roofline_of(stages, name, wl, config):
             "achieved": st["gbs"], "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": st["gbs"] / HBM_PEAK_GBS,
             "traffic": measured_traffic(name, config),
-            "bytes_per_launch": stage_bytes(name, wl.n_mesh, wl),
+            "bytes_per_launch": step_stage_bytes(name, wl.n_mesh, wl),
             "ms_per_launch": st["ms_per_launch"]}
 
 
@@ -783,7 +797,7 @@ def main():
         if st["gbs"] is not None:
             st["frac"] = st["gbs"] / HBM_PEAK_GBS
             st["traffic"] = measured_traffic(k, args.config)
-    total_model = sum(stage_bytes(k, wl.n_mesh, wl) * stages[k]["launches_per_step"]
+    total_model = sum(step_stage_bytes(k, wl.n_mesh, wl) * stages[k]["launches_per_step"]
                       for k in stages)
     step_frac = total_model / (ms_step * 1e-3) / 1e9 / HBM_PEAK_GBS
 
