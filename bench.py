@@ -238,6 +238,8 @@ def step_stage_bytes(name: str, n: int, wl) -> float:
     mesh cells or more per side the kick takes the differences of the potential itself:
     the stencil pass only reads it for the largest |a|, and no force mesh is written."""
     b = stage_bytes(name, n, wl)
+    if name in ("resort", "cell_offsets"):
+        b *= len(wl.species)                    # one launch sequence for every species
     if n == 4 * wl.n_cell and n >= 32:
         n3 = float(n) ** 3
         if name == "force_grad":
