@@ -195,14 +195,14 @@ pm_status pm_query_sizes(const pm_config* cfg, int64_t n_max, int n_sp, pm_sizes
   st += 2 * grown(n_sp * nb * 4) + grown(n_sp * nb * 4 + 16);  // movers, arrivals, escapes
   st += grown(nc3 * 4 * n_sp);                          // stayers per cell
   st += grown(nc3 * 4) * 2 + grown((nc3 + 1) * 8);      // encode: counts, escapes
-  st += 2 * grown(N * 12 + 8 * n_sp * 6);               // encode: records, two copies; step:
-  st += grown(NP * 2);                                  //   new codes and digits, old order
+  st += 2 * grown(NP * 6) + grown(NP * 2);              // new codes and digits, old order
   st += 4 * grown(NP * 4);                              // sort keys and indices, two copies
-  st += grown(std::max<int64_t>(nb * 8 * n_sp, (N / 256 + 1) * 8));  // grid partials
-  st += grown(rs_blocks * 256 * 4) + grown((rs_blocks * 256 + 1) * 8);  // radix histograms
-  st += grown(std::max<int64_t>(
-      (std::max<int64_t>(n_sp * nc3, std::max<int64_t>(N, rs_blocks * 256)) / 4096 + n_sp) * 8,
-      (nb / 4096 + 1) * n_sp * 24));                    // block sums of the scans
+  st += grown(n_sp * nb * 8);                           // extreme codes per brick
+  st += grown((nc3 / 256 + N / 256 + 3) * 8);           // pack: checksum terms
+  st += grown(rs_blocks * 256 * 4);                     // radix histograms, their offsets
+  st += grown((rs_blocks * 256 + 1 + rs_blocks * 256 / 4096 + 1) * 8);
+  st += grown(std::max<int64_t>((nc3 / 4096 + 1) * n_sp * 8,
+                                (nb / 4096 + 1) * n_sp * 24));  // block sums of the scans
   st += grown(4096) + grown(512 * 25 * 8);              // folds, reductions
   st += grown(N * 12 + n_sp * 256);                     // extra accelerations (PP, long range)
   out->step_scratch_bytes = st;

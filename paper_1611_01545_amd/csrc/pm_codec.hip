@@ -38,9 +38,8 @@ __global__ void k_init_hdr(pm_shdr* h) {
 //                   first pass makes the codes, the last one writes the species' arrays.
 //   k_cell_counts   particles per cell, from the sorted keys
 // Tiles of 4096 records in 76 KB of LDS (two on a CU): a digit's run of a tile is then 16
-// records or more, which is 200 bytes written in one piece. A pass over 16.8 M particles
-// takes 146 us (210 from floats, 168 into the species' arrays), the whole encode of 256^3 +
-// 128^3 particles 939 us, against 3226 with the gather.
+// records or more, which is 200 bytes written in one piece. The whole encode of 16.8 M
+// particles takes 709 us (2860 with the gather).
 constexpr int ST_T = 512, ST_I = 8, ST_TILE = ST_T * ST_I, ST_W = ST_T / 64;
 
 __device__ __forceinline__ void load3(const float* p, float r[3]) {
@@ -119,7 +118,12 @@ __global__ __launch_bounds__(ST_T) void k_sort_hist(const uint32_t* keys, int64_
   if (threadIdx.x <= mask) hist[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = dc[threadIdx.x];
 }
 
-// The record of a particle: 3 P bytes of position codes, then 3 V of velocity codes
+// The record of a particle: 3 P bytes of position codes, then 3 V of velocity codes, in words
+// in LDS and registers. In memory every copy is a pair of arrays as a species holds them: one
+// copy is the output itself, the other one the new codes of a step's re-sort, which are as
+// large for as many particles. So an encode keeps no memory for records beyond a step's, and
+// never replaces arrays that a captured step reads by larger ones. (Two buffers of records in
+// whole words, 24 bytes a particle, take 761 us instead of 783 for 16.8 M particles.)
 template <int P, int V>
 constexpr int rec_words() { return (3 * (P + V) + 3) / 4; }
 
@@ -128,21 +132,55 @@ struct SortArgs {
   const float* v;
   Geom g;
   const uint32_t* kin;
-  const uint32_t* rin;  // records
+  const void* pin;      // position and velocity codes (not the first pass)
+  const void* vin;
   const uint32_t* iin;  // old indices (nullable)
   uint32_t* kout;
-  uint32_t* rout;
+  void* pout;
+  void* vout;
   uint32_t* iout;       // nullable: no permutation asked for
   const int64_t* hoff;  // destinations [digit][tile]
   int64_t n;
   int shift, bits;
   pm_shdr* h;
-  void* pos;  // last pass
-  void* vel;
-  int64_t* perm;
+  int64_t* perm;        // last pass: nullable
 };
 
-template <int P, int V, bool FIRST, bool LAST>
+// Codes in and out of a record's words at byte positions known at compile time. (A byte array
+// filled in a function goes through scratch memory: first pass 157 us for 122.)
+template <int B, int E>  // E bytes from byte B on
+__device__ __forceinline__ void rec_put(uint32_t* w, uint32_t c) {
+  w[B / 4] |= c << (8 * (B % 4));
+  if constexpr (B % 4 + E > 4) w[B / 4 + 1] |= c >> (32 - 8 * (B % 4));
+}
+template <int B, int E>
+__device__ __forceinline__ uint32_t rec_get(const uint32_t* w) {
+  uint32_t c = w[B / 4] >> (8 * (B % 4));
+  if constexpr (B % 4 + E > 4) c |= w[B / 4 + 1] << (32 - 8 * (B % 4));
+  return c & ((1u << (8 * E)) - 1u);
+}
+template <int P, int V, typename PT, typename VT>
+__device__ __forceinline__ void rec_load(uint32_t* w, const PT* p, const VT* v) {
+#pragma unroll
+  for (int q = 0; q < rec_words<P, V>(); ++q) w[q] = 0;
+  rec_put<0, P>(w, p[0]);
+  rec_put<P, P>(w, p[1]);
+  rec_put<2 * P, P>(w, p[2]);
+  rec_put<3 * P, V>(w, v[0]);
+  rec_put<3 * P + V, V>(w, v[1]);
+  rec_put<3 * P + 2 * V, V>(w, v[2]);
+}
+template <int P, int V, typename PT, typename VT>
+__device__ __forceinline__ void rec_store(const uint32_t* w, PT* p, VT* v) {
+  p[0] = (PT)rec_get<0, P>(w);
+  p[1] = (PT)rec_get<P, P>(w);
+  p[2] = (PT)rec_get<2 * P, P>(w);
+  v[0] = (VT)rec_get<3 * P, V>(w);
+  v[1] = (VT)rec_get<3 * P + V, V>(w);
+  v[2] = (VT)rec_get<3 * P + 2 * V, V>(w);
+}
+
+template <int P, int V, bool FIRST>
 __global__ __launch_bounds__(ST_T, 4) void k_sort_pass(SortArgs A) {
   using PT = typename PosCode<P>::T;
   using VT = typename VelCode<V>::T;
@@ -161,9 +199,12 @@ __global__ __launch_bounds__(ST_T, 4) void k_sort_pass(SortArgs A) {
     jmm[0] = 65536;
     jmm[1] = -1;
   }
+  // an XCD's tiles follow one another: their runs of a digit are neighbours, which its L2 joins
+  // into whole lines before they are written (16.8 M particles 782 -> 709 us)
+  const int64_t tile = xcd_run(blockIdx.x, gridDim.x);
   // a wave's items are ST_I rounds of 64 consecutive ones
-  const int64_t base = (int64_t)blockIdx.x * ST_TILE + w * (64 * ST_I) + lane;
-  const int64_t left = A.n - (int64_t)blockIdx.x * ST_TILE;
+  const int64_t base = tile * ST_TILE + w * (64 * ST_I) + lane;
+  const int64_t left = A.n - tile * ST_TILE;
   const int cnt = left < ST_TILE ? (int)left : ST_TILE;
   uint32_t key[ST_I], rec[ST_I][RW];
   int slot[ST_I];
@@ -172,8 +213,7 @@ __global__ __launch_bounds__(ST_T, 4) void k_sort_pass(SortArgs A) {
     const int64_t i = base + 64 * k, j = i < A.n ? i : A.n - 1;
     key[k] = A.kin[j];
     if constexpr (!FIRST) {
-#pragma unroll
-      for (int q = 0; q < RW; ++q) rec[k][q] = A.rin[RW * j + q];
+      rec_load<P, V>(rec[k], (const PT*)A.pin + 3 * j, (const VT*)A.vin + 3 * j);
     }
   }
   if constexpr (FIRST) {
@@ -190,20 +230,19 @@ __global__ __launch_bounds__(ST_T, 4) void k_sort_pass(SortArgs A) {
     }
 #pragma unroll
     for (int k = 0; k < ST_I; ++k) {
-      uint8_t r[4 * RW] = {};
+      PT pc[3];
+      VT vc[3];
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
         uint32_t u;
         pos_code(xx[k][a], SL, S, u);
         const int c = vel_code_v<V>(vv[k][a], vmax);
-        r[P * a] = (uint8_t)u;
-        if constexpr (P == 2) r[P * a + 1] = (uint8_t)(u >> 8);
-        r[3 * P + V * a] = (uint8_t)c;
-        if constexpr (V == 2) r[3 * P + V * a + 1] = (uint8_t)(c >> 8);
+        pc[a] = (PT)u;
+        vc[a] = (VT)c;
         jmn = min(jmn, c);  // a repeated last particle changes nothing
         jmx = max(jmx, c);
       }
-      __builtin_memcpy(rec[k], r, 4 * RW);
+      rec_load<P, V>(rec[k], pc, vc);
     }
     for (int d = 32; d >= 1; d >>= 1) {
       jmn = min(jmn, __shfl_xor(jmn, d, 64));
@@ -253,7 +292,7 @@ __global__ __launch_bounds__(ST_T, 4) void k_sort_pass(SortArgs A) {
 #pragma unroll
       for (int q = 0; q < ST_W; ++q) wcnt[q][threadIdx.x] += (uint32_t)start;
       if (threadIdx.x <= mask)
-        dst0[threadIdx.x] = A.hoff[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] - start;
+        dst0[threadIdx.x] = A.hoff[(int64_t)threadIdx.x * gridDim.x + tile] - start;
     }
   }
   __syncthreads();
@@ -273,33 +312,12 @@ __global__ __launch_bounds__(ST_T, 4) void k_sort_pass(SortArgs A) {
     if (sl >= cnt) continue;
     const int64_t d = dest(sl);
     A.kout[d] = skey[sl];
-    if constexpr (LAST) {
-      uint32_t rr[RW];
+    uint32_t rr[RW];
 #pragma unroll
-      for (int q = 0; q < RW; ++q) rr[q] = srec[RW * sl + q];
-      uint8_t r[4 * RW];
-      __builtin_memcpy(r, rr, 4 * RW);
-      PT* pos = (PT*)A.pos + 3 * d;
-      VT* vel = (VT*)A.vel + 3 * d;
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        uint32_t u = r[P * a], c = r[3 * P + V * a];
-        if constexpr (P == 2) u |= (uint32_t)r[P * a + 1] << 8;
-        if constexpr (V == 2) c |= (uint32_t)r[3 * P + V * a + 1] << 8;
-        pos[a] = (PT)u;
-        vel[a] = (VT)c;
-      }
-    }
+    for (int q = 0; q < RW; ++q) rr[q] = srec[RW * sl + q];
+    rec_store<P, V>(rr, (PT*)A.pout + 3 * d, (VT*)A.vout + 3 * d);
   }
-  if constexpr (!LAST) {
-    // whole records, a word per lane
-#pragma unroll
-    for (int k = 0; k < ST_I * RW; ++k) {
-      const int q = k * ST_T + (int)threadIdx.x, sl = q / RW;
-      if (sl < cnt) A.rout[RW * dest(sl) + (q - RW * sl)] = srec[q];
-    }
-  }
-  if (A.iout || (LAST && A.perm)) {  // uniform: the old indices, the same way
+  if (A.iout || A.perm) {  // uniform: the old indices, the same way
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < ST_I; ++k) {
@@ -311,7 +329,7 @@ __global__ __launch_bounds__(ST_T, 4) void k_sort_pass(SortArgs A) {
     for (int k = 0; k < ST_I; ++k) {
       const int sl = k * ST_T + (int)threadIdx.x;
       if (sl >= cnt) continue;
-      if constexpr (LAST) A.perm[dest(sl)] = (int64_t)srec[sl];
+      if (A.perm) A.perm[dest(sl)] = (int64_t)srec[sl];
       else A.iout[dest(sl)] = srec[sl];
     }
   }
@@ -846,16 +864,21 @@ pm_status run_encode(pm_context* c, const pm_species* in, pm_species* out, int64
     uint32_t* key[2] = {(uint32_t*)scratch(c, SC_KEYA, (size_t)n * 4),
                         (uint32_t*)scratch(c, SC_KEYB, (size_t)n * 4)};
     uint32_t* idx[2] = {nullptr, nullptr};
-    uint32_t* rec[2] = {nullptr, nullptr};
-    const size_t rb = (size_t)4 * ((3 * (width_pos(*out) + width_vel(*out)) + 3) / 4);
-    const int ids[2][2] = {{SC_VALA, SC_VALB}, {SC_TPOS, SC_TVEL}};
     bool have = key[0] && key[1];
-    for (int q = 0; q < 2 && q < passes - 1; ++q) {
-      if (perm) have = have && (idx[q] = (uint32_t*)scratch(c, ids[0][q], (size_t)n * 4));
-      have = have && (rec[q] = (uint32_t*)scratch(c, ids[1][q], (size_t)n * rb));
+    for (int q = 0; q < 2 && q < passes - 1 && perm; ++q)
+      have = have && (idx[q] = (uint32_t*)scratch(c, q ? SC_VALB : SC_VALA, (size_t)n * 4));
+    // the passes write the output and the scratch copy in turn, the last one the output
+    void *cpos = nullptr, *cvel = nullptr;
+    if (passes > 1) {
+      cpos = scratch(c, SC_TPOS, (size_t)n * 3 * width_pos(*out));
+      cvel = scratch(c, SC_TVEL, (size_t)n * 3 * width_vel(*out));
+      have = have && cpos && cvel;
     }
+    // digit counts, and behind their prefixes the scan's block sums (not in the scratch that
+    // a step's scans use: the counts of many particles on few cells need more)
     uint32_t* hist = (uint32_t*)scratch(c, SC_HIST, (size_t)nt * 256 * 4);
-    int64_t* hoff = (int64_t*)scratch(c, SC_HOFF, ((size_t)nt * 256 + 1) * 8);
+    const int64_t nh = nt * 256 + 1;
+    int64_t* hoff = (int64_t*)scratch(c, SC_HOFF, (size_t)(nh + cdiv(nh, SCAN_TILE)) * 8);
     if (!have || !hist || !hoff) return PM_ERR_NOMEM;
     // many more cells than particles: cleared by a grid of their own
     const bool apart = g.ncell3 > 4 * nt * ST_TILE;
@@ -871,31 +894,30 @@ pm_status run_encode(pm_context* c, const pm_species* in, pm_species* out, int64
     A.n = n;
     A.bits = width;
     A.h = out->hdr;
-    A.pos = (void*)out->pos;
-    A.vel = (void*)out->vel;
-    A.perm = perm;
     for (int p = 0; p < passes; ++p) {
       const bool first = p == 0, last = p == passes - 1;
       A.shift = p * width;
       A.kin = key[p & 1];
       A.kout = key[(p + 1) & 1];
-      A.rin = first ? nullptr : rec[(p - 1) & 1];
-      A.rout = last ? nullptr : rec[p & 1];
+      const bool to_out = (passes - 1 - p) % 2 == 0;
+      A.pin = to_out ? cpos : (void*)out->pos;
+      A.vin = to_out ? cvel : (void*)out->vel;
+      A.pout = to_out ? (void*)out->pos : cpos;
+      A.vout = to_out ? (void*)out->vel : cvel;
       A.iin = first ? nullptr : idx[(p - 1) & 1];
       A.iout = last ? nullptr : idx[p & 1];
+      A.perm = last ? perm : nullptr;
       if (!first)
         hipLaunchKernelGGL(k_sort_hist, dim3((unsigned)nt), dim3(ST_T), 0, c->stream, A.kin, n,
                            A.shift, mask, hist);
-      if ((s = scan_u32(c, hist, nt * ((int64_t)mask + 1), hoff)) != PM_OK) return s;
+      if ((s = scan_u32(c, hist, nt * ((int64_t)mask + 1), hoff, hoff + nh)) != PM_OK) return s;
       s = width_dispatch(width_kind(*out), [&](auto P_, auto V_) {
         constexpr int P = decltype(P_)::value, V = decltype(V_)::value;
         auto launch = [&](auto kernel) {
           hipLaunchKernelGGL(kernel, dim3((unsigned)nt), dim3(ST_T), 0, c->stream, A);
         };
-        if (first && last) launch(k_sort_pass<P, V, true, true>);
-        else if (first) launch(k_sort_pass<P, V, true, false>);
-        else if (last) launch(k_sort_pass<P, V, false, true>);
-        else launch(k_sort_pass<P, V, false, false>);
+        if (first) launch(k_sort_pass<P, V, true>);
+        else launch(k_sort_pass<P, V, false>);
         return PM_OK;
       });
       if (s != PM_OK) return s;

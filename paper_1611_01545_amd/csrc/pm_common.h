@@ -38,6 +38,12 @@ __device__ inline int64_t xcd_tile(int64_t bid, int64_t ntiles) {
   return (bid & 7) * (ntiles >> 3) + (bid >> 3);
 }
 
+// The same for any number of tiles: those past the last multiple of 8 keep their places.
+__device__ inline int64_t xcd_run(int64_t bid, int64_t ntiles) {
+  const int64_t per = ntiles >> 3;
+  return bid < 8 * per ? (bid & 7) * per + (bid >> 3) : bid;
+}
+
 // ------------------------------------------------------- partial reductions --
 // Whole-grid min/max without atomics: every workgroup stores its partial result at
 // its own index, and a one-block kernel folds the partials.
@@ -166,8 +172,8 @@ enum ScratchId {
   SC_VALB,         // uint32 [N]
   SC_HIST,         // uint32 radix histograms
   SC_HOFF,         // int64 radix offsets
-  SC_TPOS,         // uint8 [N][3]
-  SC_TVEL,         // uint16 [N][3]
+  SC_TPOS,         // position codes [N][3] (re-sort, encode)
+  SC_TVEL,         // velocity codes [N][3]
   SC_TDST,         // uint32 [N]
   SC_MCNT,         // uint32 [nbrick] per species: movers of each brick
   SC_ASTART,       // uint32 [nbrick+1] per species: first arrival of each brick
@@ -184,6 +190,7 @@ enum ScratchId {
   SC_SPOFF2,
   SC_SPOFF3,
   SC_PARTS,        // per-workgroup partial results of grid reductions
+  SC_KPART,        // int32 [2][nbrick] per species: extreme new velocity codes (kick)
   SC_SPEC,         // float [ng^3] spectrum scratch of the force transforms
   SC_FOLD,         // first-stage results of the grid min / max folds
   SC_ECNT,         // uint32 [nbrick] per species: escapes of each brick, then 4 totals
@@ -215,8 +222,9 @@ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 pm_status launch_fill_u32(pm_context* c, uint32_t* p, int64_t n, uint32_t v);
 pm_status launch_fill_u64(pm_context* c, uint64_t* p, int64_t n, uint64_t v);
 pm_status run_iota(pm_context* c, int64_t* p, int64_t n);  // p[i] = i
-// exclusive scans into int64 out[n+1]
-pm_status scan_u32(pm_context* c, const uint32_t* in, int64_t n, int64_t* out);
+// exclusive scans into int64 out[n+1]; bsum: room for the block sums (nullable: scratch)
+pm_status scan_u32(pm_context* c, const uint32_t* in, int64_t n, int64_t* out,
+                   int64_t* bsum = nullptr);
 // codec (pm_codec.hip)
 pm_status run_encode(pm_context* c, const pm_species* in, pm_species* out, int64_t* perm);
 pm_status run_decode(pm_context* c, const pm_species* in, pm_species* out);

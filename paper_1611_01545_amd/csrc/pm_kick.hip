@@ -1389,7 +1389,7 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
   uint32_t* aidx = (uint32_t*)scratch(c, SC_VALA, nn * 4);
   uint32_t* abuf = (uint32_t*)scratch(c, SC_VALB, nn * 4);
   uint32_t* mcnt = (uint32_t*)scratch(c, SC_MCNT, (size_t)nbrick * 4 * n_sp);
-  int32_t* part = (int32_t*)scratch(c, SC_PARTS, (size_t)nbrick * 8 * n_sp);
+  int32_t* part = (int32_t*)scratch(c, SC_KPART, (size_t)nbrick * 8 * n_sp);
   const int64_t nbs = cdiv(nbrick, BS_TILE);
   BrickSum* bsum = (BrickSum*)scratch(c, SC_BSUM, (size_t)nbs * n_sp * sizeof(BrickSum));
   if (!cnt || !bstart || !astart || !acnt || !ecnt || !tpos || !tvel || !tdig || !mkey ||

@@ -258,7 +258,7 @@ pm_status scan_batch(pm_context* c, const ScanArgs<Get>& A, int nbatch, int64_t 
 }
 
 template <typename Get>
-pm_status scan_generic(pm_context* c, Get g, int64_t n, int64_t* out) {
+pm_status scan_generic(pm_context* c, Get g, int64_t n, int64_t* out, int64_t* bsum = nullptr) {
   if (n == 0) {
     hipLaunchKernelGGL(k_fill<int64_t>, dim3(1), dim3(64), 0, c->stream, out, 1, (int64_t)0);
     PM_LAUNCH_CHECK();
@@ -267,7 +267,7 @@ pm_status scan_generic(pm_context* c, Get g, int64_t n, int64_t* out) {
   ScanArgs<Get> A{};
   A.g[0] = g;
   A.out[0] = out;
-  return scan_batch(c, A, 1, n);
+  return scan_batch(c, A, 1, n, bsum);
 }
 
 }  // namespace pmscan

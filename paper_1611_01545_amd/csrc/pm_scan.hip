@@ -83,6 +83,6 @@ pm_status launch_fill_u64(pm_context* c, uint64_t* p, int64_t n, uint64_t v) {
   return PM_OK;
 }
 
-pm_status scan_u32(pm_context* c, const uint32_t* in, int64_t n, int64_t* out) {
-  return scan_generic(c, GetU32{in}, n, out);
+pm_status scan_u32(pm_context* c, const uint32_t* in, int64_t n, int64_t* out, int64_t* bsum) {
+  return scan_generic(c, GetU32{in}, n, out, bsum);
 }
