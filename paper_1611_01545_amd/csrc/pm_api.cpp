@@ -151,6 +151,7 @@ pm_status pm_create(const pm_config* cfg, void* stream, pm_ctx* out) {
   pm_status s = PM_OK;
   if (hipMalloc(&c->err, sizeof(DevErr)) != hipSuccess ||
       hipMalloc(&c->amax, 64) != hipSuccess ||
+      hipMalloc(&c->room, unpack_room_bytes()) != hipSuccess ||
       hipMalloc(&c->nyq, (size_t)3 * ng * ng * sizeof(float2)) != hipSuccess) {
     s = PM_ERR_NOMEM;
   }
@@ -180,9 +181,9 @@ pm_status pm_query_sizes(const pm_config* cfg, int64_t n_max, int n_sp, pm_sizes
   auto grown = [](int64_t b) { return b + b / 8; };
   *out = pm_sizes{};
   // pm_create: kernel tables (by |n|^2 and the octant copy), twiddles, gradient symbol,
-  // three Nyquist planes, error word and max |a|
+  // three Nyquist planes, error word, max |a| and pm_unpack's room
   out->context_bytes = (3 * (ng / 2) * (ng / 2) + 1) * 4 + h1 * h1 * h1 * 4 + ng * 8 + ng * 4 +
-                       3 * n2 * 8 + (int64_t)sizeof(DevErr) + 64;
+                       3 * n2 * 8 + (int64_t)sizeof(DevErr) + 64 + (int64_t)unpack_room_bytes();
   out->step_mesh_bytes = 3 * n3 * 4;
   // pm_encode / pm_step of N particles in n_sp species
   const int64_t rs_blocks = N / 4096 + 1;  // radix-sort tiles of the encode
@@ -236,6 +237,7 @@ pm_status pm_destroy(pm_ctx c) {
   hipFree(c->nyq);
   hipFree(c->err);
   hipFree(c->amax);
+  hipFree(c->room);
   for (auto& b : c->scratch)
     if (b.p) hipFree(b.p);
   for (auto e : c->prof_pool) hipEventDestroy(e);

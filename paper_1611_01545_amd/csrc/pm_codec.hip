@@ -599,15 +599,16 @@ __global__ __launch_bounds__(T256) void k_checksum(const uint8_t* b, int64_t n, 
 
 // Records of a byte stream into the species' arrays. A workgroup takes UT consecutive cells,
 // whose first byte and first particle the host found as it walked the counts; the counts
-// give the other cells' places. b: bytes from body byte `at` on.
+// give the other cells' places. b: bytes from body byte `at` on; only the records that start
+// in body bytes [at, end) are taken (all of them are there).
 constexpr int UT = 64;
 struct UnpackTile {
   int64_t byte, part;
 };
 template <int P, int V>
 __global__ __launch_bounds__(T256) void k_unpack_cells(const uint8_t* b, int64_t at,
-                                                      const UnpackTile* tiles, int64_t cell0,
-                                                      int64_t ncell, GetCount counts, void* pos_,
+                                                      int64_t end, const UnpackTile* tiles,
+                                                      int64_t cell0, int64_t ncell, GetCount counts, void* pos_,
                                                       void* vel_, pm_shdr* h) {
   constexpr int RB = 3 * (P + V);
   typename PosCode<P>::T* pos = (typename PosCode<P>::T*)pos_;
@@ -628,7 +629,17 @@ __global__ __launch_bounds__(T256) void k_unpack_cells(const uint8_t* b, int64_t
   __syncthreads();
   const uint8_t* src = b + (t.byte - at);
   int jmin = 65536, jmax = -1;
-  for (int64_t q = threadIdx.x; q < part[UT]; q += T256) {
+  // the tile's first record that starts at body byte p or later
+  auto first_from = [&](int64_t p) -> int64_t {
+    p -= t.byte;
+    int c = 0;
+#pragma unroll
+    for (int d = UT / 2; d >= 1; d >>= 1) c += byte[c + d] <= p ? d : 0;
+    const int64_t k = p > byte[c] ? (p - byte[c] + RB - 1) / RB : 0;
+    return min(part[c] + k, part[c + 1]);
+  };
+  const int64_t q1 = first_from(end);
+  for (int64_t q = first_from(at) + threadIdx.x; q < q1; q += T256) {
     int lo = 0;  // the largest cell with part[lo] <= q
 #pragma unroll
     for (int d = UT / 2; d >= 1; d >>= 1) lo += part[lo + d] <= q ? d : 0;
@@ -1030,17 +1041,38 @@ struct DevMem {
     if (p) hipFree(p);
   }
 };
+// Device memory of an unpack: a table of cell runs, the checksum, and room for stream bytes
+struct UnpackRoom {
+  UnpackTile* tab;
+  uint64_t* sum;
+  uint8_t* buf;
+  int64_t tabs, size;
+  UnpackRoom(void* p, int64_t n, int64_t bytes) : tabs(n), size(bytes) {
+    tab = (UnpackTile*)p;
+    sum = (uint64_t*)(tab + n);
+    buf = (uint8_t*)(sum + 2);
+  }
+  static size_t need(int64_t n, int64_t bytes) {
+    return (size_t)n * sizeof(UnpackTile) + 16 + (size_t)bytes;
+  }
+};
+constexpr int64_t ROOM_TABS = 4096, ROOM_BYTES = (int64_t)1 << 20;  // the context's own
 }  // namespace
+
+size_t unpack_room_bytes() { return UnpackRoom::need(ROOM_TABS, ROOM_BYTES); }
 
 // Only the chain of counts is sequential: the host follows it (one byte per cell) while the
 // body goes to the GPU, which sums it and takes the records apart. Two species of 256^3 and
 // 128^3 particles on 128^3 cells (176 MB), with their decode: 11.2 ms, against 178 ms with
-// the host's parse of every byte. What is left is the walk (7 ns a cell) and the upload
-// from pageable memory (30 GB/s), which run side by side. Bodies beyond
-// UNPACK_CHUNK go through a buffer of that size, once to be summed and once to be parsed.
+// the host's parse of every byte. What is left is the walk and the upload from pageable memory
+// (30 GB/s), which run side by side. Bodies up to 1 MB go through the context's own room,
+// larger ones through an allocation of up to 256 MB for the call, or, where the card has none
+// left, through that room too; a body beyond the room goes through it in pieces, once to be
+// summed and once to be parsed. Nothing of the destination is written before everything that
+// can be refused has been looked at.
 pm_status run_unpack(pm_context* c, const uint8_t* body, int64_t blen, uint64_t csum,
                      float vmax, pm_species* out) {
-  constexpr int64_t UNPACK_CHUNK = (int64_t)256 << 20;
+  constexpr int64_t CHUNK = (int64_t)256 << 20, CHUNK_TABS = 65536;
   const int64_t ncell = c->g.ncell3;
   const int P = width_pos(*out), V = width_vel(*out);
   BodyWalk w;
@@ -1063,24 +1095,32 @@ pm_status run_unpack(pm_context* c, const uint8_t* body, int64_t blen, uint64_t 
   } join{helper};
   if (!walked) walk();
 
-  DevMem chunk, sum;
-  const int64_t size = std::max<int64_t>(std::min(blen, UNPACK_CHUNK), 16);
-  if (hipMalloc(&chunk.p, (size_t)size) != hipSuccess || hipMalloc(&sum.p, 8) != hipSuccess) {
-    (void)hipGetLastError();
-    return PM_ERR_NOMEM;
+  UnpackRoom r(c->room, ROOM_TABS, ROOM_BYTES);
+  DevMem more;
+  if (blen > r.size) {
+    const int64_t tabs = std::min(cdiv(ncell, UT), CHUNK_TABS), size = std::min(blen, CHUNK);
+    if (hipMalloc(&more.p, UnpackRoom::need(tabs, size)) == hipSuccess) {
+      r = UnpackRoom(more.p, tabs, size);
+    } else {
+      more.p = nullptr;
+      (void)hipGetLastError();
+    }
   }
-  hipLaunchKernelGGL(k_fill<uint64_t>, dim3(1), dim3(64), 0, c->stream, (uint64_t*)sum.p,
-                     (int64_t)1, (uint64_t)0);
-  for (int64_t at = 0; at < blen; at += size) {
-    const int64_t n = std::min(size, blen - at);
-    PM_HIP_CHECK(hipMemcpyAsync(chunk.p, body + at, (size_t)n, hipMemcpyHostToDevice, c->stream));
+  auto up = [&](void* d, const void* s, int64_t n) {
+    return hipMemcpyAsync(d, s, (size_t)n, hipMemcpyHostToDevice, c->stream);
+  };
+  hipLaunchKernelGGL(k_fill<uint64_t>, dim3(1), dim3(64), 0, c->stream, r.sum, (int64_t)1,
+                     (uint64_t)0);
+  for (int64_t at = 0; at < blen; at += r.size) {
+    const int64_t n = std::min(r.size, blen - at);
+    PM_HIP_CHECK(up(r.buf, body + at, n));
     hipLaunchKernelGGL(k_checksum, dim3((unsigned)std::min<int64_t>(cdiv(n, 16 * T256), CS_BLOCKS)),
-                       dim3(T256), 0, c->stream, (const uint8_t*)chunk.p, n, at,
-                       (unsigned long long*)sum.p);
+                       dim3(T256), 0, c->stream, (const uint8_t*)r.buf, n, at,
+                       (unsigned long long*)r.sum);
     PM_LAUNCH_CHECK();
   }
   uint64_t got = 0;
-  PM_HIP_CHECK(hipMemcpyAsync(&got, sum.p, 8, hipMemcpyDeviceToHost, c->stream));
+  PM_HIP_CHECK(hipMemcpyAsync(&got, r.sum, 8, hipMemcpyDeviceToHost, c->stream));
   PM_HIP_CHECK(hipStreamSynchronize(c->stream));
   if (helper.joinable()) helper.join();
   if (w.nomem) return PM_ERR_NOMEM;
@@ -1096,48 +1136,37 @@ pm_status run_unpack(pm_context* c, const uint8_t* body, int64_t blen, uint64_t 
   h.j_min = 65536;
   h.j_max = -1;
   h.n_esc = n_esc;
-  auto up = [&](void* d, const void* s, size_t n) {
-    return hipMemcpyAsync(d, s, n, hipMemcpyHostToDevice, c->stream);
-  };
   PM_HIP_CHECK(up(out->hdr, &h, sizeof(h)));
-  PM_HIP_CHECK(up(out->count, w.count.data(), (size_t)ncell));
-  if (n_esc > 0) PM_HIP_CHECK(up(out->esc, w.esc.data(), w.esc.size() * 8));
+  PM_HIP_CHECK(up(out->count, w.count.data(), ncell));
+  if (n_esc > 0) PM_HIP_CHECK(up(out->esc, w.esc.data(), n_esc * 16));
+  const int64_t nt = (int64_t)w.tiles.size() - 1;
+  const int64_t over = 3 * (P + V) - 1;  // bytes of a record that may lie beyond a piece
   pm_status st = PM_OK;
-  if (out->n > 0) {
-    const int64_t nt = (int64_t)w.tiles.size() - 1;
-    DevMem tiles, big;
-    if (hipMalloc(&tiles.p, (size_t)nt * sizeof(UnpackTile)) != hipSuccess ||
-        (w.largest > size && hipMalloc(&big.p, (size_t)w.largest) != hipSuccess)) {
-      (void)hipGetLastError();
-      st = PM_ERR_NOMEM;
-    }
-    uint8_t* buf = (uint8_t*)(big.p ? big.p : chunk.p);
-    const int64_t room = std::max(size, w.largest);
-    if (st == PM_OK && up(tiles.p, w.tiles.data(), (size_t)nt * sizeof(UnpackTile)) != hipSuccess)
-      st = PM_ERR_DEVICE;
-    for (int64_t t0 = 0, t1 = 0; st == PM_OK && t0 < nt; t0 = t1) {
-      const int64_t at = blen <= size ? 0 : w.tiles[t0].byte;
-      if (blen <= size) t1 = nt;  // the body is there
-      else
-        while (t1 < nt && w.tiles[t1 + 1].byte - at <= room) ++t1;
-      if (blen > size && up(buf, body + at, (size_t)(w.tiles[t1].byte - at)) != hipSuccess) {
+  for (int64_t at = 0, t0 = 0, t1 = 0; st == PM_OK && out->n > 0 && at < blen;) {
+    const int64_t n = std::min(r.size, blen - at);
+    const int64_t end = at + n == blen ? blen : at + n - over;
+    if (blen > r.size && up(r.buf, body + at, n) != hipSuccess) st = PM_ERR_DEVICE;
+    while (t0 < nt && w.tiles[t0 + 1].byte <= at) ++t0;
+    while (t1 < nt && w.tiles[t1].byte < end) ++t1;
+    for (int64_t t = t0; t < t1 && st == PM_OK; t += r.tabs) {
+      const int64_t m = std::min(r.tabs, t1 - t);
+      if (up(r.tab, w.tiles.data() + t, m * (int64_t)sizeof(UnpackTile)) != hipSuccess) {
         st = PM_ERR_DEVICE;
         break;
       }
       st = width_dispatch(width_kind(*out), [&](auto P_, auto V_) {
         hipLaunchKernelGGL((k_unpack_cells<decltype(P_)::value, decltype(V_)::value>),
-                           dim3((unsigned)(t1 - t0)), dim3(T256), 0, c->stream, buf, at,
-                           (const UnpackTile*)tiles.p + t0, t0 * UT, ncell,
+                           dim3((unsigned)m), dim3(T256), 0, c->stream, (const uint8_t*)r.buf, at,
+                           end, (const UnpackTile*)r.tab, t * UT, ncell,
                            GetCount{out->count, out->esc, out->hdr}, (void*)out->pos,
                            (void*)out->vel, out->hdr);
         return hipGetLastError() == hipSuccess ? PM_OK : PM_ERR_DEVICE;
       });
     }
-    if (hipStreamSynchronize(c->stream) != hipSuccess && st == PM_OK) st = PM_ERR_DEVICE;
-    return st;
+    at = end;
   }
-  PM_HIP_CHECK(hipStreamSynchronize(c->stream));
-  return PM_OK;
+  if (hipStreamSynchronize(c->stream) != hipSuccess && st == PM_OK) st = PM_ERR_DEVICE;
+  return st;
 }
 
 pm_status scan_generic_pack(pm_context* c, const int64_t* off, int64_t n, int64_t* out,

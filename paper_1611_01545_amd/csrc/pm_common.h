@@ -129,6 +129,7 @@ struct pm_context {
   float2* nyq = nullptr;
   DevErr* err = nullptr;
   float* amax = nullptr;  // device scalar
+  void* room = nullptr;   // pm_unpack's own device memory (unpack_room_bytes)
   // grow-on-demand scratch
   DevBuf scratch[40];
   // this device's fixed array of pm_reduce_noalloc (device address, set by pm_create)
@@ -238,6 +239,7 @@ pm_status run_pack(pm_context* c, const pm_species* sp, int32_t sid, uint8_t* bu
 // body: the stream after its header, in host memory (synchronous)
 pm_status run_unpack(pm_context* c, const uint8_t* body, int64_t blen, uint64_t csum,
                      float vmax, pm_species* out);
+size_t unpack_room_bytes();
 pm_status run_reduce(pm_context* c, const pm_species* sp, int n_sp, const float* rho,
                      const float* acc, double* out);
 // the same reductions with every buffer in a fixed device array (no allocation)
