@@ -193,7 +193,8 @@ pm_status pm_query_sizes(const pm_config* cfg, int64_t n_max, int n_sp, pm_sizes
   st += n_sp * grown((nc3 + 1) * 8);                    // cell offsets per species
   st += grown((nc3 + 1) * 8);                           // decode/pack offsets
   st += grown(n_sp * (nb + 1) * 8) + grown(n_sp * (nb + 1) * 4);  // re-sort: brick starts
-  st += 2 * grown(n_sp * nb * 4) + grown(n_sp * nb * 4 + 16);  // movers, arrivals, escapes
+  st += grown(n_sp * nb * 4) + grown(n_sp * nb * 4 + 16);  // movers, escapes
+  st += grown(n_sp * std::max<int64_t>(nb, std::min<int64_t>(32 * nb, 1 << 20)) * 4);  // arrivals
   st += grown(nc3 * 4 * n_sp);                          // stayers per cell
   st += grown(nc3 * 4) * 2 + grown((nc3 + 1) * 8);      // encode: counts, escapes
   st += 2 * grown(NP * 6) + grown(NP * 2);              // new codes and digits, old order
@@ -203,7 +204,7 @@ pm_status pm_query_sizes(const pm_config* cfg, int64_t n_max, int n_sp, pm_sizes
   st += grown(rs_blocks * 256 * 4);                     // radix histograms, their offsets
   st += grown((rs_blocks * 256 + 1 + rs_blocks * 256 / 4096 + 1) * 8);
   st += grown(std::max<int64_t>((nc3 / 4096 + 1) * n_sp * 8,
-                                (nb / 4096 + 1) * n_sp * 24));  // block sums of the scans
+                                (nb / 1024 + 1) * n_sp * 24));  // block sums of the scans
   st += grown(4096) + grown(512 * 25 * 8);              // folds, reductions
   st += grown(N * 12 + n_sp * 256);                     // extra accelerations (PP, long range)
   out->step_scratch_bytes = st;

@@ -198,7 +198,7 @@ enum ScratchId {
   SC_PPMAX,        // per-workgroup max |a| of the PP force
   SC_PPACC,        // float [N][3] PP accelerations of pm_step_pp
   SC_LRACC,        // float [N][3] long-range accelerations of pm_step_p3m
-  SC_ACNT,         // uint32 [nbrick] per species: arrivals of each brick (re-sort)
+  SC_ACNT,         // uint32 [nbrick << apad] per species: arrivals of each brick (re-sort)
   SC_N
 };
 

@@ -136,7 +136,7 @@ struct KickSpecies {
   uint32_t* mkey;      // movers: new cell key, at the old stream index
   uint32_t* cnt;       // stayers per cell
   uint32_t* mcnt;      // movers per brick
-  uint32_t* acnt;      // arrivals per brick
+  uint32_t* acnt;      // arrivals per brick (2^apad words apart)
   int32_t* pmn;        // per-brick extreme new velocity codes, folded into hout
   int32_t* pmx;
   const float* app;    // nullable: per-particle acceleration added to the mesh force
@@ -146,6 +146,7 @@ struct KickArgs {
   int n_sp;
   const float* acc;  // [3][ng^3], or the potential [ng^3] (k_kick_pair with PHI)
   float scale;       // of its difference: ng / 12
+  int apad;
   float ck;
   double cdS;        // c_d S / L (position codes per unit velocity)
 };
@@ -258,7 +259,7 @@ __device__ inline void kick_lane(const KickSpecies& S, const KickArgs& A, const 
       const uint32_t key = cell_key(g, un[0] >> SH, un[1] >> SH, un[2] >> SH);
       S.mkey[j] = key;
       atomicAdd(mvc, 1u);
-      atomicAdd(&S.acnt[key >> (3 * g.lgB)], 1u);
+      atomicAdd(&S.acnt[(key >> (3 * g.lgB)) << A.apad], 1u);
     }
   }
 }
@@ -834,20 +835,24 @@ struct PlaceSpecies {
 };
 struct PlaceArgs {
   PlaceSpecies sp[MAXSP];
+  int apad;
 };
+constexpr int64_t APAD_WORDS = 1 << 20;
 
 // First new stream position and first arrival of every brick: exclusive prefixes of the
 // bricks' new particle counts (old particles less movers plus arrivals) and of their
 // arrivals. One launch up to BS_TILE bricks; beyond that k_brick_sums first leaves each
-// block's sums, and a block of k_brick_scan adds up those before its own. The extreme
-// velocity codes ride along and end in the header.
-constexpr int BS_T = 1024, BS_I = 4, BS_TILE = BS_T * BS_I;
+// block's sums, and a block of k_brick_scan adds up those before its own (at most 2048: a kick
+// of more than 2^21 bricks exceeds the largest grid). The extreme velocity codes ride along
+// and end in the header. A brick per thread: the loads of distant offsets and counters are
+// what takes the time (32768 bricks, sums and scan 36 us with four per thread, 18 with one).
+constexpr int BS_T = 1024, BS_I = 1, BS_TILE = BS_T * BS_I;
 struct BrickSum {
   int64_t tot, arr;
   int32_t mn, mx;
 };
 
-__device__ inline void brick_items(const PlaceSpecies& S, int B3, int64_t nbrick, int64_t b0,
+__device__ inline void brick_items(const PlaceSpecies& S, int apad, int B3, int64_t nbrick, int64_t b0,
                                    uint32_t t[BS_I], uint32_t a[BS_I], int& mn, int& mx) {
   mn = 65536;
   mx = -1;
@@ -857,7 +862,7 @@ __device__ inline void brick_items(const PlaceSpecies& S, int B3, int64_t nbrick
     t[k] = a[k] = 0;
     if (b >= nbrick) continue;
     const int64_t j0 = min(S.off[b * B3], S.n), j1 = min(S.off[(b + 1) * B3], S.n);
-    a[k] = S.acnt[b];
+    a[k] = S.acnt[b << apad];
     const int64_t v = (j1 > j0 ? j1 - j0 : 0) - (int64_t)S.mcnt[b] + (int64_t)a[k];
     t[k] = (uint32_t)(v > 0 ? v : 0);
     mn = min(mn, S.pmn[b]);
@@ -890,7 +895,7 @@ __global__ __launch_bounds__(BS_T) void k_brick_sums(PlaceArgs A, int B3, int64_
   __shared__ int sm[32];
   uint32_t t[BS_I], a[BS_I];
   int mn, mx;
-  brick_items(A.sp[blockIdx.y], B3, nbrick, (int64_t)blockIdx.x * BS_TILE + threadIdx.x * BS_I,
+  brick_items(A.sp[blockIdx.y], A.apad, B3, nbrick, (int64_t)blockIdx.x * BS_TILE + threadIdx.x * BS_I,
               t, a, mn, mx);
   int64_t st = 0, sa = 0, tt, ta;
 #pragma unroll
@@ -912,7 +917,7 @@ __global__ __launch_bounds__(BS_T) void k_brick_scan(PlaceArgs A, int B3, int64_
   const int64_t b0 = (int64_t)blockIdx.x * BS_TILE + threadIdx.x * BS_I;
   uint32_t t[BS_I], a[BS_I];
   int mn, mx;
-  brick_items(S, B3, nbrick, b0, t, a, mn, mx);
+  brick_items(S, A.apad, B3, nbrick, b0, t, a, mn, mx);
   int64_t pt = 0, pa = 0;  // the sums of the blocks before this one
   if (gridDim.x > 1) {
     const BrickSum* bs = sums + (int64_t)blockIdx.y * gridDim.x;
@@ -1009,7 +1014,7 @@ __global__ __launch_bounds__(KT) void k_list_arrivals(PlaceArgs A, int lgB3, int
     // counts inconsistent with n (latched by the offset check) leave stale digits
     const bool ok = b < nbrick;
     const uint32_t first = S.astart[ok ? b : 0];
-    const uint32_t left = ok ? atomicSub(&S.acnt[b], 1u) : 0u;
+    const uint32_t left = ok ? atomicSub(&S.acnt[b << A.apad], 1u) : 0u;
     const int64_t slot = left ? (int64_t)first + left - 1 : S.n;
     if (slot < S.n) S.aidx[slot] = (uint32_t)j;
     else latch_error(err, ERRBIT_CORRUPT);
@@ -1380,7 +1385,12 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
   uint32_t* cnt = (uint32_t*)scratch(c, SC_CNT, (size_t)g.ncell3 * 4 * n_sp);
   int64_t* bstart = (int64_t*)scratch(c, SC_OFF2, (size_t)(nbrick + 1) * 8 * n_sp);
   uint32_t* astart = (uint32_t*)scratch(c, SC_ASTART, (size_t)(nbrick + 1) * 4 * n_sp);
-  uint32_t* acnt = (uint32_t*)scratch(c, SC_ACNT, (size_t)nbrick * 4 * n_sp);
+  // Arrival counters in cache lines of their own up to 4 MB: atomics on one line follow one
+  // another. 4096 bricks, 16.8 M particles of which few leave them: listing 131 -> 34 us; all
+  // leave: listing 2580 -> 540, kick 2550 -> 930. 32768 bricks, all leave: kick 1425 -> 735.
+  int apad = 0;
+  while (apad < 5 && nbrick << (apad + 1) <= APAD_WORDS) ++apad;
+  uint32_t* acnt = (uint32_t*)scratch(c, SC_ACNT, (size_t)(nbrick << apad) * 4 * n_sp);
   uint32_t* ecnt = (uint32_t*)scratch(c, SC_ECNT, ((size_t)nbrick * n_sp + MAXSP) * 4);
   char* tpos = (char*)scratch(c, SC_TPOS, nn * 3 * P);
   char* tvel = (char*)scratch(c, SC_TVEL, nn * 3 * V);
@@ -1399,11 +1409,13 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
   PrepArgs R{};
   R.n_sp = n_sp;
   PlaceArgs Q{};
+  Q.apad = apad;
   int64_t nmax = 0;
   KickArgs A{};
   A.n_sp = n_sp;
   A.acc = acc;
   A.scale = grad_scale(g.ng);
+  A.apad = apad;
   A.ck = (float)ck;
   A.cdS = cd * g.SL * (P == 1 ? 1.0 : 256.0);
   for (int s = 0; s < n_sp; ++s) {
@@ -1420,7 +1432,7 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
     S.cnt = cnt + (int64_t)s * g.ncell3;
     S.mkey = mkey + nbase[s];
     S.mcnt = mcnt + (int64_t)s * g.nbrick;
-    S.acnt = acnt + (int64_t)s * g.nbrick;
+    S.acnt = acnt + (s * nbrick << apad);
     S.pmn = part + (int64_t)2 * s * g.nbrick;
     S.pmx = S.pmn + g.nbrick;
     S.app = app ? app[s] : nullptr;
@@ -1455,7 +1467,7 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
     L.perm = perm ? perm[s] : nullptr;
   }
   {
-    const int64_t na = nbrick * n_sp;
+    const int64_t na = n_sp * (nbrick << apad);
     hipLaunchKernelGGL(k_kick_prep<V>, dim3((unsigned)std::min<int64_t>(cdiv(na, KT), 1024)),
                        dim3(KT), 0, c->stream, R, amax, ck, acnt, na, nesc);
     ProfScope ps(c, ST_KICK);
