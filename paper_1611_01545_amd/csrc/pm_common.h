@@ -194,11 +194,11 @@ enum ScratchId {
   SC_KPART,        // int32 [2][nbrick] per species: extreme new velocity codes (kick)
   SC_SPEC,         // float [ng^3] spectrum scratch of the force transforms
   SC_FOLD,         // first-stage results of the grid min / max folds
-  SC_ECNT,         // uint32 [nbrick] per species: escapes of each brick, then 4 totals
+  SC_ECNT,         // uint32 [nbrick] per species: escapes of each brick
   SC_PPMAX,        // per-workgroup max |a| of the PP force
   SC_PPACC,        // float [N][3] PP accelerations of pm_step_pp
   SC_LRACC,        // float [N][3] long-range accelerations of pm_step_p3m
-  SC_ACNT,         // uint32 [nbrick << apad] per species: arrivals of each brick (re-sort)
+  SC_ACNT,         // uint32: arrivals of each brick and what else a re-sort clears
   SC_N
 };
 

@@ -91,10 +91,9 @@ struct PrepArgs {
 };
 template <int VB = 2>  // velocity bytes per axis
 __global__ __launch_bounds__(KT) void k_kick_prep(PrepArgs A, const float* amax, double ck,
-                                                 uint32_t* acnt, int64_t nacnt,
-                                                 uint32_t* nesc) {
-  for (int64_t i = (int64_t)blockIdx.x * KT + threadIdx.x; i < nacnt; i += (int64_t)gridDim.x * KT)
-    acnt[i] = 0u;
+                                                 uint32_t* clear, int64_t nclear) {
+  for (int64_t i = (int64_t)blockIdx.x * KT + threadIdx.x; i < nclear; i += (int64_t)gridDim.x * KT)
+    clear[i] = 0u;
   if (blockIdx.x || (int)threadIdx.x >= A.n_sp) return;
   const pm_shdr* hin = A.hin[threadIdx.x];
   pm_shdr* hout = A.hout[threadIdx.x];
@@ -117,7 +116,6 @@ __global__ __launch_bounds__(KT) void k_kick_prep(PrepArgs A, const float* amax,
   hout->flags = 0;
   hout->n_esc = 0;
   hout->reserved = 0;
-  nesc[threadIdx.x] = 0u;
 }
 
 constexpr int KB = 512;  // threads per workgroup of the brick kicks
@@ -824,7 +822,8 @@ struct PlaceSpecies {
   uint32_t* aidx;          // old stream indices of the arrivals, by brick
   uint32_t* abuf;          // the same size, for sorting long lists
   uint32_t* ecnt;          // cells of 255 and more per brick
-  uint32_t* nesc;          // their total
+  uint32_t* etile;         // the same per ET bricks
+  uint32_t* tot;           // their total
   pm_shdr* hout;
   void* pos;
   void* vel;
@@ -837,6 +836,7 @@ struct PlaceArgs {
   PlaceSpecies sp[MAXSP];
   int apad;
 };
+constexpr int ET = 4096;
 constexpr int64_t APAD_WORDS = 1 << 20;
 
 // First new stream position and first arrival of every brick: exclusive prefixes of the
@@ -1234,7 +1234,10 @@ __global__ __launch_bounds__(NW == 1 ? 64 * WB : 64 * NW) void k_place(
     }
     if (tid == 0) {
       S.ecnt[b] = (uint32_t)ne;
-      if (ne) atomicAdd(S.nesc, (uint32_t)ne);
+      if (ne) {
+        atomicAdd(&S.tot[0], (uint32_t)ne);
+        atomicAdd(&S.etile[b / ET], (uint32_t)ne);
+      }
     }
   }
   sync();
@@ -1302,34 +1305,40 @@ __global__ __launch_bounds__(NW == 1 ? 64 * WB : 64 * NW) void k_place(
 }
 
 // The escape table in cell order (cells of 255 particles and more are rare: without any,
-// every workgroup returns after one load). Workgroup x takes a range of bricks; the
-// escapes before it are the sum of the earlier bricks' counts.
-__global__ __launch_bounds__(KT) void k_escape_table(PlaceArgs A, int B3, int64_t nbrick,
+// every workgroup returns after one load). A workgroup takes ET bricks at a time; the escapes
+// before them are the sum of the earlier tiles' counts, at most 512, one load per thread.
+// (Adding up every earlier brick's count took the last workgroup 1024 rounds at 1024^3: 291 us
+// with 400 escapes, 36 this way.)
+constexpr int RT = 1024;
+__global__ __launch_bounds__(RT) void k_escape_table(PlaceArgs A, int B3, int64_t nbrick,
                                                     DevErr* err) {
   const PlaceSpecies& S = A.sp[blockIdx.y];
-  const uint32_t total = *S.nesc;
+  const uint32_t total = S.tot[0];
   if (total == 0) return;  // the header's n_esc is 0 already
-  __shared__ int64_t lw[KT / 64 + 1];
-  const int64_t per = (nbrick + gridDim.x - 1) / gridDim.x;
-  const int64_t q0 = min((int64_t)blockIdx.x * per, nbrick), q1 = min(q0 + per, nbrick);
-  int64_t before = 0, tot;
-  for (int64_t b = threadIdx.x; b < q0; b += KT) before += S.ecnt[b];
-  pmscan::block_excl_scan(before, lw, &tot);
-  int64_t at = tot;
-  for (int64_t b0 = q0; b0 < q1; b0 += KT) {
-    const int64_t b = b0 + threadIdx.x;
-    const uint32_t ne = b < q1 ? S.ecnt[b] : 0u;
-    int64_t k = at + pmscan::block_excl_scan((int64_t)ne, lw, &tot);
-    at += tot;
-    if (!ne) continue;
-    for (int64_t i = b * B3; i < (b + 1) * B3; ++i)
-      if (S.count[i] == 255) {
-        if (k < S.cap_esc) {
-          S.esc[2 * k] = (uint64_t)i;
-          S.esc[2 * k + 1] = (uint64_t)S.cnt[i];
+  __shared__ int64_t lw[RT / 64 + 1];
+  const int64_t nt = (nbrick + ET - 1) / ET;
+  for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
+    if (S.etile[t] == 0) continue;
+    int64_t before = 0, tot;
+    for (int64_t q = threadIdx.x; q < t; q += RT) before += S.etile[q];
+    pmscan::block_excl_scan(before, lw, &tot);
+    int64_t at = tot;
+    const int64_t q1 = min((t + 1) * ET, nbrick);
+    for (int64_t b0 = t * ET; b0 < q1; b0 += RT) {
+      const int64_t b = b0 + threadIdx.x;
+      const uint32_t ne = b < q1 ? S.ecnt[b] : 0u;
+      int64_t k = at + pmscan::block_excl_scan((int64_t)ne, lw, &tot);
+      at += tot;
+      if (!ne) continue;
+      for (int64_t i = b * B3; i < (b + 1) * B3; ++i)
+        if (S.count[i] == 255) {
+          if (k < S.cap_esc) {
+            S.esc[2 * k] = (uint64_t)i;
+            S.esc[2 * k + 1] = (uint64_t)S.cnt[i];
+          }
+          ++k;
         }
-        ++k;
-      }
+    }
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     S.hout->n_esc = (int64_t)total;
@@ -1390,8 +1399,11 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
   // leave: listing 2580 -> 540, kick 2550 -> 930. 32768 bricks, all leave: kick 1425 -> 735.
   int apad = 0;
   while (apad < 5 && nbrick << (apad + 1) <= APAD_WORDS) ++apad;
-  uint32_t* acnt = (uint32_t*)scratch(c, SC_ACNT, (size_t)(nbrick << apad) * 4 * n_sp);
-  uint32_t* ecnt = (uint32_t*)scratch(c, SC_ECNT, ((size_t)nbrick * n_sp + MAXSP) * 4);
+  // what every call clears: the arrival counters, and per species the escapes' tiles and total
+  const int64_t ntile = cdiv(nbrick, ET);
+  const int64_t nclear = n_sp * ((nbrick << apad) + ntile + 1);
+  uint32_t* acnt = (uint32_t*)scratch(c, SC_ACNT, (size_t)nclear * 4);
+  uint32_t* ecnt = (uint32_t*)scratch(c, SC_ECNT, (size_t)nbrick * n_sp * 4);
   char* tpos = (char*)scratch(c, SC_TPOS, nn * 3 * P);
   char* tvel = (char*)scratch(c, SC_TVEL, nn * 3 * V);
   uint16_t* tdig = (uint16_t*)scratch(c, SC_TDST, nn * 2);
@@ -1405,7 +1417,8 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
   if (!cnt || !bstart || !astart || !acnt || !ecnt || !tpos || !tvel || !tdig || !mkey ||
       !aidx || !abuf || !mcnt || !part || !bsum)
     return PM_ERR_NOMEM;
-  uint32_t* nesc = ecnt + nbrick * n_sp;
+  uint32_t* etile = acnt + n_sp * (nbrick << apad);
+  uint32_t* tot = etile + n_sp * ntile;
   PrepArgs R{};
   R.n_sp = n_sp;
   PlaceArgs Q{};
@@ -1457,7 +1470,8 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
     L.aidx = aidx + nbase[s];
     L.abuf = abuf + nbase[s];
     L.ecnt = ecnt + s * nbrick;
-    L.nesc = nesc + s;
+    L.etile = etile + s * ntile;
+    L.tot = tot + s;
     L.hout = out[s].hdr;
     L.pos = out[s].pos;
     L.vel = out[s].vel;
@@ -1467,9 +1481,8 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
     L.perm = perm ? perm[s] : nullptr;
   }
   {
-    const int64_t na = n_sp * (nbrick << apad);
-    hipLaunchKernelGGL(k_kick_prep<V>, dim3((unsigned)std::min<int64_t>(cdiv(na, KT), 1024)),
-                       dim3(KT), 0, c->stream, R, amax, ck, acnt, na, nesc);
+    hipLaunchKernelGGL(k_kick_prep<V>, dim3((unsigned)std::min<int64_t>(cdiv(nclear, KT), 1024)),
+                       dim3(KT), 0, c->stream, R, amax, ck, acnt, nclear);
     ProfScope ps(c, ST_KICK);
     const int RN = g.B * g.r;
     const size_t tail = (size_t)MAXSP * (B3 + 1) * 4 * 2;
@@ -1514,8 +1527,8 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
     hipLaunchKernelGGL((k_place<P, V, 1>), dim3((unsigned)cdiv(nbrick, WB), ny), dim3(64 * WB),
                        (size_t)WB * (ACAP + ((B3 + 3) & ~3)) * 4, c->stream, Q, B3, 3 * g.lgB, nbrick, ibits,
                        c->err);
-  hipLaunchKernelGGL(k_escape_table, dim3((unsigned)std::min<int64_t>(cdiv(nbrick, KT), 64), ny),
-                     dim3(KT), 0, c->stream, Q, B3, nbrick, c->err);
+  hipLaunchKernelGGL(k_escape_table, dim3((unsigned)std::min<int64_t>(ntile, 512), ny), dim3(RT), 0,
+                     c->stream, Q, B3, nbrick, c->err);
   PM_LAUNCH_CHECK();
   return PM_OK;
 }
