@@ -195,7 +195,7 @@ pm_status pm_query_sizes(const pm_config* cfg, int64_t n_max, int n_sp, pm_sizes
   st += grown(n_sp * (nb + 1) * 8) + grown(n_sp * (nb + 1) * 4);  // re-sort: brick starts
   st += 2 * grown(n_sp * nb * 4);                       // movers and escapes per brick
   st += grown(n_sp * (std::max<int64_t>(nb, std::min<int64_t>(32 * nb, 1 << 20)) +
-                      nb / 4096 + 4) * 4);              // arrivals, escapes per tile, totals
+                      nb / 4096 + 4) * 4);  // arrivals, escapes per tile, totals
   st += grown(nc3 * 4 * n_sp);                          // stayers per cell
   st += grown(nc3 * 4) * 2 + grown((nc3 + 1) * 8);      // encode: counts, escapes
   st += 2 * grown(NP * 6) + grown(NP * 2);              // new codes and digits, old order

@@ -22,8 +22,8 @@
 //   k_place         per brick: its arrivals sorted by old index, then arrivals from
 //                   earlier bricks, stayers and arrivals from later bricks written at
 //                   their final stream positions, and the new count bytes.
-//   k_escape_table  the cells of 255 particles and more.
-// Seven launches for all species, whatever the mesh. The movers are few (1% of the
+//   k_place_rest    the cells of 255 particles and more; bricks that k_place leaves.
+// Seven launches for all species on most meshes. The movers are few (1% of the
 // neutrinos at the large workload), so grouping them by brick with one atomic each and
 // sorting each brick's handful in LDS replaces a device-wide radix sort by cell: at
 // 64^3 its 60 small launches took 170 of the step's 275 us.
@@ -813,7 +813,7 @@ struct PlaceSpecies {
   const void* tpos;        // new codes, old stream order
   const void* tvel;
   uint32_t* cnt;           // stayers per cell; the new count of cells of 255 and more
-  const uint32_t* mcnt;    // movers per brick
+  uint32_t* mcnt;          // movers per brick; after the scan: the bricks that k_place left
   uint32_t* acnt;          // arrivals per brick (counted down to 0 as they are listed)
   const int32_t* pmn;      // per-brick extreme new velocity codes
   const int32_t* pmx;
@@ -823,7 +823,8 @@ struct PlaceSpecies {
   uint32_t* abuf;          // the same size, for sorting long lists
   uint32_t* ecnt;          // cells of 255 and more per brick
   uint32_t* etile;         // the same per ET bricks
-  uint32_t* tot;           // their total
+  uint32_t* tot;           // [0] their total, [1] crowded bricks, [2] bricks of long lists
+  int64_t crowd;           // a brick of more stayers is crowded
   pm_shdr* hout;
   void* pos;
   void* vel;
@@ -846,6 +847,7 @@ constexpr int64_t APAD_WORDS = 1 << 20;
 // of more than 2^21 bricks exceeds the largest grid). The extreme velocity codes ride along
 // and end in the header. A brick per thread: the loads of distant offsets and counters are
 // what takes the time (32768 bricks, sums and scan 36 us with four per thread, 18 with one).
+constexpr int LONG = 1024;  // arrivals of a brick that one wave sorts
 constexpr int BS_T = 1024, BS_I = 1, BS_TILE = BS_T * BS_I;
 struct BrickSum {
   int64_t tot, arr;
@@ -972,6 +974,15 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// The same for global memory that only this wave's workgroup writes and reads. (A device-wide
+// fence writes back and drops the XCD's L2 every time: bricks of 512 arrivals then took five
+// times as long.)
+__device__ __forceinline__ void wave_sync_global() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 // The movers into the lists of the bricks they arrive in, in no particular order (the
 // brick's wave sorts its list by old index). A thread looks at MV particles' digits in one
 // 16-byte load. A mover costs a chain of dependent accesses (key, its brick's counter, the
@@ -1031,47 +1042,99 @@ __device__ __forceinline__ uint64_t wave_match(uint32_t d, bool valid, int nbits
   return match;
 }
 
-// Ascending sort of a[0, m) in global memory by one wave (stable 8-bit digit passes, an
-// even number of them through b so that the result is in a): arrival lists too long for
-// the LDS sort. hist: 256 words of LDS. bits: significant bits of the values.
-__device__ void wave_sort_long(uint32_t* a, uint32_t* b, int64_t m, int bits, uint32_t* hist) {
+// Ascending bitonic sort of a[0, n) in LDS by one wave, n a power of two.
+__device__ __forceinline__ void wave_sort_lds(uint32_t* a, int n) {
   const int lane = threadIdx.x & 63;
+#pragma nounroll
+  for (int run = 2; run <= n; run <<= 1) {
+#pragma nounroll
+    for (int d = run >> 1; d >= 1; d >>= 1) {
+#pragma unroll 2
+      for (int i = lane; i < n / 2; i += 64) {
+        const int p = 2 * i - (i & (d - 1));
+        const uint32_t x = a[p], y = a[p + d];
+        const bool swap = (x > y) == !(p & run);
+        a[p] = swap ? y : x;
+        a[p + d] = swap ? x : y;
+      }
+      wave_sync();
+    }
+  }
+}
+
+// Ascending sort of a[0, m) in global memory by a workgroup of NW waves (stable 8-bit digit
+// passes, an even number of them through b so that the result is in a): lists too long for
+// k_place. Each wave takes a contiguous part. hist: [NW][256] words of LDS. bits: significant
+// bits of the values.
+template <int NW>
+__device__ void block_sort_long(uint32_t* a, uint32_t* b, int64_t m, int bits, uint32_t* hist,
+                                int* wsum) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const uint64_t lt = lane ? ((~0ull) >> (64 - lane)) : 0ull;
+  const int64_t per = ((m + NW - 1) / NW + 63) / 64 * 64;
+  const int64_t i0 = min(w * per, m), i1 = min(i0 + per, m);
+  uint32_t* my = hist + 256 * w;
   for (int shift = 0; shift < (bits <= 16 ? 16 : 32); shift += 8) {
-    for (int q = lane; q < 256; q += 64) hist[q] = 0;
+    for (int q = lane; q < 256; q += 64) my[q] = 0;
     wave_sync();
-    for (int64_t i = lane; i < m; i += 64) atomicAdd(&hist[(a[i] >> shift) & 255u], 1u);
-    wave_sync();
-    uint32_t h[4], s = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      h[k] = hist[4 * lane + k];
-      s += h[k];
-    }
-    uint32_t base = (uint32_t)pmscan::wave_incl_scan_dpp((int)s) - s;
-    wave_sync();
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      hist[4 * lane + k] = base;
-      base += h[k];
-    }
-    wave_sync();
-    for (int64_t i0 = 0; i0 < m; i0 += 64) {
-      const bool valid = i0 + lane < m;
-      const uint32_t v = valid ? a[i0 + lane] : 0u, d = (v >> shift) & 255u;
+    for (int64_t i = i0 + lane; i < i1; i += 64) atomicAdd(&my[(a[i] >> shift) & 255u], 1u);
+    __syncthreads();
+    uint32_t s = 0;
+    if (threadIdx.x < 256)
+      for (int q = 0; q < NW; ++q) s += hist[256 * q + threadIdx.x];
+    uint32_t at = (uint32_t)pmscan::block_excl_scan_i32((int)s, wsum);
+    if (threadIdx.x < 256)
+      for (int q = 0; q < NW; ++q) {
+        const uint32_t c = hist[256 * q + threadIdx.x];
+        hist[256 * q + threadIdx.x] = at;
+        at += c;
+      }
+    __syncthreads();
+    for (int64_t j0 = i0; j0 < i1; j0 += 64) {
+      const bool valid = j0 + lane < i1;
+      const uint32_t v = valid ? a[j0 + lane] : 0u, d = (v >> shift) & 255u;
       const uint64_t match = wave_match(d, valid, 8);
       const uint32_t rk = (uint32_t)__popcll(match & lt);
-      const uint32_t to = hist[d];
+      const uint32_t to = my[d];
       wave_sync();
-      if (valid && rk == 0) hist[d] = to + (uint32_t)__popcll(match);
+      if (valid && rk == 0) my[d] = to + (uint32_t)__popcll(match);
       wave_sync();
       if (valid) b[to + rk] = v;
     }
-    __threadfence();  // this wave reads b next
+    __syncthreads();  // the other waves read b next
     uint32_t* t = a;
     a = b;
     b = t;
   }
+}
+
+// One particle per valid lane to its cell's next positions, in lane order; run: the running
+// positions, relative to `first`.
+template <typename PC, typename VC>
+__device__ __forceinline__ void place_put(const PlaceSpecies& S, uint32_t* run, int64_t first,
+                                          int nbits, bool valid, uint32_t d, int64_t j,
+                                          const PC (&p)[3], const VC (&v)[3], DevErr* err) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t lt = lane ? ((~0ull) >> (64 - lane)) : 0ull;
+  const uint64_t match = wave_match(d, valid, nbits);
+  const uint32_t rk = (uint32_t)__popcll(match & lt);
+  uint32_t at = 0;
+  if (valid) at = run[d];
+  wave_sync();
+  if (valid && rk == 0) run[d] = at + (uint32_t)__popcll(match);
+  wave_sync();
+  if (!valid) return;
+  const int64_t dst = first + at + rk;
+  if (dst < 0 || dst >= S.n) {
+    latch_error(err, ERRBIT_CORRUPT);
+    return;
+  }
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    ((PC*)S.pos)[3 * dst + a] = p[a];
+    ((VC*)S.vel)[3 * dst + a] = v[a];
+  }
+  if (S.perm) S.perm[dst] = j;
 }
 
 // Final stream positions. A brick's new particles, cell by cell, are its arrivals from
@@ -1082,20 +1145,20 @@ __device__ void wave_sort_long(uint32_t* a, uint32_t* b, int64_t m, int bits, ui
 // NW waves per brick, each with a contiguous part of the stayers and its own running
 // positions (from a first pass over the digits): for bricks of thousands of particles,
 // which one wave takes 80 chunks for. The new count bytes are written here too, so that no
-// pass over the cells follows.
+// pass over the cells follows. A brick of more than CAP arrivals or of many times the mean of
+// stayers is only counted here and left to k_place_rest, whose code this kernel's waves then
+// need not fetch (with it here a step at 64^3 took 92.0 us, 90.1 without).
 constexpr int WB = 4;       // bricks per workgroup (NW = 1)
 constexpr int PU = 4;       // chunks whose loads are issued together
-constexpr int ACAP = 256;   // arrivals sorted in LDS, per wave
+constexpr int ACAP = 256;   // arrivals ranked in LDS, per wave
 template <int P, int V, int NW>
 __global__ __launch_bounds__(NW == 1 ? 64 * WB : 64 * NW) void k_place(
-    PlaceArgs A, int B3, int nbits, int64_t nbrick, int nbits_idx, DevErr* err) {
+    PlaceArgs A, int B3, int nbits, int64_t nbrick, DevErr* err) {
   using PC = typename PosCode<P>::T;
   using VC = typename VelCode<V>::T;
   const PlaceSpecies& S = A.sp[blockIdx.y];
   const PC* tpos = (const PC*)S.tpos;
   const VC* tvel = (const VC*)S.tvel;
-  PC* pos = (PC*)S.pos;
-  VC* vel = (VC*)S.vel;
   constexpr int NT = 64 * NW, CAP = ACAP * NW;
   extern __shared__ uint32_t lds[];
   __shared__ int wsum[16];
@@ -1119,10 +1182,11 @@ __global__ __launch_bounds__(NW == 1 ? 64 * WB : 64 * NW) void k_place(
   const int64_t a0 = S.astart[b];
   const int64_t m = (int64_t)S.astart[b + 1] - a0;  // arrivals
 
-  // the arrivals in old stream order: al[0, m), or aidx[a0, a0 + m) when they are many
+  const bool crowded = j1 - j0 > S.crowd || m > LONG, rest = m > CAP || crowded;
+
+  // the arrivals in old stream order: al[0, m) (aidx[a0, a0 + m), in no order, for the rest)
   for (int l = tid; l < NW * B3; l += NT) runs[l] = 0;
-  const bool big = m > CAP;
-  if (!big) {
+  if (!rest) {
     uint32_t v[ACAP / 64], r[ACAP / 64];
 #pragma unroll
     for (int k = 0; k < ACAP / 64; ++k) {
@@ -1143,11 +1207,9 @@ __global__ __launch_bounds__(NW == 1 ? 64 * WB : 64 * NW) void k_place(
 #pragma unroll
     for (int k = 0; k < ACAP / 64; ++k)
       if (tid + k * NT < m) al[r[k]] = v[k];
-  } else if (bw == 0) {
-    wave_sort_long(S.aidx + a0, S.abuf + a0, m, nbits_idx, al);
   }
   sync();
-  auto arrival = [&](int64_t i) { return (int64_t)(big ? S.aidx[a0 + i] : al[i]); };
+  auto arrival = [&](int64_t i) { return (int64_t)(rest ? S.aidx[a0 + i] : al[i]); };
 
   // arrivals per cell (those from earlier bricks count with the first wave, the others
   // with the last), and for NW > 1 each wave's stayers
@@ -1165,7 +1227,7 @@ __global__ __launch_bounds__(NW == 1 ? 64 * WB : 64 * NW) void k_place(
   // this wave's stayers: [s0, s1)
   const int64_t per = NW == 1 ? j1 - j0 : ((j1 - j0 + NW - 1) / NW + 63) / 64 * 64;
   const int64_t s0 = min(j0 + bw * per, j1), s1 = min(s0 + per, j1);
-  if constexpr (NW > 1) {
+  if (NW > 1 && !rest) {
     for (int64_t base = s0; base < s1; base += 64 * PU) {
       uint32_t d[PU];
 #pragma unroll
@@ -1188,7 +1250,7 @@ __global__ __launch_bounds__(NW == 1 ? 64 * WB : 64 * NW) void k_place(
     const int l = l0 + tid;
     uint32_t x = 0;
     if (l < B3) {
-      if constexpr (NW == 1) x = S.cnt[kbase + l];
+      if (NW == 1 || rest) x = S.cnt[kbase + l];
 #pragma unroll
       for (int q = 0; q < NW; ++q) x += runs[q * B3 + l];
       S.count[kbase + l] = (uint8_t)(x >= 255u ? 255u : x);
@@ -1238,31 +1300,15 @@ __global__ __launch_bounds__(NW == 1 ? 64 * WB : 64 * NW) void k_place(
         atomicAdd(&S.tot[0], (uint32_t)ne);
         atomicAdd(&S.etile[b / ET], (uint32_t)ne);
       }
+      // the crowded bricks from the front of the array, those of long lists from its end
+      if (crowded) S.mcnt[atomicAdd(&S.tot[1], 1u)] = (uint32_t)b;
+      else if (rest) S.mcnt[nbrick - 1 - atomicAdd(&S.tot[2], 1u)] = (uint32_t)b;
     }
   }
+  if (rest) return;  // uniform: the wave (NW = 1) or the workgroup
   sync();
-  // a chunk of at most 64 particles: each valid lane's particle to its cell's next
-  // positions, in lane order
   auto put = [&](bool valid, uint32_t d, int64_t j, const PC (&p)[3], const VC (&v)[3]) {
-    const uint64_t match = wave_match(d, valid, nbits);
-    const uint32_t rk = (uint32_t)__popcll(match & lt);
-    uint32_t at = 0;
-    if (valid) at = run[d];
-    wave_sync();
-    if (valid && rk == 0) run[d] = at + (uint32_t)__popcll(match);
-    wave_sync();
-    if (!valid) return;
-    const int64_t dst = first + at + rk;
-    if (dst < 0 || dst >= n) {
-      latch_error(err, ERRBIT_CORRUPT);
-      return;
-    }
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      pos[3 * dst + a] = p[a];
-      vel[3 * dst + a] = v[a];
-    }
-    if (S.perm) S.perm[dst] = j;
+    place_put(S, run, first, nbits, valid, d, j, p, v, err);
   };
   auto put_arrivals = [&](int64_t i0, int64_t i1) {
     for (int64_t i = i0; i < i1; i += 64) {
@@ -1304,46 +1350,178 @@ __global__ __launch_bounds__(NW == 1 ? 64 * WB : 64 * NW) void k_place(
   if (bw == NW - 1) put_arrivals(early, m);
 }
 
-// The escape table in cell order (cells of 255 particles and more are rare: without any,
-// every workgroup returns after one load). A workgroup takes ET bricks at a time; the escapes
-// before them are the sum of the earlier tiles' counts, at most 512, one load per thread.
-// (Adding up every earlier brick's count took the last workgroup 1024 rounds at 1024^3: 291 us
-// with 400 escapes, 36 this way.)
-constexpr int RT = 1024;
-__global__ __launch_bounds__(RT) void k_escape_table(PlaceArgs A, int B3, int64_t nbrick,
-                                                    DevErr* err) {
+// The escape table, then the bricks that k_place left. Without any of the two (the rule: cells
+// of 255 particles and crowded bricks are rare) every workgroup returns after one load.
+//
+// Escapes in cell order: a workgroup takes ET bricks at a time; the escapes before them are the
+// sum of the earlier tiles' counts, at most 512, one load per thread. (Adding up every earlier brick's count took the last workgroup 1024 rounds at 1024^3.)
+//
+// A brick's sequence of early arrivals, old particles and late arrivals is dealt to the waves in
+// contiguous parts: a pass counts each wave's particles per cell, a prefix over cells and waves
+// gives its running positions, a second pass places them. A brick of a long list takes one
+// wave, a crowded one the whole workgroup: one wave takes 600 ns for a chunk of 64, all in one
+// chain (1.9 M particles in one brick: 19.1 ms in k_place, 3.8 here).
+constexpr int RT = 1024, RW = RT / 64;
+
+// NW waves (all of the workgroup's, or this one alone) place brick b. lds: [NW][LONG].
+template <int P, int V, int NW>
+__device__ __forceinline__ void place_brick(const PlaceSpecies& S, int64_t b, int B3, int nbits,
+                                            int nbits_idx, uint32_t* lds, int* wsum,
+                                            DevErr* err) {
+  using PC = typename PosCode<P>::T;
+  using VC = typename VelCode<V>::T;
+  const PC* tpos = (const PC*)S.tpos;
+  const VC* tvel = (const VC*)S.tvel;
+  const int lane = threadIdx.x & 63;
+  const int w = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tid = NW == 1 ? lane : (int)threadIdx.x;
+  auto sync = [] {
+    if constexpr (NW == 1) wave_sync();
+    else __syncthreads();
+  };
+  const int64_t kbase = b * B3, n = S.n;
+  const int64_t j0 = min(S.off[kbase], n), j1 = max(j0, min(S.off[kbase + B3], n));
+  const int64_t a0 = S.astart[b], m = (int64_t)S.astart[b + 1] - a0;
+  uint32_t* run = lds + w * B3;
+  static_assert(LONG >= 512, "the cells of a brick and the digits of a sort fit");
+  sync();  // the last brick is done with the LDS
+  if constexpr (NW == 1) {
+    const int full = m <= LONG / 2 ? LONG / 2 : LONG;
+    for (int i = lane; i < full; i += 64) lds[i] = i < m ? S.aidx[a0 + i] : 0xffffffffu;
+    wave_sync();
+    wave_sort_lds(lds, full);
+    for (int i = lane; i < m; i += 64) S.aidx[a0 + i] = lds[i];
+    wave_sync_global();  // the wave reads them back
+  } else {
+    block_sort_long<NW>(S.aidx + a0, S.abuf + a0, m, nbits_idx, lds, wsum);
+  }
+  int64_t early = 0;  // arrivals from earlier bricks: before the first with index j0 or more
+  for (int64_t hi = m; early < hi;) {
+    const int64_t mid = (early + hi) >> 1;
+    if ((int64_t)S.aidx[a0 + mid] < j0) early = mid + 1; else hi = mid;
+  }
+  for (int l = tid; l < NW * B3; l += 64 * NW) lds[l] = 0;
+  sync();
+  const int64_t all = m + (j1 - j0), late = early + (j1 - j0);
+  const int64_t per = ((all + NW - 1) / NW + 63) / 64 * 64;
+  const int64_t v0 = min(w * per, all), v1 = min(v0 + per, all);
+  // element q of the sequence: its old stream index and digit (B3: none). An arrival's key lies
+  // anywhere, so its digit is left in abuf for the second pass.
+  auto item = [&](int64_t q, int64_t& j, bool again) -> uint32_t {
+    if (q >= v1) return (uint32_t)B3;
+    const bool old = q >= early && q < late;
+    const int64_t i = a0 + (q < early ? q : q - (j1 - j0));
+    j = old ? j0 + (q - early) : (int64_t)S.aidx[i];
+    if (j >= n) return (uint32_t)B3;  // an inconsistent count (latched)
+    if (old) return (uint32_t)S.tdig[j];
+    if (again) return S.abuf[i];
+    const uint32_t d = min(S.mkey[j] - (uint32_t)kbase, (uint32_t)B3);
+    S.abuf[i] = d;
+    return d;
+  };
+  for (int64_t q0 = v0; q0 < v1; q0 += 64 * PU) {
+    uint32_t d[PU];
+    int64_t j;
+#pragma unroll
+    for (int u = 0; u < PU; ++u) d[u] = item(q0 + 64 * u + lane, j, false);
+#pragma unroll
+    for (int u = 0; u < PU; ++u)
+      if (d[u] < (uint32_t)B3) atomicAdd(&run[d[u]], 1u);
+  }
+  sync();
+  uint32_t carry = 0;
+  for (int l0 = 0; l0 < B3; l0 += 64 * NW) {  // (once, for a whole workgroup)
+    const int l = l0 + tid;
+    uint32_t x = 0;
+    if (l < B3)
+      for (int q = 0; q < NW; ++q) x += lds[q * B3 + l];
+    uint32_t at = carry;
+    if constexpr (NW == 1) {
+      const uint32_t inc = (uint32_t)pmscan::wave_incl_scan_dpp((int)x);
+      at += inc - x;
+      carry += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+    } else {
+      at += (uint32_t)pmscan::block_excl_scan_i32((int)x, wsum);
+    }
+    if (l < B3)
+      for (int q = 0; q < NW; ++q) {
+        const uint32_t c = lds[q * B3 + l];
+        lds[q * B3 + l] = at;
+        at += c;
+      }
+  }
+  if constexpr (NW == 1) wave_sync_global();  // the digits in abuf
+  else __syncthreads();
+  const int64_t first = S.bstart[b];
+  for (int64_t q0 = v0; q0 < v1; q0 += 64 * PU) {
+    uint32_t d[PU];
+    int64_t j[PU];
+    PC p[PU][3];
+    VC v[PU][3];
+#pragma unroll
+    for (int u = 0; u < PU; ++u) {
+      j[u] = 0;  // n > 0: the brick has particles
+      d[u] = item(q0 + 64 * u + lane, j[u], true);
+      const int64_t jj = d[u] < (uint32_t)B3 ? j[u] : 0;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        p[u][a] = tpos[3 * jj + a];
+        v[u][a] = tvel[3 * jj + a];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < PU; ++u)
+      place_put(S, run, first, nbits, d[u] < (uint32_t)B3, d[u], j[u], p[u], v[u], err);
+  }
+}
+
+template <int P, int V>
+__global__ __launch_bounds__(RT, 8) void k_place_rest(PlaceArgs A, int B3, int nbits,
+                                                     int64_t nbrick, int nbits_idx, DevErr* err) {
   const PlaceSpecies& S = A.sp[blockIdx.y];
-  const uint32_t total = S.tot[0];
-  if (total == 0) return;  // the header's n_esc is 0 already
-  __shared__ int64_t lw[RT / 64 + 1];
-  const int64_t nt = (nbrick + ET - 1) / ET;
-  for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
-    if (S.etile[t] == 0) continue;
-    int64_t before = 0, tot;
-    for (int64_t q = threadIdx.x; q < t; q += RT) before += S.etile[q];
-    pmscan::block_excl_scan(before, lw, &tot);
-    int64_t at = tot;
-    const int64_t q1 = min((t + 1) * ET, nbrick);
-    for (int64_t b0 = t * ET; b0 < q1; b0 += RT) {
-      const int64_t b = b0 + threadIdx.x;
-      const uint32_t ne = b < q1 ? S.ecnt[b] : 0u;
-      int64_t k = at + pmscan::block_excl_scan((int64_t)ne, lw, &tot);
-      at += tot;
-      if (!ne) continue;
-      for (int64_t i = b * B3; i < (b + 1) * B3; ++i)
-        if (S.count[i] == 255) {
-          if (k < S.cap_esc) {
-            S.esc[2 * k] = (uint64_t)i;
-            S.esc[2 * k + 1] = (uint64_t)S.cnt[i];
+  const uint32_t total = S.tot[0], crowded = S.tot[1], listed = S.tot[2];
+  if ((total | crowded | listed) == 0) return;  // the header's n_esc is 0 already
+  extern __shared__ uint32_t lds[];  // [RW][LONG]
+  __shared__ int64_t lw[RW + 1];
+  __shared__ int wsum[RW];
+  if (total > 0) {
+    const int64_t nt = (nbrick + ET - 1) / ET;
+    for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
+      if (S.etile[t] == 0) continue;
+      int64_t before = 0, tot;
+      for (int64_t q = threadIdx.x; q < t; q += RT) before += S.etile[q];
+      pmscan::block_excl_scan(before, lw, &tot);
+      int64_t at = tot;
+      const int64_t q1 = min((t + 1) * ET, nbrick);
+      for (int64_t b0 = t * ET; b0 < q1; b0 += RT) {
+        const int64_t b = b0 + threadIdx.x;
+        const uint32_t ne = b < q1 ? S.ecnt[b] : 0u;
+        int64_t k = at + pmscan::block_excl_scan((int64_t)ne, lw, &tot);
+        at += tot;
+        if (!ne) continue;
+        for (int64_t i = b * B3; i < (b + 1) * B3; ++i)
+          if (S.count[i] == 255) {
+            if (k < S.cap_esc) {
+              S.esc[2 * k] = (uint64_t)i;
+              S.esc[2 * k + 1] = (uint64_t)S.cnt[i];
+            }
+            ++k;
           }
-          ++k;
-        }
+      }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      S.hout->n_esc = (int64_t)total;
+      if ((int64_t)total > S.cap_esc) latch_error(err, ERRBIT_CAPACITY, (int64_t)total);
     }
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    S.hout->n_esc = (int64_t)total;
-    if ((int64_t)total > S.cap_esc) latch_error(err, ERRBIT_CAPACITY, (int64_t)total);
-  }
+  for (uint32_t h = blockIdx.x; h < crowded; h += gridDim.x)
+    place_brick<P, V, RW>(S, __builtin_amdgcn_readfirstlane(S.mcnt[h]), B3, nbits, nbits_idx, lds,
+                          wsum, err);
+  __syncthreads();
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (uint32_t h = w * gridDim.x + blockIdx.x; h < listed; h += RW * gridDim.x)
+    place_brick<P, V, 1>(S, __builtin_amdgcn_readfirstlane(S.mcnt[nbrick - 1 - h]), B3, nbits,
+                         nbits_idx, lds + w * LONG, wsum, err);
 }
 
 }  // namespace
@@ -1400,8 +1578,9 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
   int apad = 0;
   while (apad < 5 && nbrick << (apad + 1) <= APAD_WORDS) ++apad;
   // what every call clears: the arrival counters, and per species the escapes' tiles and total
+  // and the numbers of bricks that k_place leaves
   const int64_t ntile = cdiv(nbrick, ET);
-  const int64_t nclear = n_sp * ((nbrick << apad) + ntile + 1);
+  const int64_t nclear = n_sp * ((nbrick << apad) + ntile + 3);
   uint32_t* acnt = (uint32_t*)scratch(c, SC_ACNT, (size_t)nclear * 4);
   uint32_t* ecnt = (uint32_t*)scratch(c, SC_ECNT, (size_t)nbrick * n_sp * 4);
   char* tpos = (char*)scratch(c, SC_TPOS, nn * 3 * P);
@@ -1471,7 +1650,10 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
     L.abuf = abuf + nbase[s];
     L.ecnt = ecnt + s * nbrick;
     L.etile = etile + s * ntile;
-    L.tot = tot + s;
+    L.tot = tot + 3 * s;
+    // beyond 8 times the mean a brick is the last one to be done (and one wave takes 20 us for
+    // 2048 stayers)
+    L.crowd = std::max<int64_t>(B3 >= 512 ? 16384 : 2048, 8 * in[s].n / nbrick);
     L.hout = out[s].hdr;
     L.pos = out[s].pos;
     L.vel = out[s].vel;
@@ -1521,14 +1703,13 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
   // bricks of 8^3 cells hold thousands of particles: four waves each
   if (B3 >= 512)
     hipLaunchKernelGGL((k_place<P, V, 4>), dim3((unsigned)nbrick, ny), dim3(256),
-                       (size_t)4 * (ACAP + B3) * 4, c->stream, Q, B3, 3 * g.lgB, nbrick, ibits,
-                       c->err);
+                       (size_t)4 * (ACAP + B3) * 4, c->stream, Q, B3, 3 * g.lgB, nbrick, c->err);
   else
     hipLaunchKernelGGL((k_place<P, V, 1>), dim3((unsigned)cdiv(nbrick, WB), ny), dim3(64 * WB),
-                       (size_t)WB * (ACAP + ((B3 + 3) & ~3)) * 4, c->stream, Q, B3, 3 * g.lgB, nbrick, ibits,
-                       c->err);
-  hipLaunchKernelGGL(k_escape_table, dim3((unsigned)std::min<int64_t>(ntile, 512), ny), dim3(RT), 0,
-                     c->stream, Q, B3, nbrick, c->err);
+                       (size_t)WB * (ACAP + ((B3 + 3) & ~3)) * 4, c->stream, Q, B3, 3 * g.lgB, nbrick, c->err);
+  hipLaunchKernelGGL((k_place_rest<P, V>), dim3((unsigned)std::min<int64_t>(cdiv(nbrick, 4), 512), ny),
+                     dim3(RT), (size_t)RW * LONG * 4, c->stream, Q, B3, 3 * g.lgB,
+                     nbrick, ibits, c->err);
   PM_LAUNCH_CHECK();
   return PM_OK;
 }
