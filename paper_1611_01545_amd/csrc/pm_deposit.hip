@@ -51,7 +51,9 @@ struct DepArgs {
   int n_sp;
   int T;   // tile side in cells
   int r;   // mesh cells per compression cell
-  int R;   // tile side in nodes
+  int R;   // tile side in nodes: a power of two, 16 or (few cells) less
+  int lgR;
+  uint32_t rE;  // 2^16 / (T + 1), rounded up
   int lgt; // log2(tiles per box side)
 };
 
@@ -67,24 +69,34 @@ __host__ __device__ constexpr int dep_slots(int R) {
 // loads in flight together. Those of 8^3 cells take the species' tables one after the other
 // (three tiles on a CU).
 template <int TT> constexpr int dep_win() { return TT == 4 ? 1024 : TT == 8 ? 1536 : 2048; }
-template <int TT> constexpr int dep_tabs() { return TT == 4 ? 2 : 1; }
+template <int TT, int SP> constexpr int dep_tabs() { return TT == 4 && SP != 1 ? 2 : 1; }
 template <int TT> struct DepMark { using T = uint16_t; };
 template <> struct DepMark<4> { using T = uint8_t; };  // 125 cells
-template <int TT>
+constexpr int DEP_THREADS = 512;
+// Node sums: 32 bits a slot and species, or one species' in 64 bits. Those of a single species
+// are of the tile's own nodes alone, 32 KB, so that four tiles fit a CU: with room for a slot
+// each, as two species have, three did, and 512^3 nodes with a particle per cell took 253 us
+// instead of 218 (1.94 ms instead of 1.63 at 1024^3).
+template <int SP>
+__host__ __device__ constexpr int dep_node_bytes(int R) {
+  const int narrow = (dep_slots(R) * 4 * (SP == 1 ? 1 : 2) + 15) & ~15, wide = R * R * R * 8;
+  return narrow > wide ? narrow : wide;
+}
+template <int TT, int SP>
 size_t dep_lds_bytes(int R, int NE) {
-  return (size_t)dep_slots(R) * 8 + (size_t)dep_tabs<TT>() * (NE * 8 + (NE + 1) * 4) +
-         (size_t)dep_tabs<TT>() * dep_win<TT>() * sizeof(typename DepMark<TT>::T);
+  constexpr int tabs = dep_tabs<TT, SP>();
+  return (size_t)dep_node_bytes<SP>(R) + (size_t)tabs * (NE * 8 + (NE + 1) * 4) +
+         (size_t)tabs * dep_win<TT>() * sizeof(typename DepMark<TT>::T);
 }
 
-// Sum over the 64 lanes of a wave by DPP, in lane 63
-__device__ inline double wave_sum_dpp(double v) {
+// Sum over the 64 lanes of a wave by DPP (mod 2^64), in lane 63
+__device__ inline uint64_t wave_sum_dpp(uint64_t v) {
   auto step = [&](auto ctrl, auto rows) {
     constexpr int C = decltype(ctrl)::value, M = decltype(rows)::value;
-    const long long b = __double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, C, M, 0xf, false);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, C, M, 0xf, false);
     const uint32_t hi =
-        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)((uint64_t)b >> 32), C, M, 0xf, false);
-    v += __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), C, M, 0xf, false);
+    v += ((uint64_t)hi << 32) | lo;
   };
   step(IC<0x111>{}, IC<0xf>{});
   step(IC<0x112>{}, IC<0xf>{});
@@ -108,8 +120,6 @@ __device__ inline int wave_incl_max_dpp(int v) {
   return v;
 }
 
-constexpr int DEP_THREADS = 512;
-
 // The three codes of particle j of n: one unaligned load of 4 (8) bytes, moved back by
 // `back` bytes from the array's end where it would pass it (shift the result down by as
 // many); byte loads for a single particle.
@@ -129,9 +139,10 @@ __device__ __forceinline__ CT dep_codes(const void* pos, int64_t n, uint32_t j, 
   return c;
 }
 
-// One particle's eight weights into slots of type NT; the weight units added.
-template <int PB, typename NT, typename CT>
-__device__ __forceinline__ uint32_t dep_add(NT* node, CT code, uint32_t org, int r, int Rp) {
+// One particle's eight weights. put(dx, dy, dz, slots of the lower corner, weight); the weight
+// units added, 0 for nothing to add or a particle of the shell that reaches no node of the tile.
+template <int PB, typename CT, typename Put>
+__device__ __forceinline__ uint32_t dep_weights(CT code, uint32_t org, int r, Put put) {
   constexpr int FB = 8 * PB + 1;  // fractional bits of a mesh coordinate
   constexpr int ONE = 1 << FB;    // one mesh cell
   int sl[3], f[3];
@@ -144,9 +155,7 @@ __device__ __forceinline__ uint32_t dep_add(NT* node, CT code, uint32_t org, int
     sl[a] = (int)(int8_t)(org >> (8 * a)) + (gl >> FB);
     f[a] = gl & (ONE - 1);
   }
-  // nothing to add, or a particle of the shell that reaches no node of the tile
   if ((sl[0] | sl[1] | sl[2]) < 0) return 0;
-  NT* p = node + ((sl[2] * Rp + sl[1]) * Rp + sl[0]);
   const uint32_t wx[2] = {(uint32_t)(ONE - f[0]), (uint32_t)f[0]},
                  wy[2] = {(uint32_t)(ONE - f[1]), (uint32_t)f[1]},
                  wz[2] = {(uint32_t)(ONE - f[2]), (uint32_t)f[2]};
@@ -165,9 +174,26 @@ __device__ __forceinline__ uint32_t dep_add(NT* node, CT code, uint32_t org, int
           W = (uint32_t)((w3 + (1ull << 23)) >> 24);  // 2^-51 -> 2^-27, rounded
           sum += W;
         }
-        atomicAdd(&p[(dz * Rp + dy) * Rp + dx], (NT)W);
+        put(dx, dy, dz, sl, W);
       }
   return PB == 1 ? 1u << 27 : sum;
+}
+// into slots of type NT
+template <int PB, typename NT, typename CT>
+__device__ __forceinline__ uint32_t dep_add(NT* node, CT code, uint32_t org, int r, int Rp) {
+  return dep_weights<PB>(code, org, r, [&](int dx, int dy, int dz, const int (&sl)[3], uint32_t W) {
+    atomicAdd(&node[(sl[2] * Rp + sl[1]) * Rp + sl[0] + (dz * Rp + dy) * Rp + dx], (NT)W);
+  });
+}
+// into the tile's own nodes
+template <int PB, typename NT, typename CT>
+__device__ __forceinline__ void dep_add_own(NT* node, CT code, uint32_t org, int r, int lgR) {
+  const uint32_t R = 1u << lgR;
+  dep_weights<PB>(code, org, r, [&](int dx, int dy, int dz, const int (&sl)[3], uint32_t W) {
+    const uint32_t x = (uint32_t)(sl[0] + dx - 1), y = (uint32_t)(sl[1] + dy - 1),
+                   z = (uint32_t)(sl[2] + dz - 1);
+    if (x < R && y < R && z < R) atomicAdd(&node[(((z << lgR) + y) << lgR) + x], (NT)W);
+  });
 }
 
 // TT: tile side in cells (compile time, 0: runtime A.T); PB: position bytes per axis. With
@@ -176,27 +202,29 @@ __device__ __forceinline__ uint32_t dep_add(NT* node, CT code, uint32_t org, int
 // 2^-27, the unit of the 1-byte form, so that the same integer sums apply.
 // SP: one species, two, or (3) any larger number, in pairs.
 template <int TT, int PB, int SP>
-__global__ __launch_bounds__(DEP_THREADS, SP == 3 && TT == 0 ? 2 : SP == 3 || TT == 0 ? 4 : 6) void k_deposit_tile(
+__global__ __launch_bounds__(DEP_THREADS, SP == 3 || (TT == 0 && PB == 2) ? 4 : 6) void k_deposit_tile(
     DepArgs A, Geom g, float* rho) {
   constexpr bool MORE = SP == 3;
   constexpr int SB = SP == 1 ? 1 : 2;  // species of a batch
   using CT = typename std::conditional<PB == 1, uint32_t, uint64_t>::type;
   constexpr int NT = DEP_THREADS, NW = NT / 64;
-  constexpr int WIN = dep_win<TT>(), TABS = dep_tabs<TT>();
+  constexpr int WIN = dep_win<TT>(), TABS = dep_tabs<TT, SP>();
   constexpr int U = WIN / NT;                 // chunks of 64 particles per wave and window
   using MT = typename DepMark<TT>::T;
   extern __shared__ __align__(16) unsigned char smem[];
   // compile-time tiles have T r = 16 nodes per side (T = 16 / r)
   const int T = TT ? TT : A.T, R = TT ? 16 : A.R, r = TT ? 16 / TT : A.r;
   const bool spread = !TT && r == 1;  // the coarse mesh of the two-level force
+  const int lgR = TT ? 4 : A.lgR;
   const int E = T + 1;              // extended cells per side
   const int NE = E * E * E;
   const int Rp = R + 1, NS = TT ? dep_slots(16) : dep_slots(R);
   __shared__ int wsum[2][NW];
-  __shared__ double lost[NW];  // weight units missing from the sums, per wave
-  __shared__ int full[NW];     // a cell of the wave that 32-bit sums cannot hold
-  uint32_t* node = (uint32_t*)smem;                      // [2][NS] weight sums of two species
-  uint2* tab = (uint2*)(node + 2 * NS);                  // [TABS][NE] stream start, origin
+  __shared__ uint64_t lost[NW];  // weight units missing from the sums, per wave
+  __shared__ int over[NW];       // the wave's cells: 1 beyond 32-bit sums, 2 perhaps so
+  uint32_t* node = (uint32_t*)smem;                      // [SB][NS] weight sums per species
+  unsigned long long* wide = (unsigned long long*)smem;  // one species' in 64 bits
+  uint2* tab = (uint2*)(smem + dep_node_bytes<SP>(R));   // [TABS][NE] stream start, origin
   int* pre = (int*)(tab + TABS * NE);                    // [TABS][NE + 1] particles before
   MT* mark = (MT*)(pre + TABS * (NE + 1));               // [TABS][WIN] extended cells
   const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -211,11 +239,35 @@ __global__ __launch_bounds__(DEP_THREADS, SP == 3 && TT == 0 ? 2 : SP == 3 || TT
   if (threadIdx.x < NS % ZB * SB) node[NS / ZB * 4 + threadIdx.x] = 0;
   for (int i = threadIdx.x; i < TABS * WIN * (int)sizeof(MT) / 4; i += NT)
     ((uint32_t*)mark)[i] = 0u;
-  // per-thread density of its slots i = threadIdx.x + k NT, summed over species in order
-  constexpr int NPT = (dep_slots(16) + NT - 1) / NT;
+  // Each thread's nodes of the tile: 16 nodes per side, four consecutive ones along x in planes
+  // tid / 64 + NW k of row tid / 4 % 16; fewer nodes, one per thread. Their densities are summed
+  // over the species in order.
+  const bool full = TT || R == 16;
+  const bool own = full || (int)threadIdx.x < R * R * R;
+  const int lx = full ? 4 * (threadIdx.x & 3) : threadIdx.x & (R - 1),
+            ly = full ? (threadIdx.x >> 2) & 15 : (threadIdx.x >> lgR) & (R - 1),
+            lz = full ? threadIdx.x >> 6 : threadIdx.x >> (2 * lgR);
+  constexpr int NPT = 4096 / NT;
   float racc[NPT];
+  auto each = [&](auto f) {  // f(k, slot, node)
+    if (!own) return;
+#pragma unroll
+    for (int k = 0; k < NPT; ++k) {
+      if (!full && k > 0) break;
+      const int x = lx + (k & 3), z = lz + NW * (k >> 2);
+      f(k, ((z + 1) * Rp + ly + 1) * Rp + x + 1, (((z << lgR) + ly) << lgR) + x);
+    }
+  };
 #pragma unroll
   for (int k = 0; k < NPT; ++k) racc[k] = 0.0f;
+  auto split = [&](int e, int& ex, int& ey, int& ez) {  // extended cell e < 2^10 (T <= 8)
+    int q = e / E;
+    if constexpr (!TT) q = (int)((uint32_t)e * A.rE >> 16);
+    ex = e - q * E;
+    ez = q / E;
+    if constexpr (!TT) ez = (int)((uint32_t)q * A.rE >> 16);
+    ey = q - ez * E;
+  };
 
   const int n_sp = MORE ? A.n_sp : min(A.n_sp, 2);
   for (int s0 = 0; s0 < (MORE ? n_sp : min(n_sp, 1)); s0 += 2) {
@@ -232,7 +284,8 @@ __global__ __launch_bounds__(DEP_THREADS, SP == 3 && TT == 0 ? 2 : SP == 3 || TT
       for (int k = 0; k < KMAX; ++k) {
         const int e = e0 + k;
         const bool in = k < K && e < NE;
-        const int ex = e % E, ey = (e / E) % E, ez = e / (E * E);
+        int ex, ey, ez;
+        split(e, ex, ey, ez);
         const uint32_t key =
             in ? cell_key(g, wrapc(tx * T + ex - 1, ncs), wrapc(ty * T + ey - 1, ncs),
                           wrapc(tz * T + ez - 1, ncs))
@@ -246,12 +299,13 @@ __global__ __launch_bounds__(DEP_THREADS, SP == 3 && TT == 0 ? 2 : SP == 3 || TT
         }
       }
     };
-    // A cell of the tile gives its particles' whole weight to (r + 1)^3 slots, and 32
-    // particles' weight is 2^32: with more than 32 (r + 1)^3 of them a 32-bit slot passes
-    // 2^32 for certain. Such a tile takes the 64-bit sums at once: 79 k of 262 k particles in
-    // one cell of 128^3 nodes 1229 -> 622 us, 30% of 2 M in 1/64000 of 256^3 2359 -> 1255.
-    const int most = 32 * (r + 1) * (r + 1) * (r + 1) + 32;
-    bool crowd = false;
+    // A node of 32 particles' weight (2^32) passes a 32-bit slot, and such a tile is summed
+    // again in 64 bits. These sums alone take 1.13 times as long as those in 32 bits with 4
+    // mesh cells per compression cell and axis, 1.3 times with 2, so a tile starts with them
+    // where a cell has 16 particles per node and some more: evenly spread, their nodes pass 32
+    // about there. XXX
+    const int most = 16 * r * r * r + 48;
+    bool crowd = false, maybe = false;
     int before[2] = {0, 0}, loc[2] = {0, 0};
     if (cells) {
       fetch();
@@ -261,16 +315,25 @@ __global__ __launch_bounds__(DEP_THREADS, SP == 3 && TT == 0 ? 2 : SP == 3 || TT
         for (int k = 0; k < KMAX; ++k) {
           const int e = e0 + k;
           loc[s] += cnt[s][k];
-          if (cnt[s][k] > most) crowd |= e % E && (e / E) % E && e / (E * E);  // no shell cell
+          int ex, ey, ez;
+          split(e, ex, ey, ez);
+          if (cnt[s][k] > most) crowd |= ex && ey && ez;  // no shell cell
         }
         before[s] = pmscan::wave_incl_scan_dpp(loc[s]);
+        // A node takes weight from 2^3 cells, four pairs of neighbours along x: with no pair of
+        // more than 7 it cannot pass 28 particles, and the sums need no check. (Pairs across
+        // waves by twice either count; those across rows do no harm.)
+        const int last = K == KMAX ? cnt[s][KMAX - 1] : cnt[s][0];
+        const int next = __shfl_down(cnt[s][0], 1, 64);
+        maybe |= last + (lane == 63 ? last : next) > 7 || 2 * cnt[s][0] > 7 * (lane == 0 ? 1 : 2);
+        for (int k = 0; k + 1 < KMAX; ++k) maybe |= k + 1 < K && cnt[s][k] + cnt[s][k + 1] > 7;
       }
     }
-    const bool wave_crowd = __any(crowd);
+    const int wave_over = (__any(crowd) ? 1 : 0) | (__any(maybe) ? 2 : 0);
     if (lane == 63) {
       wsum[0][wv] = before[0];
       if (SP != 1) wsum[1][wv] = before[1];
-      full[wv] = wave_crowd;
+      over[wv] = wave_over;
     }
     __syncthreads();  // also: the last pair is done with the tables
     int np[2] = {0, 0};  // particles of the tile and its shell
@@ -286,8 +349,9 @@ __global__ __launch_bounds__(DEP_THREADS, SP == 3 && TT == 0 ? 2 : SP == 3 || TT
     }
     int any_full = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) any_full |= full[w];
-    const bool dense = __builtin_amdgcn_readfirstlane(any_full) != 0;
+    for (int w = 0; w < NW; ++w) any_full |= over[w];
+    any_full = __builtin_amdgcn_readfirstlane(any_full);
+    const bool dense = any_full & 1;
     // species s's table into slot t of the tables
     auto build = [&](int s, int t) {
       if (!cells) return;
@@ -296,7 +360,8 @@ __global__ __launch_bounds__(DEP_THREADS, SP == 3 && TT == 0 ? 2 : SP == 3 || TT
       for (int k = 0; k < KMAX; ++k) {
         const int e = e0 + k;
         if (k < K && e < NE) {
-          const int ex = e % E, ey = (e / E) % E, ez = e / (E * E);
+          int ex, ey, ez;
+          split(e, ex, ey, ez);
           // slot of the cell's first node per axis, a signed byte each: -r + 1 .. R
           const uint32_t ox = (uint32_t)((ex - 1) * r + 1) & 255u,
                          oy = (uint32_t)((ey - 1) * r + 1) & 255u,
@@ -380,22 +445,22 @@ __global__ __launch_bounds__(DEP_THREADS, SP == 3 && TT == 0 ? 2 : SP == 3 || TT
       marks_done(t, nw);
       load(s, t, rb, nw, B);
     };
-    uint32_t got = 0;  // PB = 1: particles that this thread added
-    double units = 0.0;  // PB = 2: weight units
-    auto add = [&](auto* to, const Batch& B) {
+    uint64_t units = 0;  // weight units that this thread added
+    auto narrow = [&](uint32_t* to) {
+      return [&units, to, r, Rp](CT code, uint32_t org) {
+        units += dep_add<PB>(to, code, org, r, Rp);
+      };
+    };
+    auto add = [&](const Batch& B, auto put) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint32_t w = dep_add<PB>(to, B.code[u], B.org[u], r, Rp);
-        if constexpr (PB == 1) got += w >> 27;
-        else units += (double)w;
-      }
+      for (int u = 0; u < U; ++u) put(B.code[u], B.org[u]);
     };
     // the windows of species s from rb on
-    auto rest = [&](int s, int t, auto* to, int rb) {
+    auto rest = [&](int s, int t, int rb, auto put) {
       for (; rb < (s ? np[1] : np[0]) && rb >= 0; rb += WIN) {
         Batch B;
         window(s, t, rb, B);
-        add(to, B);
+        add(B, put);
       }
     };
 
@@ -412,72 +477,66 @@ __global__ __launch_bounds__(DEP_THREADS, SP == 3 && TT == 0 ? 2 : SP == 3 || TT
         Batch B0, B1;
         load(0, 0, 0, n0, B0);
         if (SP != 1) load(ns - 1, 1, 0, n1, B1);
-        add(node, B0);
-        if (SP != 1) add(node + NS, B1);
-        rest(0, 0, node, WIN);
-        if (SP != 1) rest(1, 1, node + NS, WIN);
+        add(B0, narrow(node));
+        if (SP != 1) add(B1, narrow(node + NS));
+        rest(0, 0, WIN, narrow(node));
+        if (SP != 1) rest(1, 1, WIN, narrow(node + NS));
       }
     } else if (!dense) {
       build(0, 0);
-      rest(0, 0, node, 0);
+      rest(0, 0, 0, narrow(node));
       if (SP != 1 && ns > 1) {
         __syncthreads();
         build(1, 0);
-        rest(1, 0, node + NS, 0);
+        rest(1, 0, 0, narrow(node + NS));
       }
     }
     __syncthreads();
     // Where a sum passes 2^32 (a node of 32 particles' weight), the total falls short of the
     // weights added.
     const double unit0 = A.sp[s0].unit, unit1 = ns > 1 ? A.sp[s0 + 1].unit : 0.0;
-    double sum = 0.0;
-    float dens[NPT];
+    uint64_t all = 0;
+    if (any_full) {
+      uint64_t sum = 0;
 #pragma unroll
-    for (int k = 0; k < NPT; ++k) {
-      const int i = threadIdx.x + k * NT;
-      uint32_t v0 = 0, v1 = 0;
-      if (i < NS) {
-        v0 = node[i];
-        if (SP != 1) v1 = node[NS + i];  // 0 without a second species
+      for (int k = 0; k < (dep_slots(16) + NT - 1) / NT; ++k) {
+        const int i = threadIdx.x + k * NT;
+        if (i < NS) {
+          sum += node[i];
+          if (SP != 1) sum += node[NS + i];  // 0 without a second species
+        }
       }
-      const double w0 = (double)v0, w1 = (double)v1;
-      sum += w0 + w1;
-      dens[k] = (MORE ? racc[k] : 0.0f) + (float)(w0 * unit0);
-      if (SP != 1) dens[k] += (float)(w1 * unit1);
+      sum = wave_sum_dpp(units - sum);
+      if (lane == 63) lost[wv] = sum;
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < NW; ++w) all += lost[w];
     }
-    if constexpr (PB == 1) units = (double)got * 0x1p27;
-    sum = wave_sum_dpp(units - sum);
-    if (lane == 63) lost[wv] = sum;
-    __syncthreads();
-    double all = 0.0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) all += lost[w];
-    if (all == 0.0 && !dense) {
-#pragma unroll
-      for (int k = 0; k < NPT; ++k) racc[k] = dens[k];
+    if (all == 0 && !dense) {
+      each([&](int k, int slot, int) {
+        racc[k] += (float)((double)node[slot] * unit0);
+        if (SP != 1) racc[k] += (float)((double)node[NS + slot] * unit1);
+      });
     } else {
-      // again, one species at a time in 64-bit sums over both arrays
-      unsigned long long* wide = (unsigned long long*)node;
-      if constexpr (!MORE)
-#pragma unroll
-        for (int k = 0; k < NPT; ++k) racc[k] = 0.0f;
+      // again, one species at a time in 64-bit sums
 #pragma unroll
       for (int s = 0; s < SB; ++s) {
         if (s >= ns) break;
         __syncthreads();
-        for (int i = threadIdx.x; i < 2 * NS; i += NT) node[i] = 0;
+        for (int i = threadIdx.x; i < (SP == 1 ? 2 * R * R * R : 2 * NS); i += NT) node[i] = 0;
         if (TABS == 1) {
           if (cells) fetch();
           build(s, 0);
         }
-        rest(s, TABS == 2 ? s : 0, wide, 0);
+        rest(s, TABS == 2 ? s : 0, 0, [&](CT code, uint32_t org) {
+          if constexpr (SP == 1) dep_add_own<PB>(wide, code, org, r, lgR);
+          else dep_add<PB>(wide, code, org, r, Rp);
+        });
         __syncthreads();
         const double unit = s ? unit1 : unit0;
-#pragma unroll
-        for (int k = 0; k < NPT; ++k) {
-          const int i = threadIdx.x + k * NT;
-          if (i < NS) racc[k] += (float)((double)wide[i] * unit);
-        }
+        each([&](int k, int slot, int own) {
+          racc[k] += (float)((double)wide[SP == 1 ? own : slot] * unit);
+        });
       }
     }
     if (MORE && s0 + 2 < n_sp) {  // the next pair's sums start at 0
@@ -485,40 +544,20 @@ __global__ __launch_bounds__(DEP_THREADS, SP == 3 && TT == 0 ? 2 : SP == 3 || TT
       for (int i = threadIdx.x; i < 2 * NS; i += NT) node[i] = 0;
     }
   }
-  // the slots' densities through LDS into rows of the mesh
-  float* out = (float*)node;
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < NPT; ++k) {
-    const int i = threadIdx.x + k * NT;
-    if (i < NS) out[i] = racc[k];
-  }
-  __syncthreads();
+  if (!own) return;
   const int64_t ng = g.ng;
-  if (TT) {
-    // R = 16: four consecutive nodes x = 4 (tid % 4) .. of row y = tid / 4 % 16, planes
-    // tid / 64 + NW k
-    const int lx = 4 * (threadIdx.x & 3), ly = (threadIdx.x >> 2) & 15;
-    const bool aligned = ((uintptr_t)rho & 15) == 0;  // the caller's pointer: any float
+  float* d = rho + (((int64_t)tz * R + lz) * ng + (int64_t)ty * R + ly) * ng + (int64_t)tx * R + lx;
+  if (!full) {
+    *d = racc[0];
+    return;
+  }
+  const bool aligned = ((uintptr_t)rho & 15) == 0;  // the caller's pointer: any float
 #pragma unroll
-    for (int k = 0; k < 16 / NW; ++k) {
-      const int lz = (threadIdx.x >> 6) + NW * k;
-      const float* q = out + ((lz + 1) * 17 + ly + 1) * 17 + lx + 1;
-      float* d = rho + (((int64_t)tz * 16 + lz) * ng + (int64_t)ty * 16 + ly) * ng +
-                 (int64_t)tx * 16 + lx;
-      if (aligned) {
-        *(float4*)d = make_float4(q[0], q[1], q[2], q[3]);
-      } else {
-        for (int a = 0; a < 4; ++a) d[a] = q[a];
-      }
-    }
-  } else {
-    const int R3 = R * R * R;
-    for (int i = threadIdx.x; i < R3; i += NT) {
-      const int lx = i % R, ly = (i / R) % R, lz = i / (R * R);
-      const int64_t gx = (int64_t)tx * R + lx, gy = (int64_t)ty * R + ly,
-                    gz = (int64_t)tz * R + lz;
-      rho[(gz * ng + gy) * ng + gx] = out[((lz + 1) * Rp + ly + 1) * Rp + lx + 1];
+  for (int k = 0; k < NPT / 4; ++k, d += (int64_t)NW * ng * ng) {
+    if (aligned) {
+      *(float4*)d = make_float4(racc[4 * k], racc[4 * k + 1], racc[4 * k + 2], racc[4 * k + 3]);
+    } else {
+      for (int a = 0; a < 4; ++a) d[a] = racc[4 * k + a];
     }
   }
 }
@@ -594,6 +633,8 @@ pm_status run_deposit_tile(pm_context* c, const pm_species* sp, int n_sp,
   if (A.R > 16) return PM_ERR_SHAPE;  // at most 16 nodes per thread
   const int nt = (int)(g.nc / A.T);  // a power of two, as nc and T are
   while ((1 << A.lgt) < nt) ++A.lgt;
+  while ((1 << A.lgR) < A.R) ++A.lgR;
+  A.rE = (65536u + (uint32_t)A.T) / (uint32_t)(A.T + 1);
   const int ne = (A.T + 1) * (A.T + 1) * (A.T + 1);
   ProfScope ps(c, ST_DEPOSIT);
   const unsigned grid = (unsigned)((int64_t)nt * nt * nt);
@@ -602,13 +643,12 @@ pm_status run_deposit_tile(pm_context* c, const pm_species* sp, int n_sp,
   if (kind < 0) return PM_ERR_ARG;
   auto launch = [&](auto tt, auto pb) {
     constexpr int TT = decltype(tt)::value, PB = decltype(pb)::value;
-    const size_t lds = dep_lds_bytes<TT>(A.R, ne);
-    auto go = [&](auto kernel) {
+    auto go = [&](auto kernel, size_t lds) {
       hipLaunchKernelGGL(kernel, dim3(grid), dim3(DEP_THREADS), lds, c->stream, A, g, rho);
     };
-    if (A.n_sp > 2) go(k_deposit_tile<TT, PB, 3>);
-    else if (A.n_sp == 2) go(k_deposit_tile<TT, PB, 2>);
-    else go(k_deposit_tile<TT, PB, 1>);
+    if (A.n_sp > 2) go(k_deposit_tile<TT, PB, 3>, dep_lds_bytes<TT, 3>(A.R, ne));
+    else if (A.n_sp == 2) go(k_deposit_tile<TT, PB, 2>, dep_lds_bytes<TT, 2>(A.R, ne));
+    else go(k_deposit_tile<TT, PB, 1>, dep_lds_bytes<TT, 1>(A.R, ne));
   };
   if (width_pos(sp[0]) == 1) {
     if (A.T == 4 && A.r == 4) launch(IC<4>{}, IC<1>{});
