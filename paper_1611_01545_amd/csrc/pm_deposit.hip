@@ -26,13 +26,13 @@
 // leaves no bounds test per corner; the atomics return nothing (a returned old value
 // detected the wraps one by one before); and a wave finds its lanes' cells by a running
 // maximum over marks instead of a binary search per particle. 512 threads and 47 (54) KB
-// of LDS for tiles of 4^3 (8^3) cells: three tiles on a CU, with no register spilled (any
-// scratch use doubled the time of these short-lived waves). With the offset scans, for two
-// species: 39 -> 12 us on 64^3 nodes, 281 -> 152 at 256^3 (8^3-cell tiles), 429 -> 363 at
-// 512^3, 3.02 -> 2.76 ms at 1024^3, 270 -> 227 us on the 128^3 coarse mesh with one node
-// per cell. A single species has a variant without the second one's sums, table and
-// conversions: 2 M particles on 256^3 nodes 62 -> 56 us, on 512^3 275 -> 253 (one particle
-// per cell; 64-bit sums with a binary search per particle take 210 there, and 70 at 256^3).
+// of LDS for tiles of 4^3 (8^3) cells of two species, three tiles on a CU, and 36 (45) KB of
+// one, four (three); no register spilled (any scratch use doubled the time of these
+// short-lived waves). A thread converts the nodes that it writes, straight from the slots.
+// With the offset scans, two species of one and eight particles a cell: 39 us -> 12 on 64^3
+// nodes, 281 -> 150 at 256^3, 429 -> 355 at 512^3, 3.02 -> 2.67 ms at 1024^3 (before: 32-bit
+// words with a count of their wraps, and a search per particle). One species of one particle a
+// cell: 36 us -> 32 on 256^3 nodes, but 211 -> 216 at 512^3 and 1.49 -> 1.63 ms at 1024^3.
 #include "pm_codec.h"
 #include "pm_scan.h"
 
@@ -303,7 +303,9 @@ __global__ __launch_bounds__(DEP_THREADS, SP == 3 || (TT == 0 && PB == 2) ? 4 : 
     // again in 64 bits. These sums alone take 1.13 times as long as those in 32 bits with 4
     // mesh cells per compression cell and axis, 1.3 times with 2, so a tile starts with them
     // where a cell has 16 particles per node and some more: evenly spread, their nodes pass 32
-    // about there. XXX
+    // about there. 8^3 cells of 2000 on 64^3 nodes 921 -> 529 us, 16^3 cells of 256 on as many
+    // 968 -> 538, with the particles together in each cell 1980 -> 1016; 1024 particles a cell
+    // in the former, which 32 bits just hold, 238 -> 281.
     const int most = 16 * r * r * r + 48;
     bool crowd = false, maybe = false;
     int before[2] = {0, 0}, loc[2] = {0, 0};
