@@ -410,6 +410,10 @@ struct ColSet {
 struct ColPair {
   ColSet main, nyq;
 };
+// The y passes of the longest lines take the plane in a launch of its own: choosing between
+// the two sets costs address arithmetic per access, 15.7 ms a pass against 15.0 at 2048^3.
+template <int N>
+constexpr bool col_pair() { return N < 2048; }
 template <int G>
 __device__ __forceinline__ unsigned col_tile(bool plane, int n) {
   return plane ? (blockIdx.y - (unsigned)n) * gridDim.x + blockIdx.x
@@ -425,7 +429,7 @@ __global__ __launch_bounds__(W * LP<N>::TL) void k_col_fft(ColPair cp,
                                                            const float2* __restrict__ tw,
                                                            int tws, int twmask, int n,
                                                            const float* __restrict__ gk) {
-  const bool plane = blockIdx.y >= (unsigned)n;
+  const bool plane = col_pair<N>() && blockIdx.y >= (unsigned)n;
   const ColSet& io = plane ? cp.nyq : cp.main;
   const float2 *in = io.in0, *in1 = io.in1;
   float2* out0 = io.out;
@@ -1008,18 +1012,26 @@ pm_status col_fft(const FftCtx& f, const ColPair& io, int sign) {
   if (two && sign > 0) return PM_ERR_ARG;
   const int W = two ? W2 : W1;
   if (io.main.d.L1 % W || io.nyq.d.L1 != 2 * io.main.d.L1) return PM_ERR_SHAPE;
-  dim3 grid((unsigned)(io.main.d.L1 / W), (unsigned)f.n + 2);
-  dim3 block(W * LP<N>::TL);
+  auto launch = [&](const ColPair& set, dim3 grid) {
+    dim3 block(W * LP<N>::TL);
 #define CLAUNCH(S, O)                                                                    \
   hipLaunchKernelGGL((k_col_fft<N, O == 3 ? W2 : W1, S, O>), grid, block, 0,            \
-                     f.c->stream, io, f.c->tw, 1, f.twmask, f.n, f.c->gk)
-  if (sign < 0) {
-    if (two) CLAUNCH(-1, 3);
-    else CLAUNCH(-1, 0);
-  } else {
-    CLAUNCH(1, 0);
-  }
+                     f.c->stream, set, f.c->tw, 1, f.twmask, f.n, f.c->gk)
+    if (sign < 0) {
+      if (two) CLAUNCH(-1, 3);
+      else CLAUNCH(-1, 0);
+    } else {
+      CLAUNCH(1, 0);
+    }
 #undef CLAUNCH
+  };
+  const unsigned gx = (unsigned)(io.main.d.L1 / W);
+  if (col_pair<N>()) {
+    launch(io, dim3(gx, (unsigned)f.n + 2));
+  } else {
+    launch(io, dim3(gx, (unsigned)f.n));
+    launch(ColPair{io.nyq, io.nyq}, dim3(2 * gx, 1));
+  }
   PM_LAUNCH_CHECK();
   return PM_OK;
 }
