@@ -774,7 +774,8 @@ __global__ __launch_bounds__(rows_per_wg<M>() * Plan<M>::T) void k_row_c2r(
 // neighbouring rows and walks GZ planes along z with a window of five planes in
 // registers; the rows' y and x neighbours in the current plane come through the L1, so
 // there is no LDS tile and no barrier and a wave waits only for its own loads. Folds
-// max |a| into *amax (float bits, cleared by the forward row pass), one atomic per block.
+// max |a| into *amax (float bits, cleared by the forward row pass): at most one atomic per
+// block, none where the word holds a larger value already.
 constexpr int GRAD_T = 256;
 struct GradTile {
   int xw;       // threads along x (4 nodes each)
@@ -884,7 +885,10 @@ __global__ __launch_bounds__(GRAD_T) void k_grad4(const float* __restrict__ phi,
 // The maximum alone is bound by the rows' neighbours out of the L2 (about 2.5 reads per
 // node): at 1024^3 1.25 ms with 4 rows and 8 planes against 1.33 with 4 planes, 1.29 with 2
 // rows, 1.71 with 1 (3.38 with the stores); at 512^3 187 us with 2 rows and 4 planes against
-// 207 with 4 rows and 2 planes, 204 with 8, 235 with 1 row.
+// 207 with 4 rows and 2 planes, 204 with 8, 235 with 1 row. At 2048^3 a plane of 16 MB leaves
+// the L2 before the next workgroup refills its window from it: 30.7 ms at GZ = 4 with the
+// stores, 28.3 at 8, 27.1 at 32, 27.3 at 64 (26.2 with the LDS tile, which had 64), the
+// maximum alone 10.7 at 8, 9.6 at 32.
 GradTile grad_tile(int64_t n, bool max_only) {
   GradTile t;
   t.xw = (int)std::min<int64_t>(n / 4, 64);
@@ -894,6 +898,7 @@ GradTile grad_tile(int64_t n, bool max_only) {
     t.ry = n >= 1024 ? 4 : 2;
     t.gz = n >= 1024 ? 8 : 4;
   }
+  if (n >= 2048) t.gz = 32;
   t.yg = (int)std::min<int64_t>(GRAD_T / t.xw, n / t.ry);
   t.threads = (t.xw * t.yg + 63) / 64 * 64;
   t.blocks = (n / (4 * t.xw)) * (n / (t.yg * t.ry)) * (n / t.gz);
