@@ -838,7 +838,7 @@ struct PlaceArgs {
   int apad;
 };
 constexpr int ET = 4096;
-constexpr int64_t APAD_WORDS = 1 << 20;
+constexpr int64_t APAD_LEAST = 1 << 16, APAD_MOST = 1 << 20;
 
 // First new stream position and first arrival of every brick: exclusive prefixes of the
 // bricks' new particle counts (old particles less movers plus arrivals) and of their
@@ -1572,11 +1572,17 @@ static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_speci
   uint32_t* cnt = (uint32_t*)scratch(c, SC_CNT, (size_t)g.ncell3 * 4 * n_sp);
   int64_t* bstart = (int64_t*)scratch(c, SC_OFF2, (size_t)(nbrick + 1) * 8 * n_sp);
   uint32_t* astart = (uint32_t*)scratch(c, SC_ASTART, (size_t)(nbrick + 1) * 4 * n_sp);
-  // Arrival counters in cache lines of their own up to 4 MB: atomics on one line follow one
-  // another. 4096 bricks, 16.8 M particles of which few leave them: listing 131 -> 34 us; all
-  // leave: listing 2580 -> 540, kick 2550 -> 930. 32768 bricks, all leave: kick 1425 -> 735.
+  // Arrival counters in cache lines of their own: atomics on one line follow one another. 4096
+  // bricks, 16.8 M particles of which few leave them: listing 131 -> 34 us; all leave: listing
+  // 2580 -> 540, kick 2550 -> 930. 32768 bricks, all leave: kick 1425 -> 735. But a line for few
+  // arrivals costs more than it spares (32768 bricks of 64 particles, all leave: listing 48 us
+  // side by side, 83 with 16 words' distance): 4 MB of them from 256 particles a brick on, else
+  // 256 KB.
+  int64_t most = 0;
+  for (int s = 0; s < n_sp; ++s) most = std::max(most, in[s].n);
+  const int64_t awords = most >= 256 * nbrick ? APAD_MOST : APAD_LEAST;
   int apad = 0;
-  while (apad < 5 && nbrick << (apad + 1) <= APAD_WORDS) ++apad;
+  while (apad < 5 && nbrick << (apad + 1) <= awords) ++apad;
   // what every call clears: the arrival counters, and per species the escapes' tiles and total
   // and the numbers of bricks that k_place leaves
   const int64_t ntile = cdiv(nbrick, ET);
