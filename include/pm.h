@@ -168,7 +168,7 @@ const char* pm_status_str(pm_status s);
 
 /* Device memory of a configuration, for planning (host only, no GPU call). Bytes:
  *   context_bytes     what pm_create allocates (kernel tables, twiddles, gradient
- *                     symbol, Nyquist planes), exact;
+ *                     symbol, Nyquist planes, 1 MB for pm_unpack), exact;
  *   step_mesh_bytes   the context's force meshes (3 n_mesh^3 floats, allocated by the
  *                     first pm_step, pm_step_vjp or pm_loss_density_vjp), exact;
  *   step_scratch_bytes  upper bound of the scratch that pm_encode and pm_step (also

@@ -1549,8 +1549,7 @@ static bool pair_shape(const Geom& g) {
 
 bool kick_takes_phi(const pm_context* c) { return pair_shape(c->g); }
 
-// All species of a compressed state: one brick kernel launch, then the re-sort of each
-// species. offs[s]: input cell offsets; perm[s] (device int64 [n], nullable): new stream
+// All species of a compressed state: one brick kernel launch, then one re-sort. offs[s]: input cell offsets; perm[s] (device int64 [n], nullable): new stream
 // position -> old stream position. P, V: the species' code widths.
 template <int P, int V>
 static pm_status kick_compressed_t(pm_context* c, const pm_species* in, pm_species* out,
