@@ -17,7 +17,7 @@ def _templates():
     for path in glob.glob(os.path.join(CSRC, "*.hip")):
         with open(path) as f:
             text = f.read()
-        for m in re.finditer(r"(?:template <([^>]*)>\s*)?(?:static )?__global__[^;{]*?void\s+(k_\w+)\s*\(",
+        for m in re.finditer(r"(?:template <([^>]*)>\s*(?://[^\n]*\s*)*)?(?:static )?__global__[^;{]*?void\s+(k_\w+)\s*\(",
                              text):
             found[m[2]] = len(m[1].split(",")) if m[1] else 0
     return found
