@@ -608,8 +608,9 @@ struct UnpackTile {
 template <int P, int V>
 __global__ __launch_bounds__(T256) void k_unpack_cells(const uint8_t* b, int64_t at,
                                                       int64_t end, const UnpackTile* tiles,
-                                                      int64_t cell0, int64_t ncell, GetCount counts, void* pos_,
-                                                      void* vel_, pm_shdr* h) {
+                                                      int64_t cell0, int64_t ncell,
+                                                      GetCount counts, void* pos_, void* vel_,
+                                                      pm_shdr* h) {
   constexpr int RB = 3 * (P + V);
   typename PosCode<P>::T* pos = (typename PosCode<P>::T*)pos_;
   typename VelCode<V>::T* vel = (typename VelCode<V>::T*)vel_;

@@ -13,8 +13,8 @@
 // and the force a = -D phi (eq. (3)), D the fourth-order central difference, is one
 // stencil pass over phi (k_grad4) that also takes max |a| for the velocity bound of the
 // re-encode: 6 launches moving 52 n^3 bytes, or 40 n^3 where the kick takes the differences
-// at its particles itself and the pass only finds the maximum. The stencil is the exact real-space form of
-// the spectral factor -i D(k_a), D(k) its symbol (which is zero on the Nyquist index).
+// at its particles itself and the pass only finds the maximum. The stencil is the exact
+// real-space form of the spectral factor -i D(k_a), D(k) its symbol (which is zero on the Nyquist index).
 // The transposed force (adjoint) applies that factor in the spectrum, in the y and z
 // passes. The 1/n^3 of the inverse transform is folded into the kernel table.
 //
