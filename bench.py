@@ -54,140 +54,140 @@ WORKLOAD_TEXT = {
 # taken on (sha256 over `sources`); otherwise the traffic is reported as null.
 MEASURED_TRAFFIC = {
     ("deposit", "tile_1024"): {
-        "kernel": "k_deposit_tile<4, 1>",
+        "kernel": "k_deposit_tile<4, 1, 2>",
         "sources": ["paper_1611_01545_amd/csrc/pm_deposit.hip",
                     "paper_1611_01545_amd/csrc/pm_common.h",
                     "paper_1611_01545_amd/csrc/pm_codec.h",
                     "paper_1611_01545_amd/csrc/pm_scan.h"],
-        "sha256": "b9a87e867dd2bf2cbf2a0cc2afdd62c96ded767a8296bfd572bb2c7e4006dc23",
-        "fetch_kib": 509670.50, "fetch_factor": 1.99992,
-        "write_kib": 4195298.69, "write_factor": 1.0,
+        "sha256": "d89e0eaafbc68efa1622df820c51f1f744f72c150aa2a7ba58772a6a97b96f57",
+        "fetch_kib": 509672.69, "fetch_factor": 1.99992,
+        "write_kib": 4194841.62, "write_factor": 1.0,
     },
     ("fft_x_r2c", "tile_1024"): {
-        "kernel": "k_row_r2c<512>",
+        "kernel": "k_row_r2c<512, false>",
         "sources": ["paper_1611_01545_amd/csrc/pm_fft.hip",
                     "paper_1611_01545_amd/csrc/pm_common.h"],
-        "sha256": "4e4f6cc89a2e2681720fffdfb260f2762f1fff1ff8fe8c7ac1a081a52cac4a3a",
-        "fetch_kib": 2097307.62, "fetch_factor": 1.99992,
-        "write_kib": 4202753.28, "write_factor": 1.0,
+        "sha256": "3cd7cbb571701267b9d46690f8f901d3cd1eb372a543da58f42a70c6efaba7ed",
+        "fetch_kib": 2097407.88, "fetch_factor": 1.99992,
+        "write_kib": 4202751.81, "write_factor": 1.0,
     },
     ("fft_y_fwd", "tile_1024"): {
         "kernel": "k_col_fft<1024, 16, -1, 0>",
         "sources": ["paper_1611_01545_amd/csrc/pm_fft.hip",
                     "paper_1611_01545_amd/csrc/pm_common.h"],
-        "sha256": "4e4f6cc89a2e2681720fffdfb260f2762f1fff1ff8fe8c7ac1a081a52cac4a3a",
-        "fetch_kib": 2097320.19, "fetch_factor": 1.99992,
-        "write_kib": 4194304.00, "write_factor": 1.0,
+        "sha256": "3cd7cbb571701267b9d46690f8f901d3cd1eb372a543da58f42a70c6efaba7ed",
+        "fetch_kib": 2101671.19, "fetch_factor": 1.99992,
+        "write_kib": 4202497.50, "write_factor": 1.0,
     },
     ("fft_z", "tile_1024"): {
-        "kernel": "k_col_zconv<1024, 16, 0, true>",
+        "kernel": "k_col_zconv<1024, 16, 0>",
         "sources": ["paper_1611_01545_amd/csrc/pm_fft.hip",
                     "paper_1611_01545_amd/csrc/pm_common.h"],
-        "sha256": "4e4f6cc89a2e2681720fffdfb260f2762f1fff1ff8fe8c7ac1a081a52cac4a3a",
-        "fetch_kib": 2628255.31, "fetch_factor": 1.99992,
-        "write_kib": 4194304.00, "write_factor": 1.0,
+        "sha256": "3cd7cbb571701267b9d46690f8f901d3cd1eb372a543da58f42a70c6efaba7ed",
+        "fetch_kib": 2633832.94, "fetch_factor": 1.99992,
+        "write_kib": 4202496.00, "write_factor": 1.0,
     },
     ("fft_y_inv", "tile_1024"): {
         "kernel": "k_col_fft<1024, 16, 1, 0>",
         "sources": ["paper_1611_01545_amd/csrc/pm_fft.hip",
                     "paper_1611_01545_amd/csrc/pm_common.h"],
-        "sha256": "4e4f6cc89a2e2681720fffdfb260f2762f1fff1ff8fe8c7ac1a081a52cac4a3a",
-        "fetch_kib": 2097342.38, "fetch_factor": 1.99992,
-        "write_kib": 4194304.12, "write_factor": 1.0,
+        "sha256": "3cd7cbb571701267b9d46690f8f901d3cd1eb372a543da58f42a70c6efaba7ed",
+        "fetch_kib": 2101740.94, "fetch_factor": 1.99992,
+        "write_kib": 4202500.31, "write_factor": 1.0,
     },
     ("fft_x_c2r", "tile_1024"): {
         "kernel": "k_row_c2r<512>",
         "sources": ["paper_1611_01545_amd/csrc/pm_fft.hip",
                     "paper_1611_01545_amd/csrc/pm_common.h"],
-        "sha256": "4e4f6cc89a2e2681720fffdfb260f2762f1fff1ff8fe8c7ac1a081a52cac4a3a",
-        "fetch_kib": 2132485.69, "fetch_factor": 1.99992,
+        "sha256": "3cd7cbb571701267b9d46690f8f901d3cd1eb372a543da58f42a70c6efaba7ed",
+        "fetch_kib": 2132581.38, "fetch_factor": 1.99992,
         "write_kib": 4194304.00, "write_factor": 1.0,
     },
     ("force_grad", "tile_1024"): {
-        "kernel": "k_grad4",
+        "kernel": "k_grad4<4, 0>",
         "sources": ["paper_1611_01545_amd/csrc/pm_fft.hip",
                     "paper_1611_01545_amd/csrc/pm_common.h"],
-        "sha256": "4e4f6cc89a2e2681720fffdfb260f2762f1fff1ff8fe8c7ac1a081a52cac4a3a",
-        "fetch_kib": 4654232.88, "fetch_factor": 1.99992,
-        "write_kib": 12583241.62, "write_factor": 1.0,
+        "sha256": "3cd7cbb571701267b9d46690f8f901d3cd1eb372a543da58f42a70c6efaba7ed",
+        "fetch_kib": 4371941.81, "fetch_factor": 1.99992,
+        "write_kib": 1.19, "write_factor": 1.0,
     },
     ("interp_kick_drift", "tile_1024"): {
-        "kernel": "k_kick_pair<256, 4, 1, 2>",
+        "kernel": "k_kick_pair<256, 4, true, 1, 2>",
         "sources": ["paper_1611_01545_amd/csrc/pm_kick.hip",
                     "paper_1611_01545_amd/csrc/pm_common.h",
                     "paper_1611_01545_amd/csrc/pm_codec.h",
                     "paper_1611_01545_amd/csrc/pm_scan.h"],
-        "sha256": "b0a02528713e05ab4f8f47f7431efcc8e69725f6a97ff51bc2254cfa6440b90d",
-        "fetch_kib": 8184960.06, "fetch_factor": 1.99992,
-        "write_kib": 2258737.00, "write_factor": 1.0,
+        "sha256": "4b0f01d895b92e43c052420d97968f40e7bbc0212bbfcd8d9c41badfab448305",
+        "fetch_kib": 3659460.50, "fetch_factor": 1.99992,
+        "write_kib": 2118058.03, "write_factor": 1.0,
     },
     ("deposit", "large_2048"): {
-        "kernel": "k_deposit_tile<4, 1>",
+        "kernel": "k_deposit_tile<4, 1, 2>",
         "sources": ["paper_1611_01545_amd/csrc/pm_deposit.hip",
                     "paper_1611_01545_amd/csrc/pm_common.h",
                     "paper_1611_01545_amd/csrc/pm_codec.h",
                     "paper_1611_01545_amd/csrc/pm_scan.h"],
-        "sha256": "b9a87e867dd2bf2cbf2a0cc2afdd62c96ded767a8296bfd572bb2c7e4006dc23",
-        "fetch_kib": 4074093.69, "fetch_factor": 1.99991,
-        "write_kib": 33555662.69, "write_factor": 1.0,
+        "sha256": "d89e0eaafbc68efa1622df820c51f1f744f72c150aa2a7ba58772a6a97b96f57",
+        "fetch_kib": 4077309.50, "fetch_factor": 1.99993,
+        "write_kib": 33555665.31, "write_factor": 1.0,
     },
     ("fft_x_r2c", "large_2048"): {
-        "kernel": "k_row_r2c<1024>",
+        "kernel": "k_row_r2c<1024, false>",
         "sources": ["paper_1611_01545_amd/csrc/pm_fft.hip",
                     "paper_1611_01545_amd/csrc/pm_common.h"],
-        "sha256": "4e4f6cc89a2e2681720fffdfb260f2762f1fff1ff8fe8c7ac1a081a52cac4a3a",
-        "fetch_kib": 16778414.75, "fetch_factor": 1.99991,
-        "write_kib": 33587757.28, "write_factor": 1.0,
+        "sha256": "3cd7cbb571701267b9d46690f8f901d3cd1eb372a543da58f42a70c6efaba7ed",
+        "fetch_kib": 16778410.12, "fetch_factor": 1.99993,
+        "write_kib": 33587740.66, "write_factor": 1.0,
     },
     ("fft_y_fwd", "large_2048"): {
         "kernel": "k_col_fft<2048, 16, -1, 0>",
         "sources": ["paper_1611_01545_amd/csrc/pm_fft.hip",
                     "paper_1611_01545_amd/csrc/pm_common.h"],
-        "sha256": "4e4f6cc89a2e2681720fffdfb260f2762f1fff1ff8fe8c7ac1a081a52cac4a3a",
-        "fetch_kib": 16817661.50, "fetch_factor": 1.99991,
+        "sha256": "3cd7cbb571701267b9d46690f8f901d3cd1eb372a543da58f42a70c6efaba7ed",
+        "fetch_kib": 16817790.44, "fetch_factor": 1.99993,
         "write_kib": 33554432.00, "write_factor": 1.0,
     },
     ("fft_z", "large_2048"): {
-        "kernel": "k_col_zconv<2048, 16, 0, true>",
+        "kernel": "k_col_zconv<2048, 16, 0>",
         "sources": ["paper_1611_01545_amd/csrc/pm_fft.hip",
                     "paper_1611_01545_amd/csrc/pm_common.h"],
-        "sha256": "4e4f6cc89a2e2681720fffdfb260f2762f1fff1ff8fe8c7ac1a081a52cac4a3a",
-        "fetch_kib": 24430745.19, "fetch_factor": 1.99991,
-        "write_kib": 41418787.88, "write_factor": 1.0,
+        "sha256": "3cd7cbb571701267b9d46690f8f901d3cd1eb372a543da58f42a70c6efaba7ed",
+        "fetch_kib": 24791985.31, "fetch_factor": 1.99993,
+        "write_kib": 41459230.38, "write_factor": 1.0,
     },
     ("fft_y_inv", "large_2048"): {
         "kernel": "k_col_fft<2048, 16, 1, 0>",
         "sources": ["paper_1611_01545_amd/csrc/pm_fft.hip",
                     "paper_1611_01545_amd/csrc/pm_common.h"],
-        "sha256": "4e4f6cc89a2e2681720fffdfb260f2762f1fff1ff8fe8c7ac1a081a52cac4a3a",
-        "fetch_kib": 16816735.56, "fetch_factor": 1.99991,
+        "sha256": "3cd7cbb571701267b9d46690f8f901d3cd1eb372a543da58f42a70c6efaba7ed",
+        "fetch_kib": 16816613.81, "fetch_factor": 1.99993,
         "write_kib": 33554432.00, "write_factor": 1.0,
     },
     ("fft_x_c2r", "large_2048"): {
         "kernel": "k_row_c2r<1024>",
         "sources": ["paper_1611_01545_amd/csrc/pm_fft.hip",
                     "paper_1611_01545_amd/csrc/pm_common.h"],
-        "sha256": "4e4f6cc89a2e2681720fffdfb260f2762f1fff1ff8fe8c7ac1a081a52cac4a3a",
-        "fetch_kib": 16794199.69, "fetch_factor": 1.99991,
-        "write_kib": 33554432.50, "write_factor": 1.0,
+        "sha256": "3cd7cbb571701267b9d46690f8f901d3cd1eb372a543da58f42a70c6efaba7ed",
+        "fetch_kib": 16794187.44, "fetch_factor": 1.99993,
+        "write_kib": 33554432.25, "write_factor": 1.0,
     },
     ("force_grad", "large_2048"): {
-        "kernel": "k_grad4",
+        "kernel": "k_grad4<4, 0>",
         "sources": ["paper_1611_01545_amd/csrc/pm_fft.hip",
                     "paper_1611_01545_amd/csrc/pm_common.h"],
-        "sha256": "4e4f6cc89a2e2681720fffdfb260f2762f1fff1ff8fe8c7ac1a081a52cac4a3a",
-        "fetch_kib": 37783092.44, "fetch_factor": 1.99991,
-        "write_kib": 100666016.34, "write_factor": 1.0,
+        "sha256": "3cd7cbb571701267b9d46690f8f901d3cd1eb372a543da58f42a70c6efaba7ed",
+        "fetch_kib": 35122290.19, "fetch_factor": 1.99993,
+        "write_kib": 1.50, "write_factor": 1.0,
     },
     ("interp_kick_drift", "large_2048"): {
-        "kernel": "k_kick_pair<256, 4, 1, 2>",
+        "kernel": "k_kick_pair<256, 4, true, 1, 2>",
         "sources": ["paper_1611_01545_amd/csrc/pm_kick.hip",
                     "paper_1611_01545_amd/csrc/pm_common.h",
                     "paper_1611_01545_amd/csrc/pm_codec.h",
                     "paper_1611_01545_amd/csrc/pm_scan.h"],
-        "sha256": "b0a02528713e05ab4f8f47f7431efcc8e69725f6a97ff51bc2254cfa6440b90d",
-        "fetch_kib": 66441099.62, "fetch_factor": 1.99991,
-        "write_kib": 17960036.72, "write_factor": 1.0,
+        "sha256": "4b0f01d895b92e43c052420d97968f40e7bbc0212bbfcd8d9c41badfab448305",
+        "fetch_kib": 35430535.25, "fetch_factor": 1.99993,
+        "write_kib": 16920357.06, "write_factor": 1.0,
     },
 }
 
